@@ -21,6 +21,7 @@
 // TOTALS scan: stage 2 only, on the rank totals S(r,g).
 #include "ta_device.h"
 #include "ta_internal.h"
+#include "ta_select.h"
 
 namespace ta {
 namespace {
@@ -1653,8 +1654,12 @@ __device__ void block_select(int64_t R, const int32_t *it, int I, int64_t n, Key
 // the region instead of eight).
 constexpr int S2S = 4096;              // sample keys
 constexpr int S2CAP = 14336;           // interior keys held in LDS (112 KB)
-constexpr int64_t S2_MIN_N = 16384;    // fewer active ranks: radix passes only
+constexpr int64_t S2_MIN_N = 16384;    // fewer active ranks: radix passes only (regions
+                                       // above SEL_REG_MAX ranks come here)
 constexpr size_t S2_LDS_BYTES = (size_t)S2CAP * sizeof(uint64_t);
+// Regions of up to this many ranks are selected in registers (the most that 16
+// waves hold at 32 keys per lane); longer ones by the passes over memory.
+constexpr int64_t SEL_REG_MAX = 32768;
 
 // Appends v to buf (LDS) when `in`; all lanes of the wave call it together.
 // The counter keeps counting past cap (the caller detects the overflow).
@@ -2089,6 +2094,161 @@ __global__ __launch_bounds__(RT) void sel_regions(const void *vals_t, int64_t R,
   }
 }
 
+// Stage 2 of the robust kind over up to 64 * W * V ranks: one workgroup of W
+// waves per region, the region's keys in registers from one read to the
+// score.  Bound by latency (a chain of a few barriers per order statistic);
+// sel_regions' radix passes re-read every key from memory eight times per
+// order statistic and walk each histogram with one thread.  Measured, 16
+// regions: 16 ranks 174 -> 6.6 us, 64 ranks 163 -> 9.6 us; 32 regions of
+// 10,000 ranks 273 -> 44 us; 64 regions of 1,000 ranks 217 -> 14 us.
+template <int W, int V, bool F64>
+__global__ __launch_bounds__(64 * W) void sel_regions_reg(const void *vals_t, int64_t R, int G,
+                                                          const int32_t *it, int I, double *z_t,
+                                                          double *region_score) {
+  constexpr int NT = 64 * W;
+  constexpr int NB = W >= 8 ? 2048 : 1024;
+  __shared__ SelGroup<W, NB, uint64_t> L;
+  __shared__ uint64_t rmn[W], rmx[W];
+  __shared__ uint32_t rn[W];
+  __shared__ double fb[W];
+  __shared__ int64_t xacc[W * XL];
+  __shared__ uint32_t xbad;
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint64_t *raw = reinterpret_cast<const uint64_t *>(vals_t) + (int64_t)g * R;
+  uint64_t x[V];
+  uint32_t ok = 0;  // bit v: the lane's v-th rank is active
+  auto load = [&]() {
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      const int64_t r = (int64_t)v * NT + tid;
+      x[v] = r < R ? raw[r] : 0;
+    }
+  };
+  load();
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int64_t r = (int64_t)v * NT + tid;
+    if (r < R && rank_active(it, I, r)) ok |= 1u << v;
+  }
+  sel_clear(L);
+  uint32_t n = 0;
+  // The two middle values a <= b of key(x[v]) over the active ranks (equal for
+  // an odd count); x is left holding the keys.
+  auto middle = [&](auto key, uint64_t &a, uint64_t &b) {
+    uint64_t lo = ~0ull, hi = 0;
+    uint32_t c = (uint32_t)__popc(ok);
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      x[v] = key(x[v]);
+      if (ok >> v & 1) {
+        lo = x[v] < lo ? x[v] : lo;
+        hi = x[v] > hi ? x[v] : hi;
+      }
+    }
+    for (int d = 32; d >= 1; d >>= 1) {
+      const uint64_t ol = __shfl_xor(lo, d, 64), oh = __shfl_xor(hi, d, 64);
+      lo = ol < lo ? ol : lo;
+      hi = oh > hi ? oh : hi;
+      c += __shfl_xor(c, d, 64);
+    }
+    if (lane == 0) {
+      rmn[wid] = lo;
+      rmx[wid] = hi;
+      rn[wid] = c;
+    }
+    __syncthreads();
+    n = 0;
+    lo = ~0ull;
+    hi = 0;
+    for (int q = 0; q < W; q++) {
+      lo = rmn[q] < lo ? rmn[q] : lo;
+      hi = rmx[q] > hi ? rmx[q] : hi;
+      n += rn[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < V; v++) x[v] = ok >> v & 1 ? x[v] - lo : ~0ull;
+    reg_select<false>(L, x, ~(uint64_t)0, 0u, n > 0 ? nbits64(hi - lo) : 0, n, n > 0 ? (n - 1) / 2 : 0u,
+               n > 0 && (n & 1) == 0, a, b);
+    a += lo;
+    b += lo;
+  };
+  double med = 0.0, scale = 0.0;
+  int64_t med2 = 0;
+  int mode = 0;  // 1: MAD, 2: mean absolute deviation, 0: all z = 0
+  uint64_t a, b;
+  auto f64 = [](uint64_t u) { return __longlong_as_double((long long)u); };
+  if (F64) {
+    middle([&](uint64_t u) { return key_f64(f64(u)); }, a, b);
+    if (n > 0) {
+      med = (n & 1) ? dec_f64(a) : 0.5 * (dec_f64(a) + dec_f64(b));
+      load();
+      middle([&](uint64_t u) { return key_f64(fabs(f64(u) - med)); }, a, b);
+      const double mad = (n & 1) ? dec_f64(a) : 0.5 * (dec_f64(a) + dec_f64(b));
+      if (mad > 0.0) {
+        mode = 1;
+        scale = 1.4826 * mad;
+      } else {
+        xsum_clear<NT>(xacc, &xbad);
+        for (int64_t r0 = 0; r0 < R; r0 += NT) {
+          const int64_t r = r0 + tid;
+          const bool act = r < R && rank_active(it, I, r);
+          xsum_add_wave(xacc + wid * XL, act ? fabs(f64(raw[r]) - med) : 0.0, act, &xbad);
+        }
+        const double mean_ad = xsum_block_result<NT>(xacc, &xbad, fb) / (double)n;
+        if (mean_ad > 0.0) {
+          mode = 2;
+          scale = 1.253314 * mean_ad;
+        }
+      }
+    }
+  } else {
+    auto dev = [&](uint64_t u) {
+      const int64_t d = 2 * (int64_t)u - med2;
+      return (uint64_t)(d < 0 ? -d : d);
+    };
+    middle([&](uint64_t u) { return u ^ SIGN; }, a, b);
+    if (n > 0) {
+      med2 = (int64_t)(a ^ SIGN) + (int64_t)(b ^ SIGN);
+      load();
+      middle(dev, a, b);
+      const int64_t mad4 = (int64_t)(a + b);
+      if (mad4 > 0) {
+        mode = 1;
+        scale = 1.4826 * (double)mad4;
+      } else {
+        uint64_t s = 0;
+        for (int64_t r = tid; r < R; r += NT)
+          if (rank_active(it, I, r)) s += dev(raw[r]);
+        for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
+        if (lane == 0) rmn[wid] = s;
+        __syncthreads();
+        s = 0;
+        for (int q = 0; q < W; q++) s += rmn[q];
+        if (s > 0) {
+          mode = 2;
+          scale = 1.253314 * (double)s;
+        }
+      }
+    }
+  }
+  load();
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const int64_t r = (int64_t)v * NT + tid;
+    if (r < R) {
+      double z = 0.0;
+      if ((ok >> v & 1) && mode != 0) {
+        if (F64) z = (f64(x[v]) - med) / scale;
+        else if (mode == 1) z = (double)(4 * (int64_t)x[v] - 2 * med2) / scale;
+        else z = ((double)(2 * (int64_t)x[v] - med2) * (double)n) / scale;
+      }
+      z_t[(int64_t)g * R + r] = z;
+      if (region_score) region_score[r * G + g] = z;
+    }
+  }
+}
+
 // Per-rank maximum |z| over regions, flags, per-block flag counts.
 __global__ __launch_bounds__(256) void rank_final(const double *z_t, int64_t R, int G,
                                                   const int32_t *it, int I, double tau,
@@ -2098,11 +2258,13 @@ __global__ __launch_bounds__(256) void rank_final(const double *z_t, int64_t R, 
   int64_t f = 0;
   if (r < R) {
     double best = 0.0;
-    if (rank_active(it, I, r))
-      for (int g = 0; g < G; g++) {
+    if (rank_active(it, I, r)) {
+#pragma unroll 16
+      for (int g = 0; g < G; g++) {  // 16 loads in flight: 19 -> 6 us at 64 regions
         const double v = fabs(z_t[(int64_t)g * R + r]);
         if (v > best) best = v;
       }
+    }
     score[r] = best;
     f = best > tau ? 1 : 0;
     flag[r] = (uint8_t)f;
@@ -2357,6 +2519,18 @@ hipError_t scan_row_major(const OutArgs &a, const OWs &w, int IG, hipStream_t s)
 template <bool F64, bool MAD>
 void launch_sel_regions(const void *vals_t, int64_t R, int G, const int32_t *it, int I, double *z_t,
                         double *region_score, hipStream_t s) {
+  if (MAD && R <= SEL_REG_MAX) {
+    auto go = [&](auto kern, int nt) {
+      hipLaunchKernelGGL(kern, dim3(G), dim3(nt), 0, s, vals_t, R, G, it, I, z_t, region_score);
+    };
+    if (R <= 256) go(sel_regions_reg<4, 1, F64>, 256);
+    else if (R <= 1024) go(sel_regions_reg<4, 4, F64>, 256);
+    else if (R <= 4096) go(sel_regions_reg<8, 8, F64>, 512);
+    else if (R <= 8192) go(sel_regions_reg<16, 8, F64>, 1024);
+    else if (R <= 16384) go(sel_regions_reg<16, 16, F64>, 1024);
+    else go(sel_regions_reg<16, 32, F64>, 1024);
+    return;
+  }
   hipLaunchKernelGGL((sel_regions<F64, MAD>), dim3(G), dim3(RT), MAD ? S2_LDS_BYTES : 0, s, vals_t, R,
                      G, it, I, z_t, region_score);
 }

@@ -1,0 +1,199 @@
+// ta_select.h -- exact order statistics of keys held in registers.
+//
+// A group of W waves holds up to 64 * W * V unsigned keys, V per lane.  The
+// k-th smallest is found by most-significant-digit radix passes over the
+// registers: a histogram of the digit in LDS (one atomic per key that has the
+// prefix found so far), a scan of its bins on the VALU, and the bin of rank k
+// becomes the new prefix.  As soon as at most 64 keys share the prefix they are
+// gathered into one wave and ranked by comparison, so a spread column takes
+// one pass and not one per digit.  Nothing is read twice from memory.  Every
+// count is an integer, so the results do not depend on the order of the
+// atomics.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace ta {
+
+constexpr int SEL_FEW = 64;  // keys left for the comparison step: one per lane
+
+// LDS of one group: NB bins (bin b at b + b / (bins per thread), so that the
+// lanes' runs of bins start in different banks) and the exchange words.
+template <int W, int NB, typename K>
+struct SelGroup {
+  static constexpr int BPT = NB / (64 * W);  // bins per thread of the group
+  uint32_t hist[NB + 64 * W];
+  K few[SEL_FEW];
+  K above, r1, r2;
+  uint32_t wsum[W];
+  uint32_t bin, below, cnt, nfew;
+};
+
+// Orders the LDS accesses of the lanes of a group: a barrier of the workgroup,
+// or for groups of one wave (whose LDS operations complete in order) only a
+// barrier for the compiler.
+template <int W>
+__device__ __forceinline__ void group_sync() {
+  if (W == 1) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
+// Inclusive scan over the 64 lanes of a wave on the VALU (shifts within
+// 16-lane rows, then the row totals).
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
+}
+
+// The bins of a group start at zero and are left at zero by reg_select.
+template <int W, int NB, typename K>
+__device__ __forceinline__ void sel_clear(SelGroup<W, NB, K> &L) {
+  for (int j = (int)(threadIdx.x % (64 * W)); j < NB + 64 * W; j += 64 * W) L.hist[j] = 0;
+  group_sync<W>();
+}
+
+// The k-th smallest (k from 0, k < n) of a group's n keys u[] and, with `next`,
+// the (k+1)-th (k + 1 < n).  Keys are below 2^bits; an all-ones word is no key (it
+// sorts after every key, so it needs no test in the passes).
+// HOT: the hot_cnt keys equal to `hot`, which many values may share, were counted
+// by the caller and are added to their bin once instead of by that many atomics
+// on one address.  The keys are plain words in registers:
+// a key computed on the fly is kept in a second set of registers by the
+// compiler, across the passes.  Every thread of the workgroup calls this
+// (groups with W > 1 pass its barriers together); a group with n = 0 only
+// keeps the others company.
+template <bool HOT, int V, int W, int NB, typename K>
+__device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V], K hot, uint32_t hot_cnt,
+                                           int bits, uint32_t n, uint32_t k, bool next, K &r1, K &r2) {
+  constexpr int T = 64 * W, BPT = NB / T, KB = 8 * (int)sizeof(K);
+  constexpr int DB = __builtin_ctz(NB), LB = __builtin_ctz(BPT);
+  const int t = (int)(threadIdx.x % T), lane = t & 63, sw = t >> 6;
+  K pref = 0;
+  int lo = bits;
+  uint32_t cnt = n;
+  auto top = [&](K x, int s) -> K { return s >= KB ? (K)0 : (K)(x >> s); };
+  while (true) {
+    const bool more = lo > 0 && cnt > (uint32_t)SEL_FEW;
+    if (W == 1) {
+      if (!more) break;
+    } else if (!__syncthreads_or(more)) {
+      break;
+    }
+    const int w = lo < DB ? lo : DB, nlo = lo - w;
+    const K b0 = (K)(pref << w), nb = (K)1 << w;
+    if (more) {
+      K h = hot;
+      if (HOT) asm volatile("" : "+v"(h));  // keeps V lane masks from being carried across the passes
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        const K b = (K)(top(u[v], nlo) - b0);
+        if ((!HOT || u[v] != h) && b < nb) {
+          const uint32_t bb = (uint32_t)b;
+          atomicAdd(&L.hist[bb + (bb >> LB)], 1u);
+        }
+      }
+      if (HOT && hot_cnt && t == 0) {
+        const K b = (K)(top(hot, nlo) - b0);
+        if (b < nb) {
+          const uint32_t bb = (uint32_t)b;
+          atomicAdd(&L.hist[bb + (bb >> LB)], hot_cnt);
+        }
+      }
+    }
+    group_sync<W>();
+    uint32_t c[BPT], own = 0;
+#pragma unroll
+    for (int j = 0; j < BPT; j++) {
+      c[j] = L.hist[t * (BPT + 1) + j];
+      L.hist[t * (BPT + 1) + j] = 0;
+      own += c[j];
+    }
+    const uint32_t incl = wave_scan_u32(own);
+    uint32_t excl = incl - own;
+    if (W > 1) {
+      if (lane == 63) L.wsum[sw] = incl;
+      group_sync<W>();
+      for (int q = 0; q < sw; q++) excl += L.wsum[q];
+    }
+    if (more && excl <= k && k < excl + own) {
+      uint32_t cum = excl;
+      int j = 0;
+      bool go = true;
+#pragma unroll
+      for (int q = 0; q < BPT; q++) {
+        if (go && q + 1 < BPT && cum + c[q] <= k) {
+          cum += c[q];
+          j = q + 1;
+        } else if (go) {
+          go = false;
+          L.cnt = c[q];
+        }
+      }
+      L.bin = (uint32_t)(t * BPT + j);
+      L.below = cum;
+    }
+    group_sync<W>();
+    if (more) {
+      pref = (K)(b0 + L.bin);
+      k -= L.below;
+      cnt = L.cnt;
+      lo = nlo;
+    }
+  }
+  // At most SEL_FEW keys share the prefix, or it is a whole key (lo == 0).
+  const bool few = n > 0 && lo > 0;
+  const bool want_above = n > 0 && next && k + 1 >= cnt;
+  if (t == 0) {
+    L.nfew = 0;
+    L.above = ~(K)0;
+  }
+  group_sync<W>();
+  if (few || want_above) {
+    K m = ~(K)0;
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      const K x = u[v];
+      const K tp = top(x, lo);
+      if (x != ~(K)0) {
+        if (few && tp == pref) L.few[atomicAdd(&L.nfew, 1u)] = x;
+        else if (tp > pref && x < m) m = x;
+      }
+    }
+    if (want_above) {
+      for (int d = 32; d >= 1; d >>= 1) {
+        const K o = __shfl_xor(m, d, 64);
+        m = o < m ? o : m;
+      }
+      if (lane == 0) atomicMin(&L.above, m);
+    }
+  }
+  group_sync<W>();
+  if (few && sw == 0) {
+    const K x = lane < (int)cnt ? L.few[lane] : ~(K)0;
+    uint32_t rank = 0;
+    for (uint32_t j = 0; j < cnt; j++) {
+      const K y = L.few[j];
+      rank += (y < x || (y == x && (int)j < lane)) ? 1u : 0u;
+    }
+    if (lane < (int)cnt) {
+      if (rank == k) L.r1 = x;
+      if (rank == k + 1) L.r2 = x;
+    }
+  }
+  group_sync<W>();
+  r1 = few ? L.r1 : pref;
+  r2 = !next ? r1 : (want_above ? L.above : (few ? L.r2 : pref));
+}
+
+}  // namespace ta
