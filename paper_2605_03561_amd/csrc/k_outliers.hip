@@ -2168,8 +2168,8 @@ __global__ __launch_bounds__(64 * W) void sel_regions_reg(const void *vals_t, in
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < V; v++) x[v] = ok >> v & 1 ? x[v] - lo : ~0ull;
-    reg_select<false>(L, x, ~(uint64_t)0, 0u, n > 0 ? nbits64(hi - lo) : 0, n, n > 0 ? (n - 1) / 2 : 0u,
-               n > 0 && (n & 1) == 0, a, b);
+    reg_select<false>(L, x, ~(uint64_t)0, 0u, n > 0 ? hi - lo : 0, n > 0 ? nbits64(hi - lo) : 0, n,
+                      n > 0 ? (n - 1) / 2 : 0u, n > 0 && (n & 1) == 0, a, b);
     a += lo;
     b += lo;
   };

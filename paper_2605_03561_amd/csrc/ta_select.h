@@ -19,12 +19,11 @@ namespace ta {
 
 constexpr int SEL_FEW = 64;  // keys left for the comparison step: one per lane
 
-// LDS of one group: NB bins (bin b at b + b / (bins per thread), so that the
-// lanes' runs of bins start in different banks) and the exchange words.
+// LDS of one group: NB bins and the exchange words.
 template <int W, int NB, typename K>
 struct SelGroup {
   static constexpr int BPT = NB / (64 * W);  // bins per thread of the group
-  uint32_t hist[NB + 64 * W];
+  alignas(16) uint32_t hist[NB];
   K few[SEL_FEW];
   K above, r1, r2;
   uint32_t wsum[W];
@@ -59,66 +58,53 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
 // The bins of a group start at zero and are left at zero by reg_select.
 template <int W, int NB, typename K>
 __device__ __forceinline__ void sel_clear(SelGroup<W, NB, K> &L) {
-  for (int j = (int)(threadIdx.x % (64 * W)); j < NB + 64 * W; j += 64 * W) L.hist[j] = 0;
+  for (int j = (int)(threadIdx.x % (64 * W)); j < NB; j += 64 * W) L.hist[j] = 0;
   group_sync<W>();
 }
 
 // The k-th smallest (k from 0, k < n) of a group's n keys u[] and, with `next`,
-// the (k+1)-th (k + 1 < n).  Keys are below 2^bits; an all-ones word is no key (it
-// sorts after every key, so it needs no test in the passes).
-// HOT: the hot_cnt keys equal to `hot`, which many values may share, were counted
-// by the caller and are added to their bin once instead of by that many atomics
-// on one address.  The keys are plain words in registers:
-// a key computed on the fly is kept in a second set of registers by the
-// compiler, across the passes.  Every thread of the workgroup calls this
-// (groups with W > 1 pass its barriers together); a group with n = 0 only
-// keeps the others company.
+// the (k+1)-th (k + 1 < n).  Keys are at most `last`, which takes `bits` bits; a
+// word above `last` is no key (it sorts after every key, so the passes need no
+// test for it, and it can not be selected).  HOT: the hot_cnt keys equal to
+// `hot`, which many values may share, were counted by the caller and are added
+// to their bin once instead of by that many atomics on one address.  The keys
+// are plain words in registers: a key computed on the fly is kept in a second
+// set of registers by the compiler, across the passes.  A group of more than
+// one wave is a whole workgroup; all its threads call this.
 template <bool HOT, int V, int W, int NB, typename K>
 __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V], K hot, uint32_t hot_cnt,
-                                           int bits, uint32_t n, uint32_t k, bool next, K &r1, K &r2) {
+                                           K last, int bits, uint32_t n, uint32_t k, bool next, K &r1,
+                                           K &r2) {
   constexpr int T = 64 * W, BPT = NB / T, KB = 8 * (int)sizeof(K);
-  constexpr int DB = __builtin_ctz(NB), LB = __builtin_ctz(BPT);
+  constexpr int DB = __builtin_ctz(NB);
   const int t = (int)(threadIdx.x % T), lane = t & 63, sw = t >> 6;
   K pref = 0;
   int lo = bits;
   uint32_t cnt = n;
   auto top = [&](K x, int s) -> K { return s >= KB ? (K)0 : (K)(x >> s); };
-  while (true) {
-    const bool more = lo > 0 && cnt > (uint32_t)SEL_FEW;
-    if (W == 1) {
-      if (!more) break;
-    } else if (!__syncthreads_or(more)) {
-      break;
-    }
+  while (lo > 0 && cnt > (uint32_t)SEL_FEW) {
     const int w = lo < DB ? lo : DB, nlo = lo - w;
     const K b0 = (K)(pref << w), nb = (K)1 << w;
-    if (more) {
-      K h = hot;
-      if (HOT) asm volatile("" : "+v"(h));  // keeps V lane masks from being carried across the passes
+    K h = hot;
+    if (HOT) asm volatile("" : "+v"(h));  // keeps V lane masks from being carried across the passes
 #pragma unroll
-      for (int v = 0; v < V; v++) {
-        const K b = (K)(top(u[v], nlo) - b0);
-        if ((!HOT || u[v] != h) && b < nb) {
-          const uint32_t bb = (uint32_t)b;
-          atomicAdd(&L.hist[bb + (bb >> LB)], 1u);
-        }
-      }
-      if (HOT && hot_cnt && t == 0) {
-        const K b = (K)(top(hot, nlo) - b0);
-        if (b < nb) {
-          const uint32_t bb = (uint32_t)b;
-          atomicAdd(&L.hist[bb + (bb >> LB)], hot_cnt);
-        }
-      }
+    for (int v = 0; v < V; v++) {
+      const K b = (K)((u[v] >> nlo) - b0);  // nlo < KB
+      if ((!HOT || u[v] != h) && b < nb) atomicAdd(&L.hist[(uint32_t)b], 1u);
+    }
+    if (HOT && hot_cnt && t == 0) {
+      const K b = (K)((hot >> nlo) - b0);
+      if (b < nb) atomicAdd(&L.hist[(uint32_t)b], hot_cnt);
     }
     group_sync<W>();
     uint32_t c[BPT], own = 0;
 #pragma unroll
     for (int j = 0; j < BPT; j++) {
-      c[j] = L.hist[t * (BPT + 1) + j];
-      L.hist[t * (BPT + 1) + j] = 0;
+      c[j] = L.hist[t * BPT + j];
       own += c[j];
     }
+#pragma unroll
+    for (int j = 0; j < BPT; j++) L.hist[t * BPT + j] = 0;
     const uint32_t incl = wave_scan_u32(own);
     uint32_t excl = incl - own;
     if (W > 1) {
@@ -126,7 +112,7 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
       group_sync<W>();
       for (int q = 0; q < sw; q++) excl += L.wsum[q];
     }
-    if (more && excl <= k && k < excl + own) {
+    if (excl <= k && k < excl + own) {
       uint32_t cum = excl;
       int j = 0;
       bool go = true;
@@ -144,56 +130,61 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
       L.below = cum;
     }
     group_sync<W>();
-    if (more) {
-      pref = (K)(b0 + L.bin);
-      k -= L.below;
-      cnt = L.cnt;
-      lo = nlo;
-    }
+    pref = (K)(b0 + L.bin);
+    k -= L.below;
+    cnt = L.cnt;
+    lo = nlo;
   }
   // At most SEL_FEW keys share the prefix, or it is a whole key (lo == 0).
   const bool few = n > 0 && lo > 0;
   const bool want_above = n > 0 && next && k + 1 >= cnt;
+  r1 = r2 = pref;
+  if (!few && !want_above) {
+    group_sync<W>();  // the exchange words are read
+    return;
+  }
   if (t == 0) {
     L.nfew = 0;
     L.above = ~(K)0;
   }
   group_sync<W>();
-  if (few || want_above) {
+  if (few) {
+#pragma unroll
+    for (int v = 0; v < V; v++)
+      if (top(u[v], lo) == pref && u[v] <= last) {
+        const uint32_t at = atomicAdd(&L.nfew, 1u);
+        if (at < (uint32_t)SEL_FEW) L.few[at] = u[v];
+      }
+  }
+  if (want_above) {
     K m = ~(K)0;
 #pragma unroll
-    for (int v = 0; v < V; v++) {
-      const K x = u[v];
-      const K tp = top(x, lo);
-      if (x != ~(K)0) {
-        if (few && tp == pref) L.few[atomicAdd(&L.nfew, 1u)] = x;
-        else if (tp > pref && x < m) m = x;
-      }
+    for (int v = 0; v < V; v++) m = top(u[v], lo) > pref && u[v] < m ? u[v] : m;
+    for (int d = 32; d >= 1; d >>= 1) {
+      const K o = __shfl_xor(m, d, 64);
+      m = o < m ? o : m;
     }
-    if (want_above) {
-      for (int d = 32; d >= 1; d >>= 1) {
-        const K o = __shfl_xor(m, d, 64);
-        m = o < m ? o : m;
-      }
-      if (lane == 0) atomicMin(&L.above, m);
-    }
+    if (lane == 0) atomicMin(&L.above, m);
   }
   group_sync<W>();
   if (few && sw == 0) {
-    const K x = lane < (int)cnt ? L.few[lane] : ~(K)0;
+    // cnt without the words that are no keys
+    const int nf = L.nfew < (uint32_t)SEL_FEW ? (int)L.nfew : SEL_FEW;
+    const K x = lane < nf ? L.few[lane] : ~(K)0;
     uint32_t rank = 0;
-    for (uint32_t j = 0; j < cnt; j++) {
+    for (int j = 0; j < nf; j++) {
       const K y = L.few[j];
-      rank += (y < x || (y == x && (int)j < lane)) ? 1u : 0u;
+      rank += (y < x || (y == x && j < lane)) ? 1u : 0u;
     }
-    if (lane < (int)cnt) {
+    if (lane < nf) {
       if (rank == k) L.r1 = x;
       if (rank == k + 1) L.r2 = x;
     }
   }
   group_sync<W>();
-  r1 = few ? L.r1 : pref;
-  r2 = !next ? r1 : (want_above ? L.above : (few ? L.r2 : pref));
+  if (few) r1 = L.r1;
+  r2 = want_above ? L.above : (few && next ? L.r2 : r1);
+  group_sync<W>();  // the exchange words are read
 }
 
 }  // namespace ta

@@ -48,3 +48,52 @@ def test_region_selection_edges(ta, h, oracle, R):
         assert np.array_equal(o["rank_score"].cpu().numpy(), score)
         assert np.array_equal(o["rank_flag"].cpu().numpy(), flag)
         assert int(o["n_flagged"].item()) == nf
+
+
+@pytest.mark.parametrize("R", [1024, 1025, 4096, 4097, 8193, 16384, 16385, 32768, 32769])
+def test_prescreen_selection_edges(ta, h, R):
+    """Second stage of the pre-screen's score and its top-k at the rank counts
+    where the keys per lane change, with a network of zero weights and output
+    biases c: the residual is c - x up to one FP32 rounding per row, so the mean
+    residual is off by about 1e-7 of max(|x|, |c|) <= 10, i.e. 1e-6, and the
+    score by that over a scale of at least 0.1 -- or a relative 1e-6 of the MAD
+    times the score, below 1e-4 of it."""
+    import torch
+
+    from oracle import ae
+    rng = np.random.default_rng([R, 2])
+    I = 5
+    T = np.rint(rng.gamma(4.0, 2.5e4, (R, I, 64))).astype(np.int64)
+    T[:, :, 3] = 12345                         # constant region: z = 0
+    T[: (5 * R) // 7 + 1, :, 4] = 777          # MAD 0, mean AD > 0
+    T[R // 2: R // 2 + 40] = T[R // 2]         # ranks with equal scores
+    it = np.where(rng.random(R) < 0.05, rng.integers(0, I, R), I).astype(np.int32)
+    it[R // 2: R // 2 + 40] = I
+    dT, dit = torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda()
+    h.ae_init(3)
+    h.ae_fit_norm(dT, dit)
+    state = bytearray(h.ae_get_state())
+    NP = h.AE_NP
+    tail = 4 * (3 * NP + 128)
+    w = np.zeros(NP, np.float32)
+    w[NP - 64:] = np.linspace(-0.5, 0.5, 64)
+    state[-tail:-tail + 4 * NP] = w.tobytes()
+    mu, isd = np.frombuffer(bytes(state[-512:]), np.float32).reshape(2, 64)
+    h2 = ta.Handle(0)
+    h2.ae_set_state(bytes(state))
+    h2.ae_set_score_kind(ta.AE_SCORE_RESIDUAL_Z)
+    shapes = dict(W1=(128, 64), W2=(32, 128), W3=(128, 32), W4=(64, 128), b1=(128,), b2=(32,),
+                  b3=(128,), b4=(64,))
+    params, at = {}, 0
+    for name, shape in shapes.items():
+        n = int(np.prod(shape))
+        params[name] = w[at:at + n].astype(np.float64).reshape(shape)
+        at += n
+    ref = ae.rank_scores(params, T, it, mu, (np.float32(1) / isd), kind=2)
+    for k in (1, R // 3, R):
+        top, sc, fb = h2.prescreen(dT, dit, k)
+        s = sc.cpu().numpy()
+        assert not fb
+        assert np.array_equal(top.cpu().numpy(), np.sort(np.lexsort((np.arange(R), -s))[:k]))
+    np.testing.assert_allclose(s, ref, rtol=1e-4, atol=1e-5)
+    h2.close()
