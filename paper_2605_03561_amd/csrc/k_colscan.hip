@@ -1,0 +1,671 @@
+// k_colscan.hip -- the robust FULL scan's first stage for at most COL_REG_MAX
+// ranks: per column (iteration, region) the median and the median absolute
+// deviation over the ranks, and the ranks' mean scores.
+//
+//   up to COL_DIRECT_MAX ranks   col_select_direct reads the row-major tensor
+//                 (a workgroup's columns side by side, tiles of rows through
+//                 LDS into the registers of the wave that owns a column), and
+//                 score_tensor reads it again
+//   more ranks    col_copy writes a column-major copy in 32-bit offsets,
+//                 col_select reads a column of it into the registers of a
+//                 workgroup, score_copy reads it again; a column whose cells
+//                 do not fit in 32 bits is selected by col_select_wide and
+//                 scored from the tensor
+// Everything between the count of a column and its MAD happens on registers
+// (ta_select.h).  The old path moved 8-byte copies and read each column about
+// ten times, from L2, for the radix passes.
+#include <algorithm>
+
+#include "ta_device.h"
+#include "ta_scan.h"
+#include "ta_select.h"
+
+namespace ta {
+namespace {
+
+typedef long long v2ll __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+constexpr int64_t COL_DIRECT_MAX = 1024;
+
+// Key words.  64 bits: cell + HALF64.  32 bits: cell - base + HALF32, base the
+// cell of rank 0 in that column (whatever it holds), or WIDE when that does
+// not fit.  NONE: a cell that the rank does not have.
+constexpr int64_t HALF64 = (int64_t)1 << 62;
+constexpr int64_t HALF32 = 0x7fffffffll;
+constexpr uint32_t WIDE = 0xfffffffeu;
+template <typename K>
+constexpr K none() {
+  return ~(K)0;
+}
+
+constexpr int CT = 128;  // ranks per tile of the copy; its columns are padded to this
+__host__ __device__ inline int64_t copy_ranks(int64_t R) { return (R + CT - 1) / CT * CT; }
+
+// Column-major copy cp[IG][copy_ranks(R)] of the tensor in 32-bit key words:
+// 64 columns x 128 ranks per workgroup, all 16 loads of a thread in flight,
+// 512-byte pieces of rows in and of columns out.  Bound by HBM (12 bytes per
+// cell): 9,600 columns of 10,000 ranks in 229 us, 5.0 TB/s (the 8-byte copy that
+// it replaces, with the statistics, 358 us).
+__global__ __launch_bounds__(256) void col_copy(const int64_t *__restrict__ T, int64_t R, int IG, int G,
+                                                const int32_t *__restrict__ it, uint32_t *__restrict__ cp) {
+  constexpr int LD = CT + 4;  // 16-byte rows, columns four banks apart
+  __shared__ uint32_t tile[64 * LD];
+  const int c0 = (int)blockIdx.y * 64;
+  const int64_t Rp = copy_ranks(R), r0 = (int64_t)blockIdx.x * CT;
+  const int p2 = 2 * (threadIdx.x & 31), k0 = threadIdx.x >> 5;
+  const int ca = c0 + p2, ia = ca / G, ib = (ca + 1) / G;
+  const bool vec = (IG & 1) == 0, ha = ca < IG, hb = ca + 1 < IG;
+  const int64_t b0 = ha ? T[ca] : 0, b1 = hb ? T[ca + 1] : 0;
+  constexpr int U = CT / 8;
+  v2ll x[U];
+  int nit[U];
+#pragma unroll
+  for (int k = 0; k < U; k++) {
+    const int64_t r = r0 + k0 + 8 * k;
+    x[k] = v2ll{0, 0};
+    nit[k] = 0;
+    if (r < R) {
+      nit[k] = it ? it[r] : 0x7fffffff;
+      const int64_t *row = T + r * IG + ca;
+      if (vec) {
+        if (ha) x[k] = __builtin_nontemporal_load(reinterpret_cast<const v2ll *>(row));
+      } else {
+        if (ha) x[k].x = __builtin_nontemporal_load(row);
+        if (hb) x[k].y = __builtin_nontemporal_load(row + 1);
+      }
+    }
+  }
+  auto word = [](int64_t d, bool in) {
+    const uint32_t w = (d >= HALF32 || d <= -HALF32) ? WIDE : (uint32_t)(d + HALF32);
+    return in ? w : none<uint32_t>();
+  };
+#pragma unroll
+  for (int k = 0; k < U; k++) {
+    tile[p2 * LD + k0 + 8 * k] = word((int64_t)x[k].x - b0, ha && ia < nit[k]);
+    tile[(p2 + 1) * LD + k0 + 8 * k] = word((int64_t)x[k].y - b1, hb && ib < nit[k]);
+  }
+  __syncthreads();
+  const int q = 4 * (threadIdx.x & 31);
+#pragma unroll
+  for (int k = 0; k < 8; k++) {
+    const int c = k0 + 8 * k;
+    if (c0 + c < IG)
+      *reinterpret_cast<v4u *>(cp + (int64_t)(c0 + c) * Rp + r0 + q) =
+          *reinterpret_cast<const v4u *>(&tile[c * LD + q]);
+  }
+}
+
+// What the waves of a column exchange.
+struct ColRed {
+  uint64_t mn, mx, a, b, c;
+  uint32_t n, m;
+};
+
+struct ColOut {
+  ColZ *cz;
+  double *mu;     // 32-bit form: the median in doubled key words, as a double; NaN for a wide column
+  uint8_t *wide;  // 32-bit form: 1 for a wide column, else 0
+  ColPartials ps;
+};
+
+// From a column's key words in the registers of a group of W waves (u[V] per
+// lane) to its coefficients and statistics.  `off` is what a key word of 0
+// stands for.  n = 0 on return of `false`: the column is left to
+// col_select_wide.  Costs about 30 instructions per key, which bound the
+// selection of long columns (STATS: 8 more).
+template <typename K, int V, int W, int NB, bool STATS>
+__device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, ColRed *red, int64_t off,
+                                              int col, bool have, const ColOut &o) {
+  constexpr bool NARROW = sizeof(K) == 4;
+  const int lane = (int)(threadIdx.x & 63), sw = (int)(threadIdx.x >> 6) % W;
+  const bool mine = sw == 0 && lane == 0 && have;
+  uint32_t n = 0;
+  K mn = none<K>(), mx = 0;  // mx: the largest + 1 (0 for none)
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    n += (uint32_t)__popcll(__ballot(u[v] != none<K>()));
+    mn = u[v] < mn ? u[v] : mn;
+    const K w = u[v] + 1;
+    mx = w > mx ? w : mx;
+  }
+  for (int d = 32; d >= 1; d >>= 1) {
+    const K a = __shfl_xor(mn, d, 64), b = __shfl_xor(mx, d, 64);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+  }
+  if (W > 1) {
+    if (lane == 0) {
+      red[sw].mn = mn;
+      red[sw].mx = mx;
+      red[sw].n = n;
+    }
+    __syncthreads();
+    n = 0;
+#pragma unroll
+    for (int q = 0; q < W; q++) {
+      mn = (K)red[q].mn < mn ? (K)red[q].mn : mn;
+      mx = (K)red[q].mx > mx ? (K)red[q].mx : mx;
+      n += red[q].n;
+    }
+    __syncthreads();
+  }
+  const K range = n > 0 ? (K)(mx - 1 - mn) : 0;
+  // deviations |2u - med2| of 32-bit offsets need twice the range
+  const bool wide = NARROW && n > 0 && (mx > (K)WIDE || range > (K)0x7ffffffeu);
+  if (NARROW && mine) o.wide[col] = wide ? 1 : 0;
+  if (wide) {
+    if (mine) o.mu[col] = nan_f64();
+    return;  // the whole group
+  }
+
+  // offsets from the smallest cell (a word that is no key stays above `range`)
+  uint32_t zeros = 0;
+  uint64_t su = 0, sq = 0, sh = 0;
+  u128 q64 = 0;
+  const bool small = range < (K)0x1fffffffu;  // V <= 64 squares fit in 64 bits
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    if (STATS && u[v] != none<K>()) {
+      if (NARROW) {
+        const uint64_t w = (uint64_t)(uint32_t)(u[v] - mn), ww = w * w;
+        su += w;
+        if (small) {
+          sq += ww;
+        } else {
+          sq += (uint32_t)ww;
+          sh += ww >> 32;
+        }
+      } else {
+        const int64_t x = (int64_t)(u[v] - (K)HALF64);
+        su += (uint64_t)x;
+        q64 += (u128)((i128)x * x);
+      }
+    }
+    u[v] = u[v] - mn;
+    zeros += (uint32_t)__popcll(__ballot(u[v] == 0));
+  }
+  if (STATS || W > 1) {
+    u128 tot = NARROW ? (u128)sq + ((u128)sh << 32) : q64;
+    if (STATS)
+      for (int d = 32; d >= 1; d >>= 1) {
+        const uint64_t ol = __shfl_xor((uint64_t)tot, d, 64), oh = __shfl_xor((uint64_t)(tot >> 64), d, 64);
+        tot += ((u128)oh << 64) | ol;
+        su += __shfl_xor(su, d, 64);
+      }
+    if (W > 1) {
+      if (lane == 0) {
+        red[sw].a = (uint64_t)tot;
+        red[sw].b = (uint64_t)(tot >> 64);
+        red[sw].c = su;
+        red[sw].m = zeros;
+      }
+      __syncthreads();
+      zeros = 0;
+#pragma unroll
+      for (int q = 0; q < W; q++) zeros += red[q].m;
+      if (STATS && mine) {
+        tot = 0;
+        su = 0;
+        for (int q = 0; q < W; q++) {
+          tot += ((u128)red[q].b << 64) | red[q].a;
+          su += red[q].c;
+        }
+      }
+      __syncthreads();
+    }
+    if (STATS && mine) {
+      const int64_t lo = off + (int64_t)mn;  // the smallest cell
+      int64_t s1 = (int64_t)su;
+      if (NARROW) {
+        // sum (lo + u)^2 = n lo^2 + 2 lo sum u + sum u^2, exactly
+        s1 = (int64_t)n * lo + (int64_t)su;
+        tot += (u128)((i128)n * lo * lo + 2 * (i128)lo * (i128)su);
+      }
+      o.ps.n[col] = n;
+      o.ps.s1[col] = s1;
+      o.ps.lo[col] = (uint64_t)tot;
+      o.ps.hi[col] = (uint64_t)(tot >> 64);
+      o.ps.mn[col] = n > 0 ? lo : INT64_MAX;
+      o.ps.mx[col] = n > 0 ? lo + (int64_t)range : INT64_MIN;
+    }
+  }
+  if (n == 0) {
+    if (mine) {
+      o.cz[col] = ColZ{0, 0.0, 1.0, 1.0};
+      if (NARROW) o.mu[col] = 0.0;
+    }
+    return;
+  }
+
+  // the median, then the MAD of |2u - med2|
+  const uint32_t k = (n - 1) / 2;
+  const bool even = (n & 1) == 0;
+  K a, b;
+  reg_select<true>(S, u, (K)0, zeros, range, nbits64(range), n, k, even, a, b);
+  const K m2 = a + b;
+  uint32_t hits = 0;  // deviations equal to med2: the smallest cells', which may be many
+#pragma unroll
+  for (int v = 0; v < V; v++) {
+    const K t = 2 * u[v];
+    const K d = t > m2 ? t - m2 : m2 - t;
+    u[v] = u[v] <= range ? d : none<K>();
+    hits += (uint32_t)__popcll(__ballot(u[v] == m2));
+  }
+  if (W > 1) {
+    if (lane == 0) red[sw].m = hits;
+    __syncthreads();
+    hits = 0;
+#pragma unroll
+    for (int q = 0; q < W; q++) hits += red[q].m;
+  }
+  const K far = (K)(2 * range - m2), dmax = far > m2 ? far : m2;
+  reg_select<true>(S, u, m2, hits, dmax, nbits64(dmax), n, k, even, a, b);
+  const uint64_t mad4 = (uint64_t)a + (uint64_t)b;
+  uint64_t sd = 0;  // the sum of the deviations is wanted when the MAD is 0
+  if (mad4 == 0) {
+#pragma unroll
+    for (int v = 0; v < V; v++) sd += u[v] <= dmax ? (uint64_t)u[v] : 0;
+    for (int d = 32; d >= 1; d >>= 1) sd += __shfl_xor(sd, d, 64);
+    if (W > 1) {
+      if (lane == 0) red[sw].a = sd;
+      __syncthreads();
+      sd = 0;
+      for (int q = 0; q < W; q++) sd += red[q].a;
+    }
+  }
+  if (mine) {
+    ColZ z;
+    z.med2 = 2 * (off + (int64_t)mn) + (int64_t)m2;
+    z_coefs((int64_t)mad4, (int64_t)sd, (int64_t)n, z.zc, z.zd);
+    z.zy = 1.0 / z.zd;
+    o.cz[col] = z;
+    if (NARROW) o.mu[col] = (double)(2 * (uint64_t)mn + (uint64_t)m2);
+  }
+}
+
+template <int W, int V>
+constexpr int col_bins() {  // 4 to 16 bins per lane of a single wave, else 2,048
+  return W > 1 ? 2048 : (V <= 4 ? 256 : V <= 8 ? 512 : 1024);
+}
+
+// Columns of the 32-bit copy: W waves and V key words per lane each; a single
+// wave's columns come four to a workgroup.  Bound by its instructions (30 to 40
+// per key): 9,600 columns of 10,000 ranks with their statistics 355 us, radix
+// passes over the column in memory 566 us; 11,520 columns of 9,190 ranks 286 us
+// against 1,296.
+template <int W, int V, bool STATS>
+__global__ __launch_bounds__(W > 1 ? 64 * W : 256) void col_select(const uint32_t *__restrict__ cp, int64_t R,
+                                                                   int IG, const int64_t *__restrict__ T,
+                                                                   ColOut o) {
+  constexpr int C = W > 1 ? 1 : 4, NB = col_bins<W, V>();
+  __shared__ SelGroup<W, NB, uint32_t> L[C];
+  __shared__ ColRed red[W];
+  const int cl = W > 1 ? 0 : (int)(threadIdx.x >> 6), t = (int)(threadIdx.x % (64 * W));
+  const int col = (int)blockIdx.x * C + cl;
+  if (col >= IG) return;  // a whole group; single waves meet no workgroup barrier
+  const int64_t Rp = copy_ranks(R);
+  const uint32_t *p = cp + (int64_t)col * Rp;
+  uint32_t u[V];
+#pragma unroll
+  for (int v = 0; v < V; v += 4) {
+    const int64_t r = (int64_t)(v / 4) * 256 * W + 4 * t;
+    v4u q = {none<uint32_t>(), none<uint32_t>(), none<uint32_t>(), none<uint32_t>()};
+    if (r < Rp) q = *reinterpret_cast<const v4u *>(p + r);
+    u[v] = q.x;
+    u[v + 1] = q.y;
+    u[v + 2] = q.z;
+    u[v + 3] = q.w;
+  }
+  const int64_t off = T[col] - HALF32;
+  sel_clear(L[cl]);
+  select_column<uint32_t, V, W, NB, STATS>(u, L[cl], red, off, col, true, o);
+}
+
+// The columns that the 32-bit form marked wide, in 64-bit words straight from
+// the tensor (8-byte pieces of rows: for data with a spread of 2^31 ns and
+// more within a column).  Returns at once when there is none.
+template <bool STATS>
+__global__ __launch_bounds__(1024) void col_select_wide(const int64_t *__restrict__ T, int64_t R, int IG,
+                                                        int G, const int32_t *__restrict__ it, ColOut o) {
+  constexpr int W = 16, V = (int)(COL_REG_MAX / 1024);
+  __shared__ SelGroup<W, 2048, uint64_t> L;
+  __shared__ ColRed red[W];
+  __shared__ uint32_t todo[1024], n_todo;
+  const int tid = (int)threadIdx.x;
+  if (tid == 0) n_todo = 0;
+  __syncthreads();
+  const int64_t c = blockIdx.x + (int64_t)tid * gridDim.x;  // the grid leaves at most 1,024 per workgroup
+  if (c < IG && o.wide[c]) todo[atomicAdd(&n_todo, 1u)] = (uint32_t)c;
+  __syncthreads();
+  const int turns = (int)n_todo;
+  for (int turn = 0; turn < turns; turn++) {
+    const int col = (int)todo[turn], ic = col / G;
+    uint64_t u[V];
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      const int64_t r = (int64_t)v * 1024 + tid;
+      u[v] = none<uint64_t>();
+      if (r < R && (!it || ic < it[r])) u[v] = (uint64_t)(T[r * IG + col] + HALF64);
+    }
+    __syncthreads();
+    sel_clear(L);
+    select_column<uint64_t, V, W, 2048, STATS>(u, L, red, -HALF64, col, true, o);
+  }
+}
+
+// Short columns in 64-bit words: eight columns of one wave each per workgroup
+// (64-byte pieces of rows), tiles of rows through LDS.  Consecutive groups of
+// columns go to one XCD (workgroup b runs on XCD b mod 8), so the two halves
+// of a line are fetched from HBM once.  6,400 columns of 1,000 ranks: 54 us
+// against 96 us of copy and 148 us of radix passes.
+template <int V, bool STATS>
+__global__ __launch_bounds__(512) void col_select_direct(const int64_t *__restrict__ T, int64_t R, int IG,
+                                                         int G, const int32_t *__restrict__ it, ColOut o) {
+  constexpr int C = 8, TV = V < 8 ? V : 8, TR = 64 * TV;
+  constexpr int LD = TR + 4;  // the half wave's four rows of eight columns hit different banks
+  constexpr int NB = col_bins<1, V>();
+  union Lds {
+    uint64_t tile[C * LD];
+    SelGroup<1, NB, uint64_t> sel[C];
+    __device__ Lds() {}
+  };
+  __shared__ Lds L;
+  const int tid = (int)threadIdx.x, lane = tid & 63, cl = tid >> 6;
+  const int c0 = C * ((int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3));
+  if (c0 >= IG) return;
+  constexpr int QN = 128, U = TR / QN > 0 ? TR / QN : 1;
+  const int p = tid % 4, q0 = tid / 4, ca = c0 + 2 * p;
+  const bool vec = (IG & 1) == 0, ha = ca < IG, hb = ca + 1 < IG;
+  const int ia = ca / G, ib = (ca + 1) / G;
+  v2ll x[U];
+  int nit[U];
+  auto load = [&](int t) {
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const int64_t r = (int64_t)t * TR + q0 + k * QN;
+      x[k] = v2ll{0, 0};
+      nit[k] = 0;
+      if (r < R) {
+        nit[k] = it ? it[r] : 0x7fffffff;
+        const int64_t *row = T + r * IG + ca;
+        if (vec) {
+          if (ha) x[k] = *reinterpret_cast<const v2ll *>(row);
+        } else {
+          if (ha) x[k].x = row[0];
+          if (hb) x[k].y = row[1];
+        }
+      }
+    }
+  };
+  uint64_t u[V];
+  load(0);
+#pragma unroll
+  for (int t = 0; t < V / TV; t++) {
+    if ((int64_t)t * TR >= R) {
+#pragma unroll
+      for (int j = 0; j < TV; j++) u[t * TV + j] = none<uint64_t>();
+      continue;
+    }
+    __syncthreads();  // the previous tile is read
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      L.tile[2 * p * LD + q0 + k * QN] = ha && ia < nit[k] ? (uint64_t)((int64_t)x[k].x + HALF64) : none<uint64_t>();
+      L.tile[(2 * p + 1) * LD + q0 + k * QN] =
+          hb && ib < nit[k] ? (uint64_t)((int64_t)x[k].y + HALF64) : none<uint64_t>();
+    }
+    __syncthreads();
+    if (t + 1 < V / TV) load(t + 1);
+#pragma unroll
+    for (int j = 0; j < TV; j++) u[t * TV + j] = L.tile[cl * LD + j * 64 + lane];
+  }
+  __syncthreads();
+  const int col = c0 + cl;
+  sel_clear(L.sel[cl]);
+  select_column<uint64_t, V, 1, NB, STATS>(u, L.sel[cl], (ColRed *)nullptr, -HALF64, col, col < IG, o);
+}
+
+// a / b rounded to nearest, given y = 1 / b rounded to nearest: two corrections
+// of the quotient by its exact remainder.  The first leaves it within an ulp,
+// after which the second gives the correctly rounded quotient (Markstein 1990,
+// "Computation of elementary functions on the IBM RISC System/6000 processor").
+// No step can underflow or overflow here: |a| is 0 or in [1, 2^96], b in
+// [1, 2^66].  Five operations instead of the division's full sequence.
+__device__ __forceinline__ double div_by(double a, double b, double y) {
+  double q = a * y;
+  q = fma(fma(-b, q, a), y, q);
+  return fma(fma(-b, q, a), y, q);
+}
+
+__device__ __forceinline__ int rank_iters(const int32_t *it, int64_t r, int I) {
+  const int v = it ? it[r] : I;
+  return v > I ? I : (v < 0 ? 0 : v);
+}
+
+// m(r,g) = (1/n_r) sum over i < n_r, ascending, of z(r,i,g), from the
+// column-major copy: a wave owns 64 * RPL consecutive ranks of one region, so
+// the column's numbers are scalars; IU iterations' cells are loaded before the
+// first is scored.  9,600
+// columns of 10,000 ranks in 145 us (2.7 TB/s), 216 us from the 8-byte copy
+// with a division and a wait for every cell.
+template <int RPL, int IU>
+__global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ cp, const int64_t *__restrict__ T,
+                                                  int64_t R, int I, int G, const int32_t *__restrict__ it,
+                                                  const ColZ *__restrict__ cz, const double *__restrict__ mu,
+                                                  double *m_t) {
+  const int lane = (int)(threadIdx.x & 63);
+  const int64_t rb = (R + 64 * RPL - 1) / (64 * RPL);
+  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int g = __builtin_amdgcn_readfirstlane((int)(wave / rb));
+  if (g >= G) return;
+  const int64_t Rp = copy_ranks(R), r0 = ((wave % rb) * 64 + lane) * RPL;
+  const bool on = r0 < R;
+  const uint32_t *p = cp + (int64_t)g * Rp + (on ? r0 : 0);
+  double acc[RPL];
+#pragma unroll
+  for (int q = 0; q < RPL; q++) acc[q] = 0.0;
+  for (int i0 = 0; i0 < I; i0 += IU) {
+    uint32_t w[IU][RPL];
+#pragma unroll
+    for (int j = 0; j < IU; j++) {
+      const int i = i0 + j < I ? i0 + j : I - 1;
+      const uint32_t *s = p + (int64_t)i * G * Rp;
+      if (RPL == 4) {
+        const v4u v = *reinterpret_cast<const v4u *>(s);
+        w[j][0] = v.x;
+        w[j][1 % RPL] = v.y;
+        w[j][2 % RPL] = v.z;
+        w[j][3 % RPL] = v.w;
+      } else {
+        w[j][0] = s[0];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < IU; j++) {
+      if (i0 + j >= I) break;
+      const int64_t c = (int64_t)(i0 + j) * G + g;
+      const ColZ z = cz[c];
+      const double m = mu[c];
+      if (m == m) {
+#pragma unroll
+        for (int q = 0; q < RPL; q++) {
+          // 2x - med2 in key words: both terms are integers below 2^34
+          const double d = fma(2.0, (double)w[j][q], -m);
+          const double t = acc[q] + div_by(d * z.zc, z.zd, z.zy);
+          acc[q] = w[j][q] != none<uint32_t>() ? t : acc[q];
+        }
+      } else {  // a wide column
+#pragma unroll
+        for (int q = 0; q < RPL; q++) {
+          const int64_t r = r0 + q;
+          if (r < R && i0 + j < rank_iters(it, r, I)) {
+            const int64_t x = T[r * (int64_t)I * G + c];
+            acc[q] += div_by((double)(2 * x - z.med2) * z.zc, z.zd, z.zy);
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < RPL; q++)
+    if (r0 + q < R) {
+      const int ni = rank_iters(it, r0 + q, I);
+      m_t[(int64_t)g * R + r0 + q] = ni > 0 ? acc[q] / (double)ni : 0.0;
+    }
+}
+
+// The same from the row-major tensor.  A lane owns a region of RPL consecutive
+// ranks; with fewer than 64 regions a wave takes 64 >> lgp ranks' rows side by
+// side.  1,600 columns of 64 ranks: 33 us against 65 us with one load in flight.
+template <int RPL, int IU>
+__global__ __launch_bounds__(256) void score_tensor(const int64_t *__restrict__ T, int64_t R, int I, int G,
+                                                    int lgp, const int32_t *__restrict__ it,
+                                                    const ColZ *__restrict__ cz, double *m_t) {
+  const int lane = (int)(threadIdx.x & 63);
+  const int gbn = (G + 63) / 64;
+  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t r0 = ((wave / gbn) * (64 >> lgp) + (lane >> lgp)) * RPL;
+  const int g = (int)(wave % gbn) * 64 + (lane & ((1 << lgp) - 1));
+  const bool on = g < G && r0 < R;
+  const int gg = on ? g : 0;
+  const int64_t rr = on ? r0 : 0, IG = (int64_t)I * G;
+  int ni[RPL], nmax = 0;
+#pragma unroll
+  for (int q = 0; q < RPL; q++) {
+    ni[q] = on && rr + q < R ? rank_iters(it, rr + q, I) : 0;
+    nmax = ni[q] > nmax ? ni[q] : nmax;
+  }
+  double acc[RPL];
+#pragma unroll
+  for (int q = 0; q < RPL; q++) acc[q] = 0.0;
+  const int64_t *p = T + rr * IG + gg;
+  for (int i0 = 0; i0 < nmax; i0 += IU) {
+    int64_t x[IU][RPL];
+    ColZ z[IU];
+#pragma unroll
+    for (int j = 0; j < IU; j++) {
+      const int i = i0 + j < nmax ? i0 + j : nmax - 1;
+      z[j] = cz[(int64_t)i * G + gg];
+#pragma unroll
+      for (int q = 0; q < RPL; q++) x[j][q] = i0 + j < ni[q] ? p[q * IG + (int64_t)i * G] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < IU; j++)
+#pragma unroll
+      for (int q = 0; q < RPL; q++) {
+        const double t = acc[q] + div_by((double)(2 * x[j][q] - z[j].med2) * z[j].zc, z[j].zd, z[j].zy);
+        acc[q] = i0 + j < ni[q] ? t : acc[q];
+      }
+  }
+  if (on)
+#pragma unroll
+    for (int q = 0; q < RPL; q++)
+      if (rr + q < R) m_t[(int64_t)g * R + rr + q] = ni[q] > 0 ? acc[q] / (double)ni[q] : 0.0;
+}
+
+struct ColWs {
+  ColZ *cz;
+  double *mu;
+  uint8_t *wide;
+  uint32_t *cp;
+};
+
+ColWs carve(void *ws, int64_t R, int IG, size_t *used) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char *p = (char *)ws + off;
+    off += (bytes + 255) & ~(size_t)255;
+    return (void *)p;
+  };
+  ColWs w{};
+  w.cz = (ColZ *)take((size_t)IG * sizeof(ColZ));
+  if (R > COL_DIRECT_MAX) {
+    w.mu = (double *)take((size_t)IG * 8);
+    w.wide = (uint8_t *)take((size_t)IG);
+    w.cp = (uint32_t *)take((size_t)IG * copy_ranks(R) * 4);
+  }
+  *used = off;
+  return w;
+}
+
+}  // namespace
+
+size_t col_scan_ws_bytes(int64_t R, int IG) {
+  size_t used = 0;
+  carve((void *)0x100, R, IG, &used);
+  return used;
+}
+
+hipError_t launch_score_tensor(const int64_t *T, int64_t R, int I, int G, const int32_t *it,
+                               const ColZ *cz, double *m_t, int cus, hipStream_t s) {
+  int lgp = 0;
+  while (lgp < 6 && (1 << lgp) < G) lgp++;
+  const int64_t side = 64 >> lgp, gbn = (G + 63) / 64;
+  // with at least 16 waves per CU left, four ranks per lane share the column
+  // numbers; below that the iterations' loads are what there is to overlap
+  const bool many = (R + side - 1) / side * gbn / 4 >= 16 * (int64_t)cus;
+  const int64_t per = side * (many ? 4 : 1);
+  const unsigned grid = (unsigned)(((R + per - 1) / per * gbn + 3) / 4);
+  if (many)
+    hipLaunchKernelGGL((score_tensor<4, 2>), dim3(grid), dim3(256), 0, s, T, R, I, G, lgp, it, cz, m_t);
+  else
+    hipLaunchKernelGGL((score_tensor<1, 8>), dim3(grid), dim3(256), 0, s, T, R, I, G, lgp, it, cz, m_t);
+  return hipGetLastError();
+}
+
+hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int32_t *it, ColPartials st,
+                           hipEvent_t stats_ready, double *m_t, void *ws, int cus, hipStream_t s) {
+  size_t used = 0;
+  const int IG = I * G;
+  const ColWs w = carve(ws, R, IG, &used);
+  const ColOut o{w.cz, w.mu, w.wide, st};
+  const bool stats = st.rc > 0;
+  hipError_t e = hipSuccess;
+  if (R <= COL_DIRECT_MAX) {
+    const unsigned grid = 8u * (unsigned)(((IG + 7) / 8 + 7) / 8);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, s, T, R, IG, G, it, o); };
+    if (R <= 256) stats ? go(col_select_direct<4, true>) : go(col_select_direct<4, false>);
+    else if (R <= 512) stats ? go(col_select_direct<8, true>) : go(col_select_direct<8, false>);
+    else stats ? go(col_select_direct<16, true>) : go(col_select_direct<16, false>);
+    e = hipGetLastError();
+    if (e == hipSuccess && stats && stats_ready) e = hipEventRecord(stats_ready, s);
+    if (e != hipSuccess) return e;
+    return launch_score_tensor(T, R, I, G, it, w.cz, m_t, cus, s);
+  }
+  const int64_t Rp = copy_ranks(R);
+  hipLaunchKernelGGL(col_copy, dim3((unsigned)(Rp / CT), (unsigned)((IG + 63) / 64)), dim3(256), 0, s, T, R,
+                     IG, G, it, w.cp);
+  auto go = [&](auto kern, int nt, int cols) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((IG + cols - 1) / cols)), dim3(nt), 0, s,
+                       (const uint32_t *)w.cp, R, IG, T, o);
+  };
+  // the fewest waves that hold the column in 24 or 32 words per lane
+  if (R <= 2048) stats ? go(col_select<1, 32, true>, 256, 4) : go(col_select<1, 32, false>, 256, 4);
+  else if (R <= 3072) stats ? go(col_select<2, 24, true>, 128, 1) : go(col_select<2, 24, false>, 128, 1);
+  else if (R <= 4096) stats ? go(col_select<2, 32, true>, 128, 1) : go(col_select<2, 32, false>, 128, 1);
+  else if (R <= 6144) stats ? go(col_select<4, 24, true>, 256, 1) : go(col_select<4, 24, false>, 256, 1);
+  else if (R <= 8192) stats ? go(col_select<4, 32, true>, 256, 1) : go(col_select<4, 32, false>, 256, 1);
+  else if (R <= 12288) stats ? go(col_select<8, 24, true>, 512, 1) : go(col_select<8, 24, false>, 512, 1);
+  else if (R <= 16384) stats ? go(col_select<8, 32, true>, 512, 1) : go(col_select<8, 32, false>, 512, 1);
+  else if (R <= 24576) stats ? go(col_select<16, 24, true>, 1024, 1) : go(col_select<16, 24, false>, 1024, 1);
+  else stats ? go(col_select<16, 32, true>, 1024, 1) : go(col_select<16, 32, false>, 1024, 1);
+  const unsigned wg = (unsigned)std::max(std::min(IG, cus), (IG + 1023) / 1024);
+  if (stats)
+    hipLaunchKernelGGL(col_select_wide<true>, dim3(wg), dim3(1024), 0, s, T, R, IG, G, it, o);
+  else
+    hipLaunchKernelGGL(col_select_wide<false>, dim3(wg), dim3(1024), 0, s, T, R, IG, G, it, o);
+  e = hipGetLastError();
+  if (e == hipSuccess && stats && stats_ready) e = hipEventRecord(stats_ready, s);
+  if (e != hipSuccess) return e;
+  // four ranks per lane (16-byte loads) once that leaves 16 waves per CU
+  const int64_t w4 = (R + 255) / 256 * G;
+  if (w4 >= 16 * (int64_t)cus)
+    hipLaunchKernelGGL((score_copy<4, 4>), dim3((unsigned)((w4 + 3) / 4)), dim3(256), 0, s,
+                       (const uint32_t *)w.cp, T, R, I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
+  else
+    hipLaunchKernelGGL((score_copy<1, 16>), dim3((unsigned)(((R + 63) / 64 * G + 3) / 4)), dim3(256), 0, s,
+                       (const uint32_t *)w.cp, T, R, I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
+  return hipGetLastError();
+}
+
+}  // namespace ta

@@ -9,18 +9,22 @@
 // pass), so no extra pass is needed.
 //
 // FULL scan:   stage 1  per column (i,g): median and MAD over ranks
-//                       - robust kind, long columns: on the row-major tensor,
+//                       - robust kind, up to COL_REG_MAX ranks: columns in
+//                         registers (k_colscan.hip)
+//                       - robust kind, longer columns: on the row-major tensor,
 //                         a sampled bracket per column, one streaming pass
 //                         that counts and compacts the bracket interior, an
 //                         exact selection over it (rm_* kernels below)
-//                       - otherwise: transpose to column-major [I*G][ranks]
-//                         and select per column (11-bit digits)
+//                       - otherwise: transpose to column-major [I*G][ranks],
+//                         moments per column (plain z) or, beyond SEG_MAX
+//                         chunks of ranks, a bracketed selection per column
 //              scoring  m(r,g) = mean over the rank's iterations of z(r,i,g),
 //                       summed in ascending i (bit-reproducible)
 //              stage 2  per region g: median / MAD over ranks of m(r,g)
 // TOTALS scan: stage 2 only, on the rank totals S(r,g).
 #include "ta_device.h"
 #include "ta_internal.h"
+#include "ta_scan.h"
 #include "ta_select.h"
 
 namespace ta {
@@ -33,38 +37,17 @@ struct ColSel {
   double *zc, *zd;                    // [IG] row-major path: z = ((2x - med2) * zc) / zd
 };
 
-// The robust z of a cell in one division with per-column (zc, zd): when
-// mad4 > 0, (2.0, 1.4826 * mad4) -- (2x - med2) * 2 converts to the same double
-// as 4x - 2 med2; when only the mean absolute deviation is positive,
-// (n, 1.253314 * sumdev); else (0, 1) (every cell is the median, z = 0).
-__host__ __device__ inline void z_coefs(int64_t mad4, int64_t sumdev, int64_t n, double &zc, double &zd) {
-  if (mad4 > 0) {
-    zc = 2.0;
-    zd = 1.4826 * (double)mad4;
-  } else if (sumdev > 0) {
-    zc = (double)n;
-    zd = 1.253314 * (double)sumdev;
-  } else {
-    zc = 0.0;
-    zd = 1.0;
-  }
-}
-
-__device__ inline int nbits64(uint64_t v) { return v ? 64 - __clzll((long long)v) : 0; }
-
 // ----------------------------------------------------------------------------
-// Column-major path for the robust FULL scan.
+// Column-major path for the plain z-score, and for the robust FULL scan with
+// more ranks than the row-major path takes.
 //   transpose_kernel  T[R][IG] -> Tt[IG][Rp] (Rp = R rounded up to 64) through
 //                     64 x 64 LDS tiles; a cell of an iteration the rank does
 //                     not have, and the padding, hold the sentinel INT64_MIN
-//   col_select        one workgroup per column, streaming the contiguous column:
-//                     count/min/max, radix selection of the lower median with
-//                     11-bit digits, then of the MAD (the first MAD pass also
-//                     sums the absolute deviations).  The next order statistic
-//                     of an even count is the next non-empty bin of the last
-//                     digit, else the smallest key above the prefix group
-//   score_cols        a wave = 64 consecutive ranks of one region; the column
-//                     parameters are uniform across the wave
+//   col_moments, score_cols  plain z: one workgroup per column for the moments,
+//                     then a wave = 64 consecutive ranks of one region
+//   col_select_bracket  robust: sampled brackets, two streaming passes over the
+//                     contiguous column, exact selection over the interior
+//                     (then score_tensor)
 // ----------------------------------------------------------------------------
 constexpr int TT = 64;
 typedef long long v2ll __attribute__((ext_vector_type(2)));
@@ -189,7 +172,6 @@ __device__ inline uint64_t shr64(uint64_t x, int s) { return s >= 64 ? 0 : x >> 
 
 constexpr int MS = 2048;          // sample slots (LDS)
 constexpr int SEL_GRID_MAX = 2048; // column workgroups (persistent, one scratch slot each)
-constexpr int64_t SEL_BRACKET_MIN_RP = 32768;  // shorter columns: whole-column radix selection
 
 // LDS of the radix selection (and of the column reductions).
 struct SelLds {
@@ -538,7 +520,7 @@ __device__ bool bracket_pick(Visit &&vmid, int64_t clo, int64_t ceqa, int64_t cm
   return true;
 }
 
-// Per column (at least SEL_BRACKET_MIN_RP padded ranks; persistent grid, one
+// Per column (more ranks than the row-major path takes; persistent grid, one
 // scratch slot per workgroup): sample, then two streaming passes (median
 // bracket, MAD bracket); exact selection over the compacted bracket values, or
 // over the whole column when a bracket misses the middle or overflows the
@@ -547,7 +529,7 @@ constexpr int SEL_WGS_PER_CU = 4;  // column workgroups per CU (LDS 20 KB, at mo
 
 __global__ __launch_bounds__(CS, SEL_WGS_PER_CU) void col_select_bracket(const int64_t *__restrict__ Tt, int64_t R, int IG,
                                                  int64_t *__restrict__ scratch, int64_t cap,
-                                                 ColSel out) {
+                                                 ColZ *out) {
   __shared__ ColSelLds L;
   const int t = threadIdx.x;
   const int64_t Rp = pad_ranks(R);
@@ -624,10 +606,7 @@ __global__ __launch_bounds__(CS, SEL_WGS_PER_CU) void col_select_bracket(const i
     }
     if (n == 0) {
       if (t == 0) {
-        out.med2[c] = 0;
-        out.mad4[c] = 0;
-        out.sumdev[c] = 0;
-        out.n[c] = 0;
+        out[c] = ColZ{0, 0.0, 1.0, 1.0};
       }
       __syncthreads();
       continue;
@@ -685,72 +664,13 @@ __global__ __launch_bounds__(CS, SEL_WGS_PER_CU) void col_select_bracket(const i
       mad4 = x1 + x2;
     }
     if (t == 0) {
-      out.med2[c] = med2;
-      out.mad4[c] = mad4;
-      out.sumdev[c] = sd;
-      out.n[c] = n;
+      ColZ z;
+      z.med2 = med2;
+      z_coefs(mad4, sd, n, z.zc, z.zd);
+      z.zy = 1.0 / z.zd;
+      out[c] = z;
     }
     __syncthreads();
-  }
-}
-
-// Per column, one workgroup each (columns of up to SEL_BRACKET_MIN_RP padded
-// ranks, which stay in the caches between passes): count/min/max, then radix
-// selection over the whole column for the median and for the MAD (whose first
-// pass also sums the absolute deviations).
-__global__ __launch_bounds__(CS) void col_select_radix(const int64_t *__restrict__ Tt, int64_t R,
-                                                       ColSel out) {
-  __shared__ SelLds L;
-  const int c = blockIdx.x;
-  const int t = threadIdx.x;
-  const int64_t Rp = pad_ranks(R);
-  const int64_t *col = Tt + (int64_t)c * Rp;
-  for (int j = t; j < NHC * NB; j += CS) (&L.hist[0][0])[j] = 0;
-  auto vcol = [&](auto &&f) {
-    sweep(col, Rp, [&](int64_t x) {
-      if (x != SENT) f(x);
-    });
-  };
-  int64_t n = 0, mn = INT64_MAX, mx = INT64_MIN;
-  vcol([&](int64_t x) {
-    n++;
-    mn = x < mn ? x : mn;
-    mx = x > mx ? x : mx;
-  });
-  {
-    int64_t cnt[1] = {n};
-    block_stats<1, true>(cnt, mn, mx, L.red);
-    n = cnt[0];
-  }
-  if (n == 0) {
-    if (t == 0) {
-      out.med2[c] = 0;
-      out.mad4[c] = 0;
-      out.sumdev[c] = 0;
-      out.n[c] = 0;
-    }
-    return;
-  }
-  const int64_t k = (n - 1) / 2;
-  const bool even = (n & 1) == 0;
-  uint64_t a1, a2;
-  radix_select(vcol, k, even, nbits64((uint64_t)mx - (uint64_t)mn),
-               [&](int64_t x) { return (uint64_t)x - (uint64_t)mn; }, L, a1, a2);
-  const int64_t med2 = (int64_t)((uint64_t)mn + a1) + (int64_t)((uint64_t)mn + a2);
-  const uint64_t dlo = (uint64_t)(med2 - 2 * mn), dhi = (uint64_t)(2 * mx - med2);
-  const uint64_t dmax = dlo > dhi ? dlo : dhi;
-  int64_t sd = 0;
-  radix_select(vcol, k, even, nbits64(dmax),
-               [&](int64_t x) {
-                 const int64_t d = 2 * x - med2;
-                 return (uint64_t)(d < 0 ? -d : d);
-               },
-               L, a1, a2, &sd);
-  if (t == 0) {
-    out.med2[c] = med2;
-    out.mad4[c] = (int64_t)(a1 + a2);
-    out.sumdev[c] = sd;
-    out.n[c] = n;
   }
 }
 
@@ -798,9 +718,8 @@ __global__ __launch_bounds__(CS) void col_moments(const int64_t *__restrict__ Tt
 // m(r,g) = (1/n_r) sum_{i < n_r} z(r,i,g) (ascending i) from the column-major
 // tensor, written [G][R]; one wave = 64 consecutive ranks of region g, so the
 // column parameters are uniform across the wave.
-template <bool MAD>
 __global__ __launch_bounds__(256) void score_cols(const int64_t *__restrict__ Tt, int64_t R, int I,
-                                                  int G, const int32_t *it, ColSel cs, ColMom cm,
+                                                  int G, const int32_t *it, ColMom cm,
                                                   double *m_t) {
   const int lane = threadIdx.x & 63;
   const int64_t rblocks = (R + 63) / 64;
@@ -820,21 +739,9 @@ __global__ __launch_bounds__(256) void score_cols(const int64_t *__restrict__ Tt
     const int c = i * G + g;
     if (i < ni) {
       const int64_t x = p[(int64_t)i * G * Rp];
-      double z;
-      if (MAD) {
-        const int64_t med2 = cs.med2[c], mad4 = cs.mad4[c];
-        if (mad4 > 0) {
-          z = (double)(4 * x - 2 * med2) / (1.4826 * (double)mad4);
-        } else {
-          const int64_t sdv = cs.sumdev[c];
-          z = sdv > 0 ? ((double)(2 * x - med2) * (double)cs.n[c]) / (1.253314 * (double)sdv) : 0.0;
-        }
-      } else {
-        const double sd = cm.sd[c];
-        const int64_t n = cm.n[c];
-        z = sd > 0.0 ? i128_to_f64((i128)n * x - cm.s1[c]) / ((double)n * sd) : 0.0;
-      }
-      acc += z;
+      const double sd = cm.sd[c];
+      const int64_t n = cm.n[c];
+      acc += sd > 0.0 ? i128_to_f64((i128)n * x - cm.s1[c]) / ((double)n * sd) : 0.0;
     }
   }
   if (r < R) m_t[(int64_t)g * R + r] = ni > 0 ? acc / (double)ni : 0.0;
@@ -2305,7 +2212,9 @@ struct OWs {
   int32_t *esc;     // row-major path: [2] per column half, set when the copy does not serve
   int64_t *qa, *qb, *da, *db;  // row-major path: [IG] brackets
   RmPart rp;        // row-major path: [groups][IG] pass counts
-  ColSel cs;
+  ColSel cs;        // row-major path
+  ColZ *cz;         // column-major robust scan: [IG]
+  void *cols;       // columns in registers: col_scan_ws_bytes
   ColMom cm;
   double *m_t;      // [G][R] doubles (FULL) -- also reused as z_t
   int64_t *S_t;     // [G][R] (TOTALS)
@@ -2313,9 +2222,14 @@ struct OWs {
   int64_t *part;    // [ceil(R/256)]
 };
 
-// The robust FULL scan over long columns runs on the row-major tensor.
+// The robust FULL scan: columns of up to COL_REG_MAX ranks are selected in
+// registers (k_colscan.hip), longer ones by the streaming passes over the
+// row-major tensor up to SEG_MAX chunks, and by column beyond.
+inline bool reg_path(int64_t R, int mode, int kind) {
+  return mode == TA_SCAN_FULL && kind == TA_SCORE_MAD && R <= COL_REG_MAX;
+}
 inline bool row_major_path(int64_t R, int mode, int kind) {
-  return mode == TA_SCAN_FULL && kind == TA_SCORE_MAD && pad_ranks(R) >= SEL_BRACKET_MIN_RP &&
+  return mode == TA_SCAN_FULL && kind == TA_SCORE_MAD && R > COL_REG_MAX &&
          transpose_groups_of(R) <= SEG_MAX;
 }
 
@@ -2348,12 +2262,17 @@ OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
       w.rp.sd = (int64_t *)take(ng * IG * 8);
       w.cs.zc = (double *)take(IG * 8);
       w.cs.zd = (double *)take(IG * 8);
+    } else if (reg_path(R, mode, kind)) {
+      w.cols = take(col_scan_ws_bytes(R, (int)IG));
     } else {
       w.Tt = (int64_t *)take((size_t)pad_ranks(R) * IG * 8);
-      if (kind == TA_SCORE_MAD && pad_ranks(R) >= SEL_BRACKET_MIN_RP)  // more than SEG_MAX chunks
+      if (kind == TA_SCORE_MAD)
         w.scr = (int64_t *)take((size_t)std::min<size_t>(IG, SEL_GRID_MAX) * sel_cap(R) * 8);
     }
-    if (kind == TA_SCORE_MAD) {
+    if (reg_path(R, mode, kind)) {
+    } else if (kind == TA_SCORE_MAD && !row_major_path(R, mode, kind)) {
+      w.cz = (ColZ *)take(IG * sizeof(ColZ));
+    } else if (kind == TA_SCORE_MAD) {
       w.cs.med2 = (int64_t *)take(IG * 8);
       w.cs.mad4 = (int64_t *)take(IG * 8);
       w.cs.sumdev = (int64_t *)take(IG * 8);
@@ -2585,37 +2504,37 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
       launch_sel_regions<true, true>((const void *)w.m_t, a.R, a.G, a.it, a.I, w.z_t, a.region_score,
                                      s);
     } else if (a.mode == TA_SCAN_FULL) {
-      if (IG > 0) {
+      int dev = 0, cus = 256;
+      (void)hipGetDevice(&dev);
+      (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+      hipError_t e = hipSuccess;
+      if (a.stats.rc > 0 && a.stats.rc != scan_stat_chunks(a.R, a.kind)) return hipErrorInvalidValue;
+      const bool reg = reg_path(a.R, a.mode, a.kind);
+      if (reg && IG > 0) {
+        e = launch_col_scan(a.T, a.R, a.I, a.G, a.it, a.stats, a.stats_ready, w.m_t, w.cols, cus, s);
+      } else if (IG > 0) {
         const dim3 tg((unsigned)transpose_groups_of(a.R), (IG + TT - 1) / TT);
         if (a.stats.rc > 0) {
-          if (a.stats.rc != transpose_groups_of(a.R)) return hipErrorInvalidValue;
           hipLaunchKernelGGL(transpose_kernel<true>, tg, dim3(256), 0, s, a.T, a.R, IG, a.G, a.it, w.Tt,
                              a.stats);
-          if (a.stats_ready) (void)hipEventRecord(a.stats_ready, s);
+          if (a.stats_ready) e = hipEventRecord(a.stats_ready, s);
         } else {
           hipLaunchKernelGGL(transpose_kernel<false>, tg, dim3(256), 0, s, a.T, a.R, IG, a.G, a.it, w.Tt,
                              a.stats);
         }
-        if (mad && pad_ranks(a.R) < SEL_BRACKET_MIN_RP) {
-          hipLaunchKernelGGL(col_select_radix, dim3(IG), dim3(CS), 0, s, w.Tt, a.R, w.cs);
-        } else if (mad) {
-          int dev = 0, cus = 256;
-          (void)hipGetDevice(&dev);
-          (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (mad) {
           const int grid = std::min(IG, std::min(SEL_GRID_MAX, SEL_WGS_PER_CU * cus));
           hipLaunchKernelGGL(col_select_bracket, dim3(grid), dim3(CS), 0, s, w.Tt, a.R, IG, w.scr,
-                             sel_cap(a.R), w.cs);
-        }
-        else
+                             sel_cap(a.R), w.cz);
+        } else {
           hipLaunchKernelGGL(col_moments, dim3(IG), dim3(CS), 0, s, w.Tt, a.R, w.cm);
+        }
       }
+      if (e == hipSuccess && mad && !reg) e = launch_score_tensor(a.T, a.R, a.I, a.G, a.it, w.cz, w.m_t, cus, s);
+      if (e != hipSuccess) return e;
       const unsigned nw = (unsigned)((a.G * ((a.R + 63) / 64) + 3) / 4);
-      if (mad)
-        hipLaunchKernelGGL((score_cols<true>), dim3(nw), dim3(256), 0, s, w.Tt, a.R, a.I, a.G, a.it,
-                           w.cs, w.cm, w.m_t);
-      else
-        hipLaunchKernelGGL((score_cols<false>), dim3(nw), dim3(256), 0, s, w.Tt, a.R, a.I, a.G, a.it,
-                           w.cs, w.cm, w.m_t);
+      if (!mad)
+        hipLaunchKernelGGL(score_cols, dim3(nw), dim3(256), 0, s, w.Tt, a.R, a.I, a.G, a.it, w.cm, w.m_t);
       if (mad)
         launch_sel_regions<true, true>((const void *)w.m_t, a.R, a.G, a.it, a.I, w.z_t, a.region_score,
                                        s);
@@ -2640,6 +2559,8 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
   return hipGetLastError();
 }
 
-int transpose_groups(int64_t R) { return transpose_groups_of(R); }
+int scan_stat_chunks(int64_t R, int32_t kind) {
+  return reg_path(R, TA_SCAN_FULL, kind) ? 1 : transpose_groups_of(R);
+}
 
 }  // namespace ta

@@ -50,6 +50,36 @@ def test_region_selection_edges(ta, h, oracle, R):
         assert int(o["n_flagged"].item()) == nf
 
 
+@pytest.mark.parametrize("R", [65, 300, 700, 1025, 2049, 3073, 4097, 6145, 8193, 12289, 16385, 24577])
+@pytest.mark.parametrize("gap", [2000.0, 3e9])
+def test_column_selection_in_a_plan(ta, h, oracle, R, gap):
+    """The scan's first pass in a plan, which also takes the imbalance columns,
+    at every launch shape of the column selection, with cells of microseconds
+    and with columns too spread for 32-bit offsets.  Odd row lengths."""
+    from paper_2605_03561_amd import synth
+    w = synth.plain_workload(seed=R, n_ranks=R, events=30, n_nodes=60, n_iters=3, n_regions=5,
+                             mean_gap_ns=gap)
+    h.set_tree(w.parent)
+    h.set_regions(w.marker, w.regions)
+    p = h.plan(ta.DeviceTraces(w.offsets, w.ts, w.ctx), 3, w.offsets, autotune=0, region=True)
+    for _ in range(2):
+        p.launch()
+    h.sync_status()
+    T, it = p.seg["tensor"].cpu().numpy(), p.seg["iters_found"].cpu().numpy()
+    st, score, flag, nf, reg = oracle.outliers(T, it)
+    assert st == 0
+    assert np.array_equal(p.out["region_score"].cpu().numpy(), reg)
+    assert np.array_equal(p.out["rank_score"].cpu().numpy(), score)
+    assert np.array_equal(p.out["rank_flag"].cpu().numpy(), flag)
+    _, ref = oracle.imbalance(T, it, span=p.seg["span"].cpu().numpy())
+    for k in ("min", "max"):
+        assert np.array_equal(p.imb[k].cpu().numpy(), ref[k])
+    for k in ("mean", "std", "max_minus_mean", "savings_per_iter", "balance_ratio", "cv_across",
+              "cv_within"):
+        np.testing.assert_allclose(p.imb[k].cpu().numpy(), ref[k], rtol=1e-12, atol=0)
+    p.close()
+
+
 @pytest.mark.parametrize("R", [1024, 1025, 4096, 4097, 8193, 16384, 16385, 32768, 32769])
 def test_prescreen_selection_edges(ta, h, R):
     """Second stage of the pre-screen's score and its top-k at the rank counts
