@@ -643,23 +643,22 @@ __global__ __launch_bounds__(256) void ae_rows_fill(const int64_t *__restrict__ 
 // Scoring.  One wave per rank (8 waves per workgroup share the weights in
 // LDS).  The rank's profile rows go through the network 32 at a time, as two
 // 16-row tiles of v_mfma_f32_16x16x32_bf16: every weight fragment read from
-// LDS feeds both tiles, and each layer's input fragments are read once and kept
-// in registers across its output tiles.  The FP32 input tile and the hidden
-// tile share one LDS buffer (the inputs the residual needs are held in
-// registers in the output layout), and the next 32 rows are loaded from HBM
-// into registers while the current ones are in the network.  No workgroup
-// barrier after the weights are staged.  The weights are the product's left
-// operand: a lane then holds four consecutive features of one row, which leave
-// as two packed conversions and one 8-byte LDS write (with the rows on the
-// left, as four conversions by hand of six instructions and four 2-byte writes,
-// the kernel was bound by those: 10,000 ranks x 300 rows 394 -> 327 us, 1.54 GB, 4.7 TB/s).
+// LDS feeds both tiles.  The FP32 input tile goes through LDS (the inputs the
+// residual needs are held in registers in the output layout), and the next 32
+// rows are loaded from HBM into registers while the current ones are in the
+// network.  No workgroup barrier after the weights are staged.  The weights are
+// the product's left operand: a lane then holds four consecutive features of
+// one row, two packed conversions (with the rows on the left, four conversions
+// by hand of six instructions and four 2-byte LDS writes bound the kernel), and
+// row swaps turn them into the next layer's operand, so the hidden layers stay
+// in registers.  10,000 ranks x 300 rows (1.54 GB): 394 us with the rows on the
+// left, 327 us with the hidden layers through LDS, 306 us now.
 //   kind 0: score = max_g mean_i (y - x)^2     kind 1: max_g |mean_i (y - x)|
 // ---------------------------------------------------------------------------
 constexpr int SW = 8;                  // waves per workgroup
 constexpr int SR = 32;                 // rows per wave step (two MFMA tiles)
 constexpr int P_W1 = 72, P_W2 = 136, P_W3 = 40, P_W4 = 136;   // padded row strides (bf16)
 constexpr int P_X = 68;                // FP32 row stride of the input tile
-constexpr int P_H = 136, P_H2 = 40;    // bf16 row strides of the hidden tiles
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
@@ -668,15 +667,8 @@ struct ScoreLds {
   uint16_t W1[AE_H1 * P_W1], W2[AE_H2 * P_W2], W3[AE_H3 * P_W3], W4[AE_IN * P_W4];
   float b[AE_NP - AE_NW];
   float mu[AE_IN], isd[AE_IN];
-  struct Wave {
-    union {
-      float X[SR * P_X];       // normalised inputs (FP32)
-      uint16_t H[SR * P_H];    // first, then third hidden layer (bf16)
-    } u;
-    uint16_t H2[SR * P_H2];
-  } wv[SW];
+  float X[SW][SR * P_X];  // a wave's normalised inputs (FP32)
 };
-static_assert(SR * P_X * 4 == SR * P_H * 2, "input and hidden tiles share a buffer");
 
 __device__ inline bf8 ld_bf8(const uint16_t *p) {
   return __builtin_bit_cast(bf8, *reinterpret_cast<const u4v *>(p));
@@ -709,11 +701,26 @@ __device__ inline f4 mfma32(bf8 a, bf8 b, f4 c) {
 }
 
 // Four features of a hidden layer after bias and ReLU, as bfloat16.
-__device__ inline void st_hidden(uint16_t *p, f4 acc, const float *bias) {
+__device__ inline void hidden(uint32_t *h, f4 acc, const float *bias) {
   const float4 b = *reinterpret_cast<const float4 *>(bias);
-  const uint2 u = {pack_bf2(fmaxf(acc[0] + b.x, 0.f), fmaxf(acc[1] + b.y, 0.f)),
-                   pack_bf2(fmaxf(acc[2] + b.z, 0.f), fmaxf(acc[3] + b.w, 0.f))};
-  *reinterpret_cast<uint2 *>(p) = u;
+  h[0] = pack_bf2(fmaxf(acc[0] + b.x, 0.f), fmaxf(acc[1] + b.y, 0.f));
+  h[1] = pack_bf2(fmaxf(acc[2] + b.z, 0.f), fmaxf(acc[3] + b.w, 0.f));
+}
+
+// From the output layout of two feature tiles (h[0], h[1]: features 4 * g + 0..3
+// of the first, h[2], h[3]: of the second, g = lane / 16) to the operand layout
+// of the next product, features 8 * g + 0..7 of the 32: the lane groups are
+// exchanged by two row swaps per register, with no LDS.
+__device__ inline bf8 next_operand(const uint32_t *h) {
+  u4v u;
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const auto x = __builtin_amdgcn_permlane32_swap(h[j], h[j + 2], false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(x[0], x[1], false, false);
+    u[j] = y[0];
+    u[j + 2] = y[1];
+  }
+  return __builtin_bit_cast(bf8, u);
 }
 
 // Sums v[0..16) over the 16 lanes that share lane / 16; lane l is left with
@@ -760,9 +767,7 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
     L.isd[k] = isd[k];
   }
   __syncthreads();
-  auto &V = L.wv[wid];
-  float *X = V.u.X;
-  uint16_t *H = V.u.H;
+  float *X = L.X[wid];
   // MFMA operand layout: A/B lane -> row lane & 15, k = 8 * (lane >> 4) + 0..7;
   // D lane -> rows 4 * (lane >> 4) + 0..3, column lane & 15.  A: 16 features of
   // the weights, B: 16 profile rows.
@@ -841,7 +846,8 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
           xr[t][nt] = *reinterpret_cast<const float4 *>(&X[(16 * t + row) * P_X + 16 * nt + fq]);
       }
       lds_wave_sync();
-      // L1: [32 x 64] -> [32 x 128]
+      // L1: [32 x 64] -> [32 x 128]; h[t][2 * nt ..]: feature tile nt of row tile t
+      uint32_t h[2][AE_H1 / 8];
 #pragma unroll
       for (int nt = 0; nt < AE_H1 / 16; nt++) {
         const bf8 w0 = ld_bf8(&L.W1[(16 * nt + row) * P_W1 + kq]);
@@ -851,17 +857,17 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
           f4 acc = {0.f, 0.f, 0.f, 0.f};
           acc = mfma32(w0, a1[t][0], acc);
           acc = mfma32(w1, a1[t][1], acc);
-          st_hidden(&H[(16 * t + row) * P_H + 16 * nt + fq], acc, bias + 16 * nt + fq);
+          hidden(&h[t][2 * nt], acc, bias + 16 * nt + fq);
         }
       }
-      lds_wave_sync();
       // L2: [32 x 128] -> [32 x 32]
+      uint32_t h2[2][AE_H2 / 8];
       {
         bf8 a2[2][4];
 #pragma unroll
         for (int t = 0; t < 2; t++)
 #pragma unroll
-          for (int k = 0; k < 4; k++) a2[t][k] = ld_bf8(&H[(16 * t + row) * P_H + 32 * k + kq]);
+          for (int k = 0; k < 4; k++) a2[t][k] = next_operand(&h[t][4 * k]);
 #pragma unroll
         for (int nt = 0; nt < AE_H2 / 16; nt++) {
           bf8 bw[4];
@@ -872,16 +878,15 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
             f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int k = 0; k < 4; k++) acc = mfma32(bw[k], a2[t][k], acc);
-            st_hidden(&V.H2[(16 * t + row) * P_H2 + 16 * nt + fq], acc, bias + AE_B2 - AE_B1 + 16 * nt + fq);
+            hidden(&h2[t][2 * nt], acc, bias + AE_B2 - AE_B1 + 16 * nt + fq);
           }
         }
       }
-      lds_wave_sync();
       // L3: [32 x 32] -> [32 x 128]
       {
         bf8 a3[2];
 #pragma unroll
-        for (int t = 0; t < 2; t++) a3[t] = ld_bf8(&V.H2[(16 * t + row) * P_H2 + kq]);
+        for (int t = 0; t < 2; t++) a3[t] = next_operand(h2[t]);
 #pragma unroll
         for (int nt = 0; nt < AE_H3 / 16; nt++) {
           const bf8 bw = ld_bf8(&L.W3[(16 * nt + row) * P_W3 + kq]);
@@ -889,18 +894,17 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
           for (int t = 0; t < 2; t++) {
             f4 acc = {0.f, 0.f, 0.f, 0.f};
             acc = mfma32(bw, a3[t], acc);
-            st_hidden(&H[(16 * t + row) * P_H + 16 * nt + fq], acc, bias + AE_B3 - AE_B1 + 16 * nt + fq);
+            hidden(&h[t][2 * nt], acc, bias + AE_B3 - AE_B1 + 16 * nt + fq);
           }
         }
       }
-      lds_wave_sync();
       // L4: [32 x 128] -> [32 x 64], residuals of the valid rows
       {
         bf8 a4[2][4];
 #pragma unroll
         for (int t = 0; t < 2; t++)
 #pragma unroll
-          for (int k = 0; k < 4; k++) a4[t][k] = ld_bf8(&H[(16 * t + row) * P_H + 32 * k + kq]);
+          for (int k = 0; k < 4; k++) a4[t][k] = next_operand(&h[t][4 * k]);
 #pragma unroll
         for (int nt = 0; nt < AE_IN / 16; nt++) {
           bf8 bw[4];
@@ -925,7 +929,6 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
           }
         }
       }
-      lds_wave_sync();  // the next step's inputs overwrite H
     }
     // lane l is left with feature 16 * ((l mod 16) / 4) + fq + l mod 4
     float best = 0.f;
@@ -1152,12 +1155,9 @@ __global__ __launch_bounds__(RS) void region_robust_reg(const float *__restrict_
         hi = u[j] > hi ? u[j] : hi;
       }
     }
-    for (int d = 32; d >= 1; d >>= 1) {
-      const uint32_t ol = __shfl_xor(lo, d, 64), oh = __shfl_xor(hi, d, 64);
-      lo = ol < lo ? ol : lo;
-      hi = oh > hi ? oh : hi;
-      c += __shfl_xor(c, d, 64);
-    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    c = wave_sum(c);
     if (lane == 0) {
       wmn[wid] = lo;
       wmx[wid] = hi;
@@ -1323,15 +1323,26 @@ __global__ __launch_bounds__(1024) void topk_reg(const float *__restrict__ score
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   uint64_t u[V];
   uint32_t ab = 0;
+  float f[V];
+#pragma unroll
+  for (int j = 0; j < V; j += 4) {
+    const int64_t r = (int64_t)t * V + j;
+    if (r + 4 <= R) {
+      const float4 q = *reinterpret_cast<const float4 *>(score + r);
+      f[j] = q.x;
+      f[j + 1] = q.y;
+      f[j + 2] = q.z;
+      f[j + 3] = q.w;
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; q++) f[j + q] = r + q < R ? score[r + q] : 0.f;
+    }
+  }
 #pragma unroll
   for (int j = 0; j < V; j++) {
-    const int64_t r = (int64_t)t * V + j;
-    u[j] = ~0ull;
-    if (r < R) {
-      const float f = score[r];
-      u[j] = fkey(f);
-      ab += f > thr ? 1u : 0u;
-    }
+    const bool in = (int64_t)t * V + j < R;
+    u[j] = in ? (uint64_t)fkey(f[j]) : ~0ull;
+    ab += in && f[j] > thr ? 1u : 0u;
   }
   sel_clear(L);
   // K*: the (R - k)-th smallest key; greater keys are all selected, keys equal

@@ -1880,9 +1880,11 @@ ta_status ta_prescreen(ta_handle h, const int64_t *tensor, int64_t n_ranks, int3
     e = ta::launch_ae_score(h->ae, tensor, n_ranks, n_iters, iters_found, score, aws,
                             h->ws_bytes - (fl + 256), s);
     const float thr = h->ae.threshold >= 0.f ? h->ae.threshold : 3.4e38f;
-    if (e == hipSuccess) e = ta::launch_topk(score, n_ranks, k, topk_ranks, above, thr, s);
+    // the count goes straight to the pinned host word: no copy before the wait
+    int32_t *pin_dev = nullptr;
     if (e == hipSuccess && !h->pin) e = hipHostMalloc((void **)&h->pin, sizeof(int32_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMemcpyAsync(h->pin, above, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&pin_dev, h->pin, 0);
+    if (e == hipSuccess) e = ta::launch_topk(score, n_ranks, k, topk_ranks, pin_dev, thr, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hipfail(h, e, "prescreen");
     const int32_t n_above = *h->pin;

@@ -55,6 +55,62 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t x) {
   return x;
 }
 
+// Reductions over the 64 lanes on the VALU (a few cycles per step where an
+// exchange through LDS waits for about a hundred); every lane gets the result.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t x, uint32_t none) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)x, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_or(uint64_t x, uint64_t none) {
+  return ((uint64_t)dpp_or<CTRL, ROWS>((uint32_t)(x >> 32), (uint32_t)(none >> 32)) << 32) |
+         dpp_or<CTRL, ROWS>((uint32_t)x, (uint32_t)none);
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int l) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t x, int l) {
+  return ((uint64_t)lane_value((uint32_t)(x >> 32), l) << 32) | lane_value((uint32_t)x, l);
+}
+template <typename K, class Op>
+__device__ __forceinline__ K wave_reduce(K x, K none, Op op) {
+  x = op(x, dpp_or<0x111, 0xf>(x, none));  // row_shr:1
+  x = op(x, dpp_or<0x112, 0xf>(x, none));
+  x = op(x, dpp_or<0x114, 0xf>(x, none));
+  x = op(x, dpp_or<0x118, 0xf>(x, none));
+  x = op(x, dpp_or<0x142, 0xa>(x, none));  // row_bcast:15
+  x = op(x, dpp_or<0x143, 0xc>(x, none));  // row_bcast:31
+  return lane_value(x, 63);
+}
+template <typename K>
+__device__ __forceinline__ K wave_min(K x) {
+  return wave_reduce(x, ~(K)0, [](K a, K b) { return a < b ? a : b; });
+}
+template <typename K>
+__device__ __forceinline__ K wave_max(K x) {
+  return wave_reduce(x, (K)0, [](K a, K b) { return a > b ? a : b; });
+}
+template <typename K>
+__device__ __forceinline__ K wave_sum(K x) {
+  return wave_reduce(x, (K)0, [](K a, K b) { return (K)(a + b); });
+}
+
+// x, hidden from the compiler: comparisons of all V registers with it in one
+// loop are then not kept as V lane masks (spilled scalar registers) for the
+// same comparisons in another.
+template <typename K>
+__device__ __forceinline__ K opaque(K x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Ends a loop body over V registers: the scheduler does not mix the steps of
+// more than four of them, which would keep a second set of registers busy.
+template <int N = 4>
+__device__ __forceinline__ void pace(int v) {
+  if (v % N == N - 1) __builtin_amdgcn_sched_barrier(0);
+}
+
 // The bins of a group start at zero and are left at zero by reg_select.
 template <int W, int NB, typename K>
 __device__ __forceinline__ void sel_clear(SelGroup<W, NB, K> &L) {
@@ -85,12 +141,12 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
   while (lo > 0 && cnt > (uint32_t)SEL_FEW) {
     const int w = lo < DB ? lo : DB, nlo = lo - w;
     const K b0 = (K)(pref << w), nb = (K)1 << w;
-    K h = hot;
-    if (HOT) asm volatile("" : "+v"(h));  // keeps V lane masks from being carried across the passes
+    const K h = HOT ? opaque(hot) : hot;
 #pragma unroll
     for (int v = 0; v < V; v++) {
       const K b = (K)((u[v] >> nlo) - b0);  // nlo < KB
       if ((!HOT || u[v] != h) && b < nb) atomicAdd(&L.hist[(uint32_t)b], 1u);
+      pace(v);
     }
     if (HOT && hot_cnt && t == 0) {
       const K b = (K)((hot >> nlo) - b0);
@@ -110,7 +166,11 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
     if (W > 1) {
       if (lane == 63) L.wsum[sw] = incl;
       group_sync<W>();
-      for (int q = 0; q < sw; q++) excl += L.wsum[q];
+#pragma unroll
+      for (int q = 0; q < W; q++) {
+        const uint32_t x = L.wsum[q];
+        excl += q < sw ? x : 0u;
+      }
     }
     if (excl <= k && k < excl + own) {
       uint32_t cum = excl;
@@ -149,9 +209,10 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
   }
   group_sync<W>();
   if (few) {
+    const K lim = opaque(last);
 #pragma unroll
     for (int v = 0; v < V; v++)
-      if (top(u[v], lo) == pref && u[v] <= last) {
+      if (top(u[v], lo) == pref && u[v] <= lim) {
         const uint32_t at = atomicAdd(&L.nfew, 1u);
         if (at < (uint32_t)SEL_FEW) L.few[at] = u[v];
       }
@@ -160,10 +221,7 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
     K m = ~(K)0;
 #pragma unroll
     for (int v = 0; v < V; v++) m = top(u[v], lo) > pref && u[v] < m ? u[v] : m;
-    for (int d = 32; d >= 1; d >>= 1) {
-      const K o = __shfl_xor(m, d, 64);
-      m = o < m ? o : m;
-    }
+    m = wave_min(m);
     if (lane == 0) atomicMin(&L.above, m);
   }
   group_sync<W>();
@@ -172,8 +230,10 @@ __device__ __forceinline__ void reg_select(SelGroup<W, NB, K> &L, const K (&u)[V
     const int nf = L.nfew < (uint32_t)SEL_FEW ? (int)L.nfew : SEL_FEW;
     const K x = lane < nf ? L.few[lane] : ~(K)0;
     uint32_t rank = 0;
-    for (int j = 0; j < nf; j++) {
-      const K y = L.few[j];
+    const int nu = __builtin_amdgcn_readfirstlane(nf);
+#pragma unroll 4
+    for (int j = 0; j < nu; j++) {
+      const K y = lane_value(x, j);
       rank += (y < x || (y == x && j < lane)) ? 1u : 0u;
     }
     if (lane < nf) {
