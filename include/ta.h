@@ -224,7 +224,7 @@ ta_status ta_imbalance_noalloc(ta_handle h, const int64_t *tensor, int64_t n_ran
  * Cell values must lie in (-2^61, 2^61); n_iters * n_regions <= 4,194,240
  * (TA_ERR_SIZE_OVERFLOW otherwise).  The FULL scan's workspace is about as
  * large as the tensor or smaller: none of that size for the robust kind up to
- * 1,024 ranks; a 32-bit column-major copy (half its size) up to 32,768 ranks;
+ * 1,024 ranks; a 32-bit column-major copy (half its size) up to 49,152 ranks;
  * above, a 32-bit copy and a slot of 256 cells per column and chunk of 1,024
  * ranks for the bracket interiors (a quarter of the tensor), plus the column
  * samples and one gathered column per selection workgroup; for the plain

@@ -12,9 +12,10 @@
 //                 do not fit in 32 bits is selected by col_select_wide and
 //                 scored from the tensor
 // Everything between the count of a column and its MAD happens on registers
-// (ta_select.h).  The old path moved 8-byte copies and read each column about
-// ten times, from L2, for the radix passes.
+// (ta_select.h).  The row-major passes of longer columns (k_outliers.hip) took
+// 10.0 ms for 32,000 columns of 40,000 ranks where this takes 7.1.
 #include <algorithm>
+#include <type_traits>
 
 #include "ta_device.h"
 #include "ta_scan.h"
@@ -43,21 +44,52 @@ constexpr int CT = 128;  // ranks per tile of the copy; its columns are padded t
 __host__ __device__ inline int64_t copy_ranks(int64_t R) { return (R + CT - 1) / CT * CT; }
 
 // Column-major copy cp[IG][copy_ranks(R)] of the tensor in 32-bit key words:
-// 64 columns x 128 ranks per workgroup, all 16 loads of a thread in flight,
-// 512-byte pieces of rows in and of columns out.  Bound by HBM (12 bytes per
-// cell): 9,600 columns of 10,000 ranks in 229 us, 5.0 TB/s (the 8-byte copy that
-// it replaces, with the statistics, 358 us).
-__global__ __launch_bounds__(256) void col_copy(const int64_t *__restrict__ T, int64_t R, int IG, int G,
-                                                const int32_t *__restrict__ it, uint32_t *__restrict__ cp) {
+// 64 columns x 128 ranks per workgroup, all 16 loads of a thread in flight, 512-byte pieces of rows in and of columns out.  Bound by
+// HBM (12 bytes per cell): 9,600 columns of 10,000 ranks in 229 us, 5.0 TB/s
+// (the 8-byte copy that it replaces, with the statistics, 358 us).  Several tiles
+// per workgroup were slower (330 -> 537 us for 16,000 ranks): one tile's loads
+// wait for the other's stores.
+// STATS: also each column's valid cells as one chunk of the imbalance partials
+// per workgroup.  The copy leaves the VALU some room for it (233 -> 279 us), the
+// selection does not (206 -> 311 us).
+struct ColSum {  // exact, over any cells of one column
+  int64_t s1;
+  uint64_t lo, hi;  // 128-bit sum of squares
+  int64_t mn, mx;
+  uint32_t n;
+  __device__ void add(const ColSum &o) {
+    const u128 q = (((u128)hi << 64) | lo) + (((u128)o.hi << 64) | o.lo);
+    n += o.n;
+    s1 += o.s1;
+    lo = (uint64_t)q;
+    hi = (uint64_t)(q >> 64);
+    mn = o.mn < mn ? o.mn : mn;
+    mx = o.mx > mx ? o.mx : mx;
+  }
+};
+
+template <bool STATS>
+__global__ __launch_bounds__(256, 4) void col_copy(const int64_t *__restrict__ T, int64_t R, int IG, int G,
+                                                const int32_t *__restrict__ it, uint32_t *__restrict__ cp,
+                                                ColPartials ps) {
   constexpr int LD = CT + 4;  // 16-byte rows, columns four banks apart
-  __shared__ uint32_t tile[64 * LD];
+  union Lds {
+    uint32_t tile[64 * LD];
+    ColSum sum[8][64];
+    __device__ Lds() {}
+  };
+  __shared__ Lds L;
   const int c0 = (int)blockIdx.y * 64;
-  const int64_t Rp = copy_ranks(R), r0 = (int64_t)blockIdx.x * CT;
+  const int64_t Rp = copy_ranks(R);
   const int p2 = 2 * (threadIdx.x & 31), k0 = threadIdx.x >> 5;
   const int ca = c0 + p2, ia = ca / G, ib = (ca + 1) / G;
   const bool vec = (IG & 1) == 0, ha = ca < IG, hb = ca + 1 < IG;
-  const int64_t b0 = ha ? T[ca] : 0, b1 = hb ? T[ca + 1] : 0;
+  const int64_t base[2] = {ha ? T[ca] : 0, hb ? T[ca + 1] : 0};
+  ColSum tot[2];
+#pragma unroll
+  for (int h = 0; h < 2; h++) tot[h] = ColSum{0, 0, 0, INT64_MAX, INT64_MIN, 0};
   constexpr int U = CT / 8;
+  const int64_t r0 = (int64_t)blockIdx.x * CT;
   v2ll x[U];
   int nit[U];
 #pragma unroll
@@ -76,14 +108,48 @@ __global__ __launch_bounds__(256) void col_copy(const int64_t *__restrict__ T, i
       }
     }
   }
-  auto word = [](int64_t d, bool in) {
-    const uint32_t w = (d >= HALF32 || d <= -HALF32) ? WIDE : (uint32_t)(d + HALF32);
-    return in ? w : none<uint32_t>();
-  };
 #pragma unroll
-  for (int k = 0; k < U; k++) {
-    tile[p2 * LD + k0 + 8 * k] = word((int64_t)x[k].x - b0, ha && ia < nit[k]);
-    tile[(p2 + 1) * LD + k0 + 8 * k] = word((int64_t)x[k].y - b1, hb && ib < nit[k]);
+  for (int h = 0; h < 2; h++) {
+    bool far = false;  // an offset of 2^29 and more
+    int64_t sum = 0;
+    uint64_t sq = 0;
+    int32_t mn = INT32_MAX, mx = INT32_MIN;
+    uint32_t n = 0;
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const bool in = h == 0 ? ha && ia < nit[k] : hb && ib < nit[k];
+      const int64_t d = (int64_t)(h == 0 ? x[k].x : x[k].y) - base[h];
+      const uint32_t w = (d >= HALF32 || d <= -HALF32) ? WIDE : (uint32_t)(d + HALF32);
+      L.tile[(p2 + h) * LD + k0 + 8 * k] = in ? w : none<uint32_t>();
+      if (STATS) {
+        far |= in && (w == WIDE || (uint32_t)((int32_t)d + (1 << 29)) > (1u << 30));
+        const int32_t e = in ? (int32_t)d : 0;
+        const uint32_t m = (uint32_t)(e < 0 ? -e : e);
+        n += in ? 1u : 0u;
+        sum += e;
+        sq += (uint64_t)m * m;
+        mn = in && e < mn ? e : mn;
+        mx = in && e > mx ? e : mx;
+      }
+    }
+    if (STATS && !far && n > 0) {
+      // sum (base + d)^2 = n base^2 + 2 base sum d + sum d^2, exactly
+      const i128 b = base[h];
+      const u128 q = (u128)((i128)n * b * b + 2 * b * (i128)sum) + sq;
+      tot[h].add(ColSum{(int64_t)n * base[h] + sum, (uint64_t)q, (uint64_t)(q >> 64), base[h] + mn,
+                        base[h] + mx, n});
+    }
+    if (STATS && far) {
+#pragma unroll 1
+      for (int k = 0; k < U; k++) {
+        const int64_t r = r0 + k0 + 8 * k;
+        const int c = ca + h;
+        if (r >= R || c >= IG || (it && c / G >= it[r])) continue;
+        const int64_t v = T[r * IG + c];
+        const u128 q = (u128)((i128)v * v);
+        tot[h].add(ColSum{v, (uint64_t)q, (uint64_t)(q >> 64), v, v, 1});
+      }
+    }
   }
   __syncthreads();
   const int q = 4 * (threadIdx.x & 31);
@@ -92,13 +158,31 @@ __global__ __launch_bounds__(256) void col_copy(const int64_t *__restrict__ T, i
     const int c = k0 + 8 * k;
     if (c0 + c < IG)
       *reinterpret_cast<v4u *>(cp + (int64_t)(c0 + c) * Rp + r0 + q) =
-          *reinterpret_cast<const v4u *>(&tile[c * LD + q]);
+          *reinterpret_cast<const v4u *>(&L.tile[c * LD + q]);
+  }
+  if (STATS) {
+    __syncthreads();
+    L.sum[k0][p2] = tot[0];
+    L.sum[k0][p2 + 1] = tot[1];
+    __syncthreads();
+    const int c = c0 + (int)threadIdx.x;
+    if (threadIdx.x < 64 && c < IG) {
+      ColSum s = L.sum[0][threadIdx.x];
+      for (int k = 1; k < 8; k++) s.add(L.sum[k][threadIdx.x]);
+      const int64_t p = (int64_t)blockIdx.x * IG + c;
+      ps.n[p] = s.n;
+      ps.s1[p] = s.s1;
+      ps.lo[p] = s.lo;
+      ps.hi[p] = s.hi;
+      ps.mn[p] = s.mn;
+      ps.mx[p] = s.mx;
+    }
   }
 }
 
 // What the waves of a column exchange.
 struct ColRed {
-  uint64_t mn, mx, a, b, c;
+  uint64_t mn, mx, a;
   uint32_t n, m;
 };
 
@@ -110,30 +194,28 @@ struct ColOut {
 };
 
 // From a column's key words in the registers of a group of W waves (u[V] per
-// lane) to its coefficients and statistics.  `off` is what a key word of 0
-// stands for.  n = 0 on return of `false`: the column is left to
-// col_select_wide.  Costs about 30 instructions per key, which bound the
-// selection of long columns (STATS: 8 more).
+// lane) to its coefficients, and with STATS its imbalance statistics.  `off` is
+// what a key word of 0 stands for.  A wide column is left to col_select_wide.
 template <typename K, int V, int W, int NB, bool STATS>
 __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, ColRed *red, int64_t off,
                                               int col, bool have, const ColOut &o) {
   constexpr bool NARROW = sizeof(K) == 4;
+  static_assert(!STATS || (W == 1 && !NARROW), "statistics: 64-bit words, one wave");
   const int lane = (int)(threadIdx.x & 63), sw = (int)(threadIdx.x >> 6) % W;
   const bool mine = sw == 0 && lane == 0 && have;
   uint32_t n = 0;
   K mn = none<K>(), mx = 0;  // mx: the largest + 1 (0 for none)
 #pragma unroll
   for (int v = 0; v < V; v++) {
-    n += (uint32_t)__popcll(__ballot(u[v] != none<K>()));
+    n += u[v] != none<K>() ? 1u : 0u;
     mn = u[v] < mn ? u[v] : mn;
     const K w = u[v] + 1;
     mx = w > mx ? w : mx;
+    pace(v);
   }
-  for (int d = 32; d >= 1; d >>= 1) {
-    const K a = __shfl_xor(mn, d, 64), b = __shfl_xor(mx, d, 64);
-    mn = a < mn ? a : mn;
-    mx = b > mx ? b : mx;
-  }
+  mn = wave_min(mn);
+  mx = wave_max(mx);
+  n = wave_sum(n);
   if (W > 1) {
     if (lane == 0) {
       red[sw].mn = mn;
@@ -161,69 +243,38 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
 
   // offsets from the smallest cell (a word that is no key stays above `range`)
   uint32_t zeros = 0;
-  uint64_t su = 0, sq = 0, sh = 0;
-  u128 q64 = 0;
-  const bool small = range < (K)0x1fffffffu;  // V <= 64 squares fit in 64 bits
+  uint64_t su = 0;
+  u128 tot = 0;
 #pragma unroll
   for (int v = 0; v < V; v++) {
     if (STATS && u[v] != none<K>()) {
-      if (NARROW) {
-        const uint64_t w = (uint64_t)(uint32_t)(u[v] - mn), ww = w * w;
-        su += w;
-        if (small) {
-          sq += ww;
-        } else {
-          sq += (uint32_t)ww;
-          sh += ww >> 32;
-        }
-      } else {
-        const int64_t x = (int64_t)(u[v] - (K)HALF64);
-        su += (uint64_t)x;
-        q64 += (u128)((i128)x * x);
-      }
+      const int64_t x = (int64_t)(u[v] - (K)HALF64);
+      su += (uint64_t)x;
+      tot += (u128)((i128)x * x);
     }
     u[v] = u[v] - mn;
-    zeros += (uint32_t)__popcll(__ballot(u[v] == 0));
+    zeros += u[v] == 0 ? 1u : 0u;
+    pace(v);
   }
-  if (STATS || W > 1) {
-    u128 tot = NARROW ? (u128)sq + ((u128)sh << 32) : q64;
-    if (STATS)
-      for (int d = 32; d >= 1; d >>= 1) {
-        const uint64_t ol = __shfl_xor((uint64_t)tot, d, 64), oh = __shfl_xor((uint64_t)(tot >> 64), d, 64);
-        tot += ((u128)oh << 64) | ol;
-        su += __shfl_xor(su, d, 64);
-      }
-    if (W > 1) {
-      if (lane == 0) {
-        red[sw].a = (uint64_t)tot;
-        red[sw].b = (uint64_t)(tot >> 64);
-        red[sw].c = su;
-        red[sw].m = zeros;
-      }
-      __syncthreads();
-      zeros = 0;
+  zeros = wave_sum(zeros);
+  if (W > 1) {
+    if (lane == 0) red[sw].m = zeros;
+    __syncthreads();
+    zeros = 0;
 #pragma unroll
-      for (int q = 0; q < W; q++) zeros += red[q].m;
-      if (STATS && mine) {
-        tot = 0;
-        su = 0;
-        for (int q = 0; q < W; q++) {
-          tot += ((u128)red[q].b << 64) | red[q].a;
-          su += red[q].c;
-        }
-      }
-      __syncthreads();
-    }
-    if (STATS && mine) {
+    for (int q = 0; q < W; q++) zeros += red[q].m;
+    __syncthreads();
+  }
+  if (STATS) {
+    // 32-bit pieces of the 128-bit totals, summed apart
+    const uint64_t p0 = wave_sum((uint64_t)(uint32_t)tot), p1 = wave_sum((uint64_t)(uint32_t)(tot >> 32)),
+                   p2 = wave_sum((uint64_t)(tot >> 64));
+    tot = (u128)p0 + ((u128)p1 << 32) + ((u128)p2 << 64);
+    su = wave_sum(su);
+    if (mine) {
       const int64_t lo = off + (int64_t)mn;  // the smallest cell
-      int64_t s1 = (int64_t)su;
-      if (NARROW) {
-        // sum (lo + u)^2 = n lo^2 + 2 lo sum u + sum u^2, exactly
-        s1 = (int64_t)n * lo + (int64_t)su;
-        tot += (u128)((i128)n * lo * lo + 2 * (i128)lo * (i128)su);
-      }
       o.ps.n[col] = n;
-      o.ps.s1[col] = s1;
+      o.ps.s1[col] = (int64_t)su;
       o.ps.lo[col] = (uint64_t)tot;
       o.ps.hi[col] = (uint64_t)(tot >> 64);
       o.ps.mn[col] = n > 0 ? lo : INT64_MAX;
@@ -241,8 +292,9 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
   // the median, then the MAD of |2u - med2|
   const uint32_t k = (n - 1) / 2;
   const bool even = (n & 1) == 0;
-  K a, b;
-  reg_select<true>(S, u, (K)0, zeros, range, nbits64(range), n, k, even, a, b);
+  K a = 0, b = 0;
+  if (k + (even ? 1u : 0u) >= zeros)  // else both middle cells are the smallest
+    reg_select<true>(S, u, (K)0, zeros, range, nbits64(range), n, k, even, a, b);
   const K m2 = a + b;
   uint32_t hits = 0;  // deviations equal to med2: the smallest cells', which may be many
 #pragma unroll
@@ -250,8 +302,10 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
     const K t = 2 * u[v];
     const K d = t > m2 ? t - m2 : m2 - t;
     u[v] = u[v] <= range ? d : none<K>();
-    hits += (uint32_t)__popcll(__ballot(u[v] == m2));
+    hits += u[v] == m2 ? 1u : 0u;
+    pace(v);
   }
+  hits = wave_sum(hits);
   if (W > 1) {
     if (lane == 0) red[sw].m = hits;
     __syncthreads();
@@ -260,13 +314,15 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
     for (int q = 0; q < W; q++) hits += red[q].m;
   }
   const K far = (K)(2 * range - m2), dmax = far > m2 ? far : m2;
-  reg_select<true>(S, u, m2, hits, dmax, nbits64(dmax), n, k, even, a, b);
+  a = b = 0;
+  if (m2 != 0 || k + (even ? 1u : 0u) >= zeros)  // else both middle deviations are 0
+    reg_select<true>(S, u, m2, hits, dmax, nbits64(dmax), n, k, even, a, b);
   const uint64_t mad4 = (uint64_t)a + (uint64_t)b;
   uint64_t sd = 0;  // the sum of the deviations is wanted when the MAD is 0
   if (mad4 == 0) {
 #pragma unroll
     for (int v = 0; v < V; v++) sd += u[v] <= dmax ? (uint64_t)u[v] : 0;
-    for (int d = 32; d >= 1; d >>= 1) sd += __shfl_xor(sd, d, 64);
+    sd = wave_sum(sd);
     if (W > 1) {
       if (lane == 0) red[sw].a = sd;
       __syncthreads();
@@ -289,13 +345,20 @@ constexpr int col_bins() {  // 4 to 16 bins per lane of a single wave, else 2,04
   return W > 1 ? 2048 : (V <= 4 ? 256 : V <= 8 ? 512 : 1024);
 }
 
+// Waves per SIMD that V key words and what else a lane needs leave room for (the
+// compiler takes up to twice the registers when it is not told).
+template <int V>
+constexpr int sel_waves() {
+  return V <= 40 ? 8 : V <= 48 ? 6 : V <= 64 ? 5 : 4;
+}
+
 // Columns of the 32-bit copy: W waves and V key words per lane each; a single
-// wave's columns come four to a workgroup.  Bound by its instructions (30 to 40
-// per key): 9,600 columns of 10,000 ranks with their statistics 355 us, radix
-// passes over the column in memory 566 us; 11,520 columns of 9,190 ranks 286 us
-// against 1,296.
-template <int W, int V, bool STATS>
-__global__ __launch_bounds__(W > 1 ? 64 * W : 256) void col_select(const uint32_t *__restrict__ cp, int64_t R,
+// wave's columns come four to a workgroup.  Radix passes over the column in
+// memory took 566 us for 9,600 columns of 10,000 ranks and 1,296 us for 11,520
+// of 9,190; this takes 206 and 228 us, bound by its instructions (about 30 per
+// key) and the LDS atomics (a quarter of the time).
+template <int W, int V>
+__global__ __launch_bounds__(W > 1 ? 64 * W : 256, sel_waves<V>()) void col_select(const uint32_t *__restrict__ cp, int64_t R,
                                                                    int IG, const int64_t *__restrict__ T,
                                                                    ColOut o) {
   constexpr int C = W > 1 ? 1 : 4, NB = col_bins<W, V>();
@@ -319,13 +382,12 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256) void col_select(const uint32_
   }
   const int64_t off = T[col] - HALF32;
   sel_clear(L[cl]);
-  select_column<uint32_t, V, W, NB, STATS>(u, L[cl], red, off, col, true, o);
+  select_column<uint32_t, V, W, NB, false>(u, L[cl], red, off, col, true, o);
 }
 
 // The columns that the 32-bit form marked wide, in 64-bit words straight from
 // the tensor (8-byte pieces of rows: for data with a spread of 2^31 ns and
 // more within a column).  Returns at once when there is none.
-template <bool STATS>
 __global__ __launch_bounds__(1024) void col_select_wide(const int64_t *__restrict__ T, int64_t R, int IG,
                                                         int G, const int32_t *__restrict__ it, ColOut o) {
   constexpr int W = 16, V = (int)(COL_REG_MAX / 1024);
@@ -350,7 +412,7 @@ __global__ __launch_bounds__(1024) void col_select_wide(const int64_t *__restric
     }
     __syncthreads();
     sel_clear(L);
-    select_column<uint64_t, V, W, 2048, STATS>(u, L, red, -HALF64, col, true, o);
+    select_column<uint64_t, V, W, 2048, false>(u, L, red, -HALF64, col, true, o);
   }
 }
 
@@ -443,65 +505,75 @@ __device__ __forceinline__ int rank_iters(const int32_t *it, int64_t r, int I) {
 }
 
 // m(r,g) = (1/n_r) sum over i < n_r, ascending, of z(r,i,g), from the
-// column-major copy: a wave owns 64 * RPL consecutive ranks of one region, so
-// the column's numbers are scalars; IU iterations' cells are loaded before the
-// first is scored.  9,600
-// columns of 10,000 ranks in 145 us (2.7 TB/s), 216 us from the 8-byte copy
-// with a division and a wait for every cell.
+// column-major copy: a workgroup owns 256 * RPL consecutive ranks of one
+// region.  The region's column numbers are staged in LDS, SI iterations at a
+// time, and IU iterations' cells are loaded before the first is scored (read by
+// scalar loads, the numbers kept every iteration waiting: 1,741 ranks x 19,200
+// columns 127 -> 63 us, 10,000 x 9,600 145 -> 100 us).  Bound by the copy's 4
+// bytes per cell for long columns, by the loads' round trips for short ones.
 template <int RPL, int IU>
 __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ cp, const int64_t *__restrict__ T,
                                                   int64_t R, int I, int G, const int32_t *__restrict__ it,
                                                   const ColZ *__restrict__ cz, const double *__restrict__ mu,
                                                   double *m_t) {
-  const int lane = (int)(threadIdx.x & 63);
-  const int64_t rb = (R + 64 * RPL - 1) / (64 * RPL);
-  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int g = __builtin_amdgcn_readfirstlane((int)(wave / rb));
-  if (g >= G) return;
-  const int64_t Rp = copy_ranks(R), r0 = ((wave % rb) * 64 + lane) * RPL;
-  const bool on = r0 < R;
-  const uint32_t *p = cp + (int64_t)g * Rp + (on ? r0 : 0);
+  constexpr int SI = 256;
+  struct alignas(16) Num {
+    double mu, zc, zd, zy;
+  };
+  __shared__ Num num[SI];
+  const int tid = (int)threadIdx.x;
+  const int64_t rb = (R + 256 * RPL - 1) / (256 * RPL);
+  const int g = (int)(blockIdx.x / rb);
+  const int64_t Rp = copy_ranks(R), r0 = ((blockIdx.x % rb) * 256 + tid) * RPL;
+  const uint32_t *p = cp + (int64_t)g * Rp + (r0 < R ? r0 : 0);
   double acc[RPL];
 #pragma unroll
   for (int q = 0; q < RPL; q++) acc[q] = 0.0;
-  for (int i0 = 0; i0 < I; i0 += IU) {
-    uint32_t w[IU][RPL];
-#pragma unroll
-    for (int j = 0; j < IU; j++) {
-      const int i = i0 + j < I ? i0 + j : I - 1;
-      const uint32_t *s = p + (int64_t)i * G * Rp;
-      if (RPL == 4) {
-        const v4u v = *reinterpret_cast<const v4u *>(s);
-        w[j][0] = v.x;
-        w[j][1 % RPL] = v.y;
-        w[j][2 % RPL] = v.z;
-        w[j][3 % RPL] = v.w;
-      } else {
-        w[j][0] = s[0];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < IU; j++) {
-      if (i0 + j >= I) break;
-      const int64_t c = (int64_t)(i0 + j) * G + g;
+  for (int s0 = 0; s0 < I; s0 += SI) {
+    const int ns = I - s0 < SI ? I - s0 : SI;
+    __syncthreads();  // the previous numbers are read
+    if (tid < ns) {
+      const int64_t c = (int64_t)(s0 + tid) * G + g;
       const ColZ z = cz[c];
-      const double m = mu[c];
-      if (m == m) {
+      num[tid] = Num{mu[c], z.zc, z.zd, z.zy};
+    }
+    __syncthreads();
+    for (int i0 = 0; i0 < ns; i0 += IU) {
+      uint32_t w[IU][RPL];
 #pragma unroll
-        for (int q = 0; q < RPL; q++) {
-          // 2x - med2 in key words: both terms are integers below 2^34
-          const double d = fma(2.0, (double)w[j][q], -m);
-          const double t = acc[q] + div_by(d * z.zc, z.zd, z.zy);
-          acc[q] = w[j][q] != none<uint32_t>() ? t : acc[q];
+      for (int j = 0; j < IU; j++) {
+        const int i = i0 + j < ns ? i0 + j : ns - 1;
+        const uint32_t *src = p + (int64_t)(s0 + i) * G * Rp;
+        if (RPL == 4) {
+          const v4u v = *reinterpret_cast<const v4u *>(src);
+          w[j][0] = v.x;
+          w[j][1 % RPL] = v.y;
+          w[j][2 % RPL] = v.z;
+          w[j][3 % RPL] = v.w;
+        } else {
+          w[j][0] = src[0];
         }
-      } else {  // a wide column
+      }
 #pragma unroll
-        for (int q = 0; q < RPL; q++) {
-          const int64_t r = r0 + q;
-          if (r < R && i0 + j < rank_iters(it, r, I)) {
-            const int64_t x = T[r * (int64_t)I * G + c];
-            acc[q] += div_by((double)(2 * x - z.med2) * z.zc, z.zd, z.zy);
+      for (int j = 0; j < IU; j++) {
+        if (i0 + j >= ns) break;
+        const Num z = num[i0 + j];
+        if (z.mu == z.mu) {
+#pragma unroll
+          for (int q = 0; q < RPL; q++) {
+            // 2x - med2 in key words: both terms are integers below 2^34
+            const double d = fma(2.0, (double)w[j][q], -z.mu);
+            const double t = acc[q] + div_by(d * z.zc, z.zd, z.zy);
+            acc[q] = w[j][q] != none<uint32_t>() ? t : acc[q];
           }
+        } else {  // a wide column
+          const int64_t c = (int64_t)(s0 + i0 + j) * G + g, med2 = cz[c].med2;
+#pragma unroll
+          for (int q = 0; q < RPL; q++)
+            if (r0 + q < R && s0 + i0 + j < rank_iters(it, r0 + q, I)) {
+              const int64_t x = T[(r0 + q) * (int64_t)I * G + c];
+              acc[q] += div_by((double)(2 * x - med2) * z.zc, z.zd, z.zy);
+            }
         }
       }
     }
@@ -514,9 +586,66 @@ __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ c
     }
 }
 
-// The same from the row-major tensor.  A lane owns a region of RPL consecutive
-// ranks; with fewer than 64 regions a wave takes 64 >> lgp ranks' rows side by
-// side.  1,600 columns of 64 ranks: 33 us against 65 us with one load in flight.
+// The same for few ranks, from the row-major tensor: a workgroup scores NR
+// ranks' rows, every cell by a thread of its own, into LDS, and one thread per
+// region then adds the scores in ascending iteration.  A chain of additions in
+// LDS instead of a chain of loads: 1,600 columns of 64 ranks 33 -> 6 us, 6,400
+// of 1,000 ranks 37 -> 26 us.  G <= 256.
+constexpr int SC_CELLS = 4096;  // scores in LDS
+template <int NR>
+__global__ __launch_bounds__(256) void score_rank(const int64_t *__restrict__ T, int64_t R, int I, int G,
+                                                  const int32_t *__restrict__ it,
+                                                  const ColZ *__restrict__ cz, double *m_t) {
+  __shared__ double sc[SC_CELLS];
+  const int tid = (int)threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * NR, IG = (int64_t)I * G;
+  int ni[NR], nmax = 0;
+#pragma unroll
+  for (int q = 0; q < NR; q++) {
+    ni[q] = r0 + q < R ? rank_iters(it, r0 + q, I) : 0;
+    nmax = ni[q] > nmax ? ni[q] : nmax;
+  }
+  constexpr int CELLS = SC_CELLS / NR, U = CELLS / 256;
+  const int ic = CELLS / G;  // iterations per turn
+  double acc[NR];
+#pragma unroll
+  for (int q = 0; q < NR; q++) acc[q] = 0.0;
+  for (int i0 = 0; i0 < nmax; i0 += ic) {
+    const int in = nmax - i0 < ic ? nmax - i0 : ic, cells = in * G;
+    const int64_t c0 = (int64_t)i0 * G;
+    __syncthreads();  // the previous scores are added
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int k = u * 256 + tid;
+      if (k < cells) {
+        const ColZ z = cz[c0 + k];
+#pragma unroll
+        for (int q = 0; q < NR; q++) {
+          const int64_t x = r0 + q < R ? T[(r0 + q) * IG + c0 + k] : 0;
+          sc[q * CELLS + k] = div_by((double)(2 * x - z.med2) * z.zc, z.zd, z.zy);
+        }
+      }
+    }
+    __syncthreads();
+    if (tid < G) {
+#pragma unroll
+      for (int q = 0; q < NR; q++) {
+        const int e = ni[q] - i0 < in ? ni[q] - i0 : in;
+        const double *s = sc + q * CELLS + tid;
+#pragma unroll 8
+        for (int i = 0; i < e; i++) acc[q] += s[i * G];
+      }
+    }
+  }
+  if (tid < G)
+#pragma unroll
+    for (int q = 0; q < NR; q++)
+      if (r0 + q < R) m_t[(int64_t)tid * R + r0 + q] = ni[q] > 0 ? acc[q] / (double)ni[q] : 0.0;
+}
+
+// The same from the row-major tensor for many regions or ranks.  A lane owns a
+// region of RPL consecutive ranks; with fewer than 64 regions a wave takes 64
+// >> lgp ranks' rows side by side.
 template <int RPL, int IU>
 __global__ __launch_bounds__(256) void score_tensor(const int64_t *__restrict__ T, int64_t R, int I, int G,
                                                     int lgp, const int32_t *__restrict__ it,
@@ -590,6 +719,10 @@ ColWs carve(void *ws, int64_t R, int IG, size_t *used) {
 
 }  // namespace
 
+int col_stat_chunks(int64_t R) {
+  return R <= COL_DIRECT_MAX ? 1 : (int)(copy_ranks(R) / CT);
+}
+
 size_t col_scan_ws_bytes(int64_t R, int IG) {
   size_t used = 0;
   carve((void *)0x100, R, IG, &used);
@@ -630,40 +763,62 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
     e = hipGetLastError();
     if (e == hipSuccess && stats && stats_ready) e = hipEventRecord(stats_ready, s);
     if (e != hipSuccess) return e;
-    return launch_score_tensor(T, R, I, G, it, w.cz, m_t, cus, s);
+    if (G > 256) return launch_score_tensor(T, R, I, G, it, w.cz, m_t, cus, s);
+    // two ranks of a workgroup share the column numbers once that leaves one
+    // workgroup per CU
+    if (R >= 2 * (int64_t)cus)
+      hipLaunchKernelGGL(score_rank<2>, dim3((unsigned)((R + 1) / 2)), dim3(256), 0, s, T, R, I, G, it,
+                         (const ColZ *)w.cz, m_t);
+    else
+      hipLaunchKernelGGL(score_rank<1>, dim3((unsigned)R), dim3(256), 0, s, T, R, I, G, it,
+                         (const ColZ *)w.cz, m_t);
+    return hipGetLastError();
   }
   const int64_t Rp = copy_ranks(R);
-  hipLaunchKernelGGL(col_copy, dim3((unsigned)(Rp / CT), (unsigned)((IG + 63) / 64)), dim3(256), 0, s, T, R,
-                     IG, G, it, w.cp);
+  const dim3 cgrid((unsigned)(Rp / CT), (unsigned)((IG + 63) / 64));
+  if (stats)
+    hipLaunchKernelGGL(col_copy<true>, cgrid, dim3(256), 0, s, T, R, IG, G, it, w.cp, st);
+  else
+    hipLaunchKernelGGL(col_copy<false>, cgrid, dim3(256), 0, s, T, R, IG, G, it, w.cp, st);
+  e = hipGetLastError();
+  if (e == hipSuccess && stats && stats_ready) e = hipEventRecord(stats_ready, s);
+  if (e != hipSuccess) return e;
   auto go = [&](auto kern, int nt, int cols) {
     hipLaunchKernelGGL(kern, dim3((unsigned)((IG + cols - 1) / cols)), dim3(nt), 0, s,
                        (const uint32_t *)w.cp, R, IG, T, o);
   };
-  // the fewest waves that hold the column in 24 or 32 words per lane
-  if (R <= 2048) stats ? go(col_select<1, 32, true>, 256, 4) : go(col_select<1, 32, false>, 256, 4);
-  else if (R <= 3072) stats ? go(col_select<2, 24, true>, 128, 1) : go(col_select<2, 24, false>, 128, 1);
-  else if (R <= 4096) stats ? go(col_select<2, 32, true>, 128, 1) : go(col_select<2, 32, false>, 128, 1);
-  else if (R <= 6144) stats ? go(col_select<4, 24, true>, 256, 1) : go(col_select<4, 24, false>, 256, 1);
-  else if (R <= 8192) stats ? go(col_select<4, 32, true>, 256, 1) : go(col_select<4, 32, false>, 256, 1);
-  else if (R <= 12288) stats ? go(col_select<8, 24, true>, 512, 1) : go(col_select<8, 24, false>, 512, 1);
-  else if (R <= 16384) stats ? go(col_select<8, 32, true>, 512, 1) : go(col_select<8, 32, false>, 512, 1);
-  else if (R <= 24576) stats ? go(col_select<16, 24, true>, 1024, 1) : go(col_select<16, 24, false>, 1024, 1);
-  else stats ? go(col_select<16, 32, true>, 1024, 1) : go(col_select<16, 32, false>, 1024, 1);
+  // The fewest waves that hold the column in at most 80 words per lane: a column
+  // is a chain of barriers and exchanges, so as many columns as possible should
+  // be in flight, and beside the column a lane needs 20 to 45 registers.  With
+  // 24 or 32 words per lane (twice the waves, half the columns) 10,000 ranks
+  // took 311 us instead of 206, 16,000 ranks 354 instead of 261.
+  auto shape = [&](auto w, auto v) {
+    constexpr int W = decltype(w)::value, V = decltype(v)::value;
+    go(col_select<W, V>, W > 1 ? 64 * W : 256, W > 1 ? 1 : 4);
+  };
+  if (R <= 2048) shape(std::integral_constant<int, 1>(), std::integral_constant<int, 32>());
+  else if (R <= 3072) shape(std::integral_constant<int, 1>(), std::integral_constant<int, 48>());
+  else if (R <= 4096) shape(std::integral_constant<int, 1>(), std::integral_constant<int, 64>());
+  else if (R <= 5120) shape(std::integral_constant<int, 1>(), std::integral_constant<int, 80>());
+  else if (R <= 6144) shape(std::integral_constant<int, 2>(), std::integral_constant<int, 48>());
+  else if (R <= 8192) shape(std::integral_constant<int, 2>(), std::integral_constant<int, 64>());
+  else if (R <= 10240) shape(std::integral_constant<int, 2>(), std::integral_constant<int, 80>());
+  else if (R <= 12288) shape(std::integral_constant<int, 4>(), std::integral_constant<int, 48>());
+  else if (R <= 16384) shape(std::integral_constant<int, 4>(), std::integral_constant<int, 64>());
+  else if (R <= 20480) shape(std::integral_constant<int, 4>(), std::integral_constant<int, 80>());
+  else if (R <= 24576) shape(std::integral_constant<int, 8>(), std::integral_constant<int, 48>());
+  else if (R <= 32768) shape(std::integral_constant<int, 8>(), std::integral_constant<int, 64>());
+  else if (R <= 40960) shape(std::integral_constant<int, 16>(), std::integral_constant<int, 40>());
+  else shape(std::integral_constant<int, 16>(), std::integral_constant<int, 48>());
   const unsigned wg = (unsigned)std::max(std::min(IG, cus), (IG + 1023) / 1024);
-  if (stats)
-    hipLaunchKernelGGL(col_select_wide<true>, dim3(wg), dim3(1024), 0, s, T, R, IG, G, it, o);
-  else
-    hipLaunchKernelGGL(col_select_wide<false>, dim3(wg), dim3(1024), 0, s, T, R, IG, G, it, o);
-  e = hipGetLastError();
-  if (e == hipSuccess && stats && stats_ready) e = hipEventRecord(stats_ready, s);
-  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(col_select_wide, dim3(wg), dim3(1024), 0, s, T, R, IG, G, it, o);
   // four ranks per lane (16-byte loads) once that leaves 16 waves per CU
-  const int64_t w4 = (R + 255) / 256 * G;
-  if (w4 >= 16 * (int64_t)cus)
-    hipLaunchKernelGGL((score_copy<4, 4>), dim3((unsigned)((w4 + 3) / 4)), dim3(256), 0, s,
-                       (const uint32_t *)w.cp, T, R, I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
+  const int64_t b4 = (R + 1023) / 1024 * G;
+  if (b4 >= 4 * (int64_t)cus)
+    hipLaunchKernelGGL((score_copy<4, 4>), dim3((unsigned)b4), dim3(256), 0, s, (const uint32_t *)w.cp, T, R,
+                       I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
   else
-    hipLaunchKernelGGL((score_copy<1, 16>), dim3((unsigned)(((R + 63) / 64 * G + 3) / 4)), dim3(256), 0, s,
+    hipLaunchKernelGGL((score_copy<1, 16>), dim3((unsigned)((R + 255) / 256 * G)), dim3(256), 0, s,
                        (const uint32_t *)w.cp, T, R, I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
   return hipGetLastError();
 }

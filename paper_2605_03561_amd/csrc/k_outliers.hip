@@ -2052,12 +2052,9 @@ __global__ __launch_bounds__(64 * W) void sel_regions_reg(const void *vals_t, in
         hi = x[v] > hi ? x[v] : hi;
       }
     }
-    for (int d = 32; d >= 1; d >>= 1) {
-      const uint64_t ol = __shfl_xor(lo, d, 64), oh = __shfl_xor(hi, d, 64);
-      lo = ol < lo ? ol : lo;
-      hi = oh > hi ? oh : hi;
-      c += __shfl_xor(c, d, 64);
-    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    c = wave_sum(c);
     if (lane == 0) {
       rmn[wid] = lo;
       rmx[wid] = hi;
@@ -2560,7 +2557,7 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
 }
 
 int scan_stat_chunks(int64_t R, int32_t kind) {
-  return reg_path(R, TA_SCAN_FULL, kind) ? 1 : transpose_groups_of(R);
+  return reg_path(R, TA_SCAN_FULL, kind) ? col_stat_chunks(R) : transpose_groups_of(R);
 }
 
 }  // namespace ta

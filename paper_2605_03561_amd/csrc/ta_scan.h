@@ -33,10 +33,11 @@ __device__ inline int nbits64(uint64_t v) { return v ? 64 - __clzll((long long)v
 
 // The robust FULL scan's first stage with columns in registers
 // (k_colscan.hip), for at most COL_REG_MAX ranks: m_t[g][r] = mean over rank
-// r's iterations of its cells' scores.  st.rc is 0, or 1: the columns'
-// imbalance statistics too, one chunk, complete when stats_ready (if set) has
-// been recorded.
-constexpr int64_t COL_REG_MAX = 32768;
+// r's iterations of its cells' scores.  st.rc is 0, or col_stat_chunks(R): the
+// columns' imbalance partials too, complete when stats_ready (if set) has been
+// recorded.
+constexpr int64_t COL_REG_MAX = 49152;
+int col_stat_chunks(int64_t R);
 size_t col_scan_ws_bytes(int64_t R, int IG);
 hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int32_t *it, ColPartials st,
                            hipEvent_t stats_ready, double *m_t, void *ws, int cus, hipStream_t s);

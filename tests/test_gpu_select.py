@@ -50,12 +50,14 @@ def test_region_selection_edges(ta, h, oracle, R):
         assert int(o["n_flagged"].item()) == nf
 
 
-@pytest.mark.parametrize("R", [65, 300, 700, 1025, 2049, 3073, 4097, 6145, 8193, 12289, 16385, 24577])
+@pytest.mark.parametrize("R", [65, 300, 700, 1025, 2049, 3073, 4097, 5121, 6145, 8193, 10241, 12289, 16385,
+                               20481, 24577, 32769, 40961, 49153])
 @pytest.mark.parametrize("gap", [2000.0, 3e9])
 def test_column_selection_in_a_plan(ta, h, oracle, R, gap):
     """The scan's first pass in a plan, which also takes the imbalance columns,
-    at every launch shape of the column selection, with cells of microseconds
-    and with columns too spread for 32-bit offsets.  Odd row lengths."""
+    at every launch shape of the column selection and past the last, with cells
+    of microseconds and with columns too spread for 32-bit offsets.  Odd row
+    lengths."""
     from paper_2605_03561_amd import synth
     w = synth.plain_workload(seed=R, n_ranks=R, events=30, n_nodes=60, n_iters=3, n_regions=5,
                              mean_gap_ns=gap)
