@@ -13,8 +13,18 @@
 //             written once, whole and coalesced, then cleared     [Sec. V]
 //   incl      one exclusive scan of the histogram in preorder:
 //             incl[v] = P[tout(v)] - P[tin(v)]
+// What bounds it: the instructions and LDS operations per event for long traces
+// over few cells (10,000 ranks, 8.2e8 events, 300 x 32 cells: 3.05 -> 2.63 ms,
+// 4.0 TB/s), HBM when a rank writes a cell per event (40,000 ranks, 1.27e9
+// events, 500 x 64 cells: 6.90 -> 6.40 ms, 4.5 TB/s).  So a tile inside the rank
+// and a wave inside the ring's window test nothing per event, neighbours'
+// values move on the VALU (DPP) instead of through LDS, cells below 2^32 are
+// squared by one product, and the time outside the tensor is not summed: it is
+// the span less the cells.
 // Everything is integer, so the result does not depend on the order of the
 // LDS atomics.  No global atomics except the sticky error word (errors only).
+#include <type_traits>
+
 #include "ta_internal.h"
 
 namespace ta {
@@ -102,12 +112,20 @@ __device__ inline void load_tile(Tile<EPT> &t, const int64_t *__restrict__ ts,
   if (lane == 0 && c0 - 1 >= b && c0 - 1 < e) t.halo_ctx = ctx[c0 - 1];
 }
 
-__device__ inline int wave_incl_scan_i32(int v, int lane) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int t = __shfl_up(v, d, 64);
-    if (lane >= d) v += t;
-  }
+// x of the next lane (SHL) or the previous one; the last (first) lane gets `edge`.
+template <bool SHL>
+__device__ __forceinline__ int lane_shift(int x, int edge) {
+  return __builtin_amdgcn_update_dpp(edge, x, SHL ? 0x130 : 0x138, 0xf, 0xf, false);  // wave_shl:1, wave_shr:1
+}
+
+// Inclusive scan over the 64 lanes on the VALU.
+__device__ __forceinline__ int wave_incl_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return v;
 }
 
@@ -128,16 +146,23 @@ __device__ inline int64_t wave_sum_i64(int64_t v) {
 
 // 64x64 -> 128-bit unsigned square accumulated into (lo, hi).
 __device__ inline void acc_sq(uint64_t &lo, uint64_t &hi, int64_t v) {
+  if ((uint64_t)v >> 32 == 0) {  // a cell below 2^32: one 32 x 32 product
+    const uint64_t p = (uint64_t)(uint32_t)v * (uint32_t)v;
+    lo += p;
+    hi += lo < p ? 1 : 0;
+    return;
+  }
   unsigned __int128 p = (unsigned __int128)(__int128)v * (unsigned __int128)(__int128)v;
   unsigned __int128 s = ((unsigned __int128)hi << 64 | lo) + p;
   lo = (uint64_t)s;
   hi = (uint64_t)(s >> 64);
 }
 
-// NT threads per workgroup (256 or 512); a 512-thread workgroup is limited to
-// 128 VGPRs so that two fit on a CU beside each other (the LDS allows two).
+
+// NT threads per workgroup (256 or 512); with up to 4 events per thread the
+// kernel is limited to 128 VGPRs, so that 16 waves fit on a CU.
 template <bool ATTR, bool SEG, int EPT, bool NTMP, int NT, bool MULTI>
-__global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void seg_kernel(SegArgs a) {
+__global__ __launch_bounds__(NT, EPT <= 4 ? 4 : 1) void seg_kernel(SegArgs a) {
   constexpr int NWAVE = NT / 64;
   constexpr int TILE = NT * EPT;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -239,7 +264,6 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void seg_kernel(SegArgs a) {
     uint32_t errb = T.err;
     int carry = -1;      // iteration index in effect after the processed events
     int flushed = 0;     // tensor rows [0, flushed) are written
-    int64_t out_acc = 0; // time outside every region / before the first boundary
     int64_t S = 0;
     uint64_t Qlo = 0, Qhi = 0;
     int64_t *trow = SEG ? TA_OUT(tensor) + r * (int64_t)I * G : nullptr;
@@ -267,44 +291,61 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void seg_kernel(SegArgs a) {
         load_tile<EPT, NTMP>(nxt_tile, T.ts, T.ctx, T.E, c0 + TILE, b, e, lane);
       const int64_t *tsv = cur.ts;
       const int32_t *cv = cur.cv;
-      // Timestamp after my last event (lane + 1's first, or the halo at the
-      // wave edge) and context before my first event.
-      int64_t nxt = __shfl_down(tsv[0], 1, 64);
-      if (lane == 63) nxt = cur.halo_ts;
-      int32_t pc = __shfl_up(cv[EPT - 1], 1, 64);
-      if (lane == 0) pc = cur.halo_ctx;
-      int prev_in = 0;
-      if (c0 - 1 >= b && c0 - 1 < e && (uint32_t)pc < (uint32_t)N)
-        prev_in = (info[pc] & INFO_MARKER_BIT) ? 1 : 0;
-
+      // Timestamp after my last event: lane + 1's first, or the halo at the wave edge.
+      const int64_t nxt = join64(lane_shift<true>((int)tsv[0], (int)cur.halo_ts),
+                                 lane_shift<true>((int)(tsv[0] >> 32), (int)(cur.halo_ts >> 32)));
       int64_t d[EPT];
       uint32_t inf[EPT];
-      uint32_t inr = 0, bmask = 0;
+      // A tile inside the rank (all but its first and last) needs no test per
+      // event; errors are collected over the thread's events.
+      if (t0 >= b && t0 + TILE < e) {
+        int neg = 0;
+        uint32_t far = 0;
+#pragma unroll
+        for (int j = 0; j < EPT; j++) {
+          d[j] = ((j < EPT - 1) ? tsv[j + 1] : nxt) - tsv[j];
+          neg |= (int)(d[j] >> 32);
+          const uint32_t c = (uint32_t)cv[j], last = (uint32_t)(N - 1);
+          far = c > far ? c : far;
+          inf[j] = info[c < last ? c : last];
+        }
+        if (neg < 0) errb |= ERRBIT_UNSORTED;
+        if (far >= (uint32_t)N) errb |= ERRBIT_CTX;
+      } else {
+#pragma unroll
+        for (int j = 0; j < EPT; j++) {
+          const int64_t k = c0 + j;
+          const bool in_r = (k >= b) && (k < e);
+          const int64_t tn = (j < EPT - 1) ? tsv[j + 1] : nxt;
+          int64_t dj = (in_r && k + 1 < e) ? tn - tsv[j] : 0;
+          if (dj < 0) errb |= ERRBIT_UNSORTED;
+          uint32_t w = 0;
+          if (in_r) {
+            if ((uint32_t)cv[j] < (uint32_t)N) w = info[cv[j]];
+            else errb |= ERRBIT_CTX;
+          }
+          d[j] = dj;
+          inf[j] = w;
+        }
+      }
+      // Boundaries: a marker event whose predecessor is none (the previous
+      // lane's last event, or the halo; words of events outside the rank are 0).
+      int halo_in = 0;
+      if (lane == 0 && (uint32_t)cur.halo_ctx < (uint32_t)N) halo_in = (int)(info[cur.halo_ctx] & INFO_MARKER_BIT);
+      int prev_in = lane_shift<false>((int)(inf[EPT - 1] & INFO_MARKER_BIT), halo_in);
+      uint32_t bmask = 0;
       int bcount = 0;
 #pragma unroll
       for (int j = 0; j < EPT; j++) {
-        const int64_t k = c0 + j;
-        const bool in_r = (k >= b) && (k < e);
-        const int64_t tn = (j < EPT - 1) ? tsv[j + 1] : nxt;
-        int64_t dj = (in_r && k + 1 < e) ? tn - tsv[j] : 0;
-        if (dj < 0) errb |= ERRBIT_UNSORTED;
-        uint32_t w = 0;
-        if (in_r) {
-          if ((uint32_t)cv[j] < (uint32_t)N) w = info[cv[j]];
-          else errb |= ERRBIT_CTX;
-        }
-        const int inm = (w & INFO_MARKER_BIT) ? 1 : 0;
-        const int bnd = inm & (prev_in ^ 1);
+        const int inm = (int)(inf[j] & INFO_MARKER_BIT);
+        const int bnd = (int)((uint32_t)(inm & ~prev_in) / INFO_MARKER_BIT);
         prev_in = inm;
         bmask |= (uint32_t)bnd << j;
-        inr |= (uint32_t)in_r << j;
         bcount += bnd;
-        d[j] = dj;
-        inf[j] = w;
       }
 
       // Workgroup scan of boundary counts -> iteration index of each event.
-      const int inc = wave_incl_scan_i32(bcount, lane);
+      const int inc = wave_incl_scan_i32(bcount);
       int *ws = wsum + parity * NWAVE;
       parity ^= 1;
       if (lane == 63) ws[wid] = inc;
@@ -335,36 +376,42 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void seg_kernel(SegArgs a) {
       }
 
       if (SEG) {
+        // iterations of this wave's events: from before its first to its last
+        const int w_first = __builtin_amdgcn_readfirstlane(carry + wbase);
+        const int w_last = __builtin_amdgcn_readlane(run, 63);
+        if (w_last >= I) {
 #pragma unroll
-        for (int j = 0; j < EPT; j++) {
-          const int gj = (int)(inf[j] & INFO_REGION_MASK) - 1;
-          if (((inr >> j) & 1) && (itj[j] < 0 || gj < 0)) out_acc += d[j];
-          if (((inr >> j) & 1) && itj[j] >= I) errb |= ERRBIT_OVERFLOW;
+          for (int j = 0; j < EPT; j++)
+            if (itj[j] >= I && c0 + j >= b && c0 + j < e) errb |= ERRBIT_OVERFLOW;
         }
         int lo = it_first > 0 ? it_first : 0;
         while (true) {
           const int hi = lo + W - 1;
-          int64_t pend = 0;
-          int pslot = -1;
+          // Adds this thread's events to the ring, runs of one cell at once
+          // (ALL: every event of the wave is in the window and below I).
+          auto add_events = [&](auto all) {
+            constexpr bool ALL = decltype(all)::value;
+            int64_t pend = 0;
+            int pslot = -1;
 #pragma unroll
-          for (int j = 0; j < EPT; j++) {
-            const int gj = (int)(inf[j] & INFO_REGION_MASK) - 1;
-            const int it = itj[j];
-            if (((inr >> j) & 1) && gj >= 0 && it >= lo && it <= hi && it < I) {
-              const int slot = (it & (W - 1)) * G + gj;
-              if (slot == pslot) {
-                pend += d[j];
-              } else {
-                if (pslot >= 0 && pend != 0)
-                  atomicAdd(reinterpret_cast<unsigned long long *>(&ring[pslot]),
-                            (unsigned long long)pend);
+            for (int j = 0; j < EPT; j++) {
+              const int gj = (int)(inf[j] & INFO_REGION_MASK) - 1;  // -1: no region, or not in the rank
+              const int it = itj[j];
+              const bool in = gj >= 0 && (ALL || (it >= lo && it <= hi && it < I));
+              const int slot = in ? (int)__umul24((uint32_t)(it & (W - 1)), (uint32_t)G) + gj : -1;
+              if (slot != pslot) {
+                if (pslot >= 0)
+                  atomicAdd(reinterpret_cast<unsigned long long *>(&ring[pslot]), (unsigned long long)pend);
+                pend = 0;
                 pslot = slot;
-                pend = d[j];
               }
+              pend += d[j];
             }
-          }
-          if (pslot >= 0 && pend != 0)
-            atomicAdd(reinterpret_cast<unsigned long long *>(&ring[pslot]), (unsigned long long)pend);
+            if (pslot >= 0)
+              atomicAdd(reinterpret_cast<unsigned long long *>(&ring[pslot]), (unsigned long long)pend);
+          };
+          if (w_first >= lo && w_last <= hi && w_last < I) add_events(std::true_type());
+          else if (w_last >= lo && w_first <= hi) add_events(std::false_type());
           __syncthreads();
           int fl_hi = hi < it_last - 1 ? hi : it_last - 1;
           if (fl_hi > I - 1) fl_hi = I - 1;
@@ -403,8 +450,8 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void seg_kernel(SegArgs a) {
           acc_sq(Qlo, Qhi, v);
         }
       }
-      // outside: workgroup sum
-      int64_t os = wave_sum_i64(out_acc);
+      // time in the tensor: workgroup sum
+      const int64_t os = wave_sum_i64(S);
       __syncthreads();
       if (lane == 0) wsum64[wid] = os;
       redS[tid] = S;
@@ -426,8 +473,9 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void seg_kernel(SegArgs a) {
         }
       }
       if (tid == 0) {
-        int64_t s = 0;
-        for (int w = 0; w < NWAVE; w++) s += wsum64[w];
+        // the durations add up to the span: what is in no cell is outside
+        int64_t s = (e > b) ? T.ts[e - 1] - T.ts[b] : 0;
+        for (int w = 0; w < NWAVE; w++) s -= wsum64[w];
         if (TA_OUT(outside)) TA_OUT(outside)[r] = s;
         if (TA_OUT(iters_found)) TA_OUT(iters_found)[r] = carry + 1;
       }
