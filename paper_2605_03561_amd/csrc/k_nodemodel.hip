@@ -8,17 +8,18 @@
 // durations a node has a non-zero inclusive cost exactly when some node of its
 // subtree has a non-zero exclusive cost).  Both lists are in preorder.
 //
-// Pass 1 (`nm_rows`): one wave per rank finds the boundary events (entry into
+// Pass 1 (`nm_rows`): one workgroup per rank finds the boundary events (entry into
 //   the marker's subtree) and writes the first event of every row.
-// Pass 2 (`nm_short<FILL, ...>`): one wave per row of at most SHORT_CAP events
-//   (one kernel for rows of up to 64 events with the tree and the position map
-//   staged in LDS, one for 65..SHORT_CAP events with the LDS radix sort and
-//   the tree read through L2); all of a row's events are loaded at once.  The
-//   events with a positive duration are sorted by the preorder position of
-//   their node (a 64-lane bitonic network in registers up to 64 events, else an
-//   LSD radix sort with 8-bit digits in the wave's LDS), equal positions are
-//   merged into (position, exclusive cost) with a running sum Q of the sorted
-//   durations, so a node's cost is a difference of Q.  Inclusive entries: for
+// Pass 2: one wave per row of at most SHORT_CAP events (one kernel for rows of
+//   up to 64 events, one for 65..SHORT_CAP); all of a row's events are loaded at
+//   once.  Trees of up to SMALL_TAB_NODES nodes (`nm_bits`): the preorder
+//   positions of the events with a positive duration are set in a bit map in
+//   LDS, population counts number them and the durations are added to the
+//   numbered nodes.  Larger trees (`nm_short`): the events are sorted by
+//   position (a 64-lane bitonic network in registers up to 64 events, else an
+//   LSD radix sort with 8-bit digits in the wave's LDS) and equal positions are
+//   merged.  Either way (position, exclusive cost) with a running sum Q of the
+//   durations in preorder, so a node's cost is a difference of Q.  Inclusive entries: for
 //   unique nodes u_0 < u_1 < ... (preorder), the ancestors of u_j that are not
 //   ancestors of u_{j-1} lie strictly between u_{j-1} and u_j in preorder, so
 //   lane j walks up from u_j until it reaches an ancestor of u_{j-1}; the walks
@@ -33,9 +34,11 @@
 // The count run writes the entry counts, which an exclusive scan turns into
 // row offsets; the fill run writes the entries.  Integer sums throughout, so
 // the result does not depend on the order of any atomic.
+#include <algorithm>
 #include <mutex>
 
 #include "ta_internal.h"
+#include "ta_select.h"
 
 namespace ta {
 namespace {
@@ -46,7 +49,7 @@ constexpr int SHORT_CAP = 512;      // events per row handled by one wave
 constexpr int SLOT_BITS = 9;        // log2(SHORT_CAP): sort keys are pos << 9 | slot
 constexpr int LONG_T = 512;         // threads per workgroup of the long-row kernel
 constexpr int LONG_LDS_NODES = 4096;
-constexpr int SMALL_TAB_NODES = 8192; // the <= 64-event row kernel keeps the tree in LDS up to here
+constexpr int SMALL_TAB_NODES = 8192; // tree tables and row bit maps in LDS up to here (4 words of bits per lane)
 constexpr int SCAN_T = 1024;
 constexpr int SCAN_EPT = 8;
 constexpr int SCAN_B = SCAN_T * SCAN_EPT;
@@ -95,25 +98,48 @@ __device__ inline void rank_range(const int64_t *off, int64_t r, int64_t E, int6
 
 // ---- pass 1: row boundaries ---------------------------------------------------
 
-// One wave per rank; each lane takes 4 consecutive events per step (16-byte
-// context loads from 4-aligned indices), 4 steps in flight.  An event opens a
-// row when its node lies in the marker's subtree and the rank's previous event
-// does not (the rank's first event counts as following an event outside).
-__global__ __launch_bounds__(NMT) void nm_rows(const int64_t *__restrict__ off,
-                                               const int32_t *__restrict__ ctx, int64_t R,
-                                               int64_t E, int I, const uint32_t *__restrict__ info,
-                                               int N, int64_t *__restrict__ row_start,
-                                               int32_t *__restrict__ iters_found, uint32_t *err) {
-  constexpr int U = 4;
-  const int lane = lane_id();
-  const int64_t nwaves = (int64_t)gridDim.x * NMW;
+// One workgroup per rank at a time; each lane takes 4 consecutive events per
+// load (16 bytes of contexts from 4-aligned indices), 4 loads in flight, a wave
+// 1,024 consecutive events per step.  An event opens a row when its node lies
+// in the marker's subtree and the rank's previous event does not (the rank's
+// first event counts as following an event outside).  The markers are staged as
+// one bit per node (MARK_LDS, up to MARK_NODES nodes).  With one wave per rank
+// the longest rank's chain of steps was the time: 1,500 ranks, 4.7e7 events 788
+// -> 139 us.
+constexpr int RT = 512;
+constexpr int MARK_NODES = 1 << 17;
+
+template <bool MARK_LDS>
+__global__ __launch_bounds__(RT) void nm_rows(const int64_t *__restrict__ off,
+                                              const int32_t *__restrict__ ctx, int64_t R, int64_t E, int I,
+                                              const uint32_t *__restrict__ info, int N,
+                                              int64_t *__restrict__ row_start,
+                                              int32_t *__restrict__ iters_found, uint32_t *err) {
+  constexpr int U = 4, NW = RT / 64, STEP = 256 * U;  // events per wave and step
+  __shared__ int wsum[2][NW];
+  extern __shared__ uint32_t mark[];
+  const int lane = lane_id(), wid = (int)(threadIdx.x >> 6);
+  if (MARK_LDS) {
+    for (int v = (int)threadIdx.x; v < ((N + 63) & ~63); v += RT) {
+      const uint64_t m = __ballot(v < N && (info[v < N ? v : 0] & INFO_MARKER_BIT) != 0);
+      if (lane == 0) {
+        mark[v >> 5] = (uint32_t)m;
+        mark[(v >> 5) + 1] = (uint32_t)(m >> 32);
+      }
+    }
+    __syncthreads();
+  }
+  auto marked = [&](int32_t c) -> uint32_t {
+    return MARK_LDS ? (mark[c >> 5] >> (c & 31)) & 1u : ((info[c] & INFO_MARKER_BIT) ? 1u : 0u);
+  };
   uint32_t errb = 0;
-  for (int64_t r = (int64_t)blockIdx.x * NMW + (threadIdx.x >> 6); r < R; r += nwaves) {
+  int parity = 0;
+  for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
     int64_t b, e;
     rank_range(off, r, E, &b, &e, err);
-    int64_t found = 0;   // boundaries seen so far
-    int carry = 0;       // previous event lies in the marker subtree
-    for (int64_t k0 = b & ~(int64_t)3; k0 < e; k0 += 256 * U) {
+    int64_t found = 0;  // boundaries seen so far
+    for (int64_t t0 = b & ~(int64_t)3; t0 < e; t0 += NW * STEP) {
+      const int64_t k0 = t0 + (int64_t)wid * STEP;
       int32_t c[U][4];
 #pragma unroll
       for (int u = 0; u < U; u++) {
@@ -129,6 +155,14 @@ __global__ __launch_bounds__(NMT) void nm_rows(const int64_t *__restrict__ off,
           for (int j = 0; j < 4; j++) c[u][j] = (kb + j < e && kb + j < E) ? ctx[kb + j] : 0;
         }
       }
+      // membership of the event before the wave's first
+      int pin = 0;
+      if (k0 - 1 >= b && k0 - 1 < e) {
+        const int32_t pc = ctx[k0 - 1];
+        if ((uint32_t)pc < (uint32_t)N) pin = (int)marked(pc);
+      }
+      uint32_t bnd[U];
+      int before[U], tot = 0;
 #pragma unroll
       for (int u = 0; u < U; u++) {
         const int64_t kb = k0 + 256 * u + 4 * lane;
@@ -138,30 +172,44 @@ __global__ __launch_bounds__(NMT) void nm_rows(const int64_t *__restrict__ off,
           const int64_t k = kb + j;
           if (k >= b && k < e) {
             const int32_t cc = c[u][j];
-            if ((uint32_t)cc < (uint32_t)N) inm |= ((info[cc] & INFO_MARKER_BIT) ? 1u : 0u) << j;
+            if ((uint32_t)cc < (uint32_t)N) inm |= marked(cc) << j;
             else errb |= ERRBIT_CTX;
           }
         }
-        // membership of the event before my first one
-        int pin = __shfl_up((int)(inm >> 3), 1, 64);
-        if (lane == 0) pin = carry;
-        const uint32_t prev = ((inm << 1) | (uint32_t)pin) & 0xfu;
-        const uint32_t bnd = inm & ~prev;
-        int tot;
-        const int before = wave_excl_scan_i32(__popc(bnd), &tot);
-        int64_t idx = found + before;
+        const int mine = __builtin_amdgcn_update_dpp(pin, (int)(inm >> 3), 0x138, 0xf, 0xf, false);  // wave_shr:1
+        const uint32_t prev = ((inm << 1) | (uint32_t)mine) & 0xfu;
+        bnd[u] = inm & ~prev;
+        pin = __builtin_amdgcn_readlane((int)(inm >> 3), 63);
+        const uint32_t n = (uint32_t)__popc(bnd[u]), in = wave_scan_u32(n);
+        before[u] = tot + (int)(in - n);
+        tot += __builtin_amdgcn_readlane((int)in, 63);
+      }
+      int *ws = wsum[parity];
+      parity ^= 1;
+      if (lane == 0) ws[wid] = tot;
+      __syncthreads();
+      int base = 0, all = 0;
+#pragma unroll
+      for (int w = 0; w < NW; w++) {
+        const int x = ws[w];
+        base += w < wid ? x : 0;
+        all += x;
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const int64_t kb = k0 + 256 * u + 4 * lane;
+        int64_t idx = found + base + before[u];
 #pragma unroll
         for (int j = 0; j < 4; j++)
-          if ((bnd >> j) & 1u) {
+          if ((bnd[u] >> j) & 1u) {
             if (idx < I) row_start[r * (int64_t)I + idx] = kb + j;
             else errb |= ERRBIT_OVERFLOW;
             idx++;
           }
-        found += tot;
-        carry = __shfl((int)(inm >> 3), 63, 64);
       }
+      found += all;
     }
-    if (lane == 0) iters_found[r] = (int32_t)(found < I ? found : I);
+    if (threadIdx.x == 0) iters_found[r] = (int32_t)(found < I ? found : I);
   }
   if (errb) atomicOr(err, errb);
 }
@@ -217,25 +265,6 @@ struct WaveLds {
   int64_t d[CAP];        // duration by slot
   int64_t q[CAP + 1];    // running sum of the sorted durations before each unique node
   uint32_t hist[CAP > 64 ? 256 : 1];
-};
-
-// The tree by preorder position for the walks: (parent position + 1, subtree
-// end) from an LDS copy (small trees) or from the global table.
-template <bool LDS_TAB>
-struct TreeTab {
-  const uint2 *lds;
-  const int4 *glb;
-  __device__ __forceinline__ void at(int32_t x, int32_t &parent, int32_t &tout) const {
-    if (LDS_TAB) {
-      const uint2 t = lds[x];
-      parent = (int32_t)t.x - 1;
-      tout = (int32_t)t.y;
-    } else {
-      const int4 t = glb[x];
-      parent = t.y;
-      tout = t.z;
-    }
-  }
 };
 
 // Sorts keys[0 .. n) (distinct) ascending by bits [SLOT_BITS, SLOT_BITS + nbits)
@@ -329,26 +358,13 @@ __device__ inline int lower_bound_u32(const uint32_t *pos, int lo, int hi, uint3
 
 // One wave per row of LO < n <= CAP events (n = the row's event count); with
 // CAP = SHORT_CAP the rows above it are listed for the long-row kernel, and
-// with LO = 0 the empty rows' counts are written.  NT threads per workgroup;
-// LDS_TAB: the walks read the tree from an LDS copy (dynamic LDS, 8 B a node).
-template <bool FILL, int CAP, int LO, int NT, bool LDS_TAB, bool POS_LDS>
+// with LO = 0 the empty rows' counts are written.  NT threads per workgroup.
+// For trees of more than SMALL_TAB_NODES nodes.
+template <bool FILL, int CAP, int LO, int NT>
 __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
   constexpr int NW = NT / 64;
   __shared__ WaveLds<CAP> lds_all[NW];
-  extern __shared__ uint2 tab_lds[];
   WaveLds<CAP> &L = lds_all[threadIdx.x >> 6];
-  TreeTab<LDS_TAB> tree{tab_lds, a.ptab};
-  // POS_LDS: the preorder position of every caller id, after the tree table
-  uint32_t *pos_lds = reinterpret_cast<uint32_t *>(tab_lds + (LDS_TAB ? a.N : 0));
-  if (LDS_TAB) {
-    for (int p = threadIdx.x; p < a.N; p += NT) {
-      const int4 t = a.ptab[p];
-      tab_lds[p] = make_uint2((uint32_t)(t.y + 1), (uint32_t)t.z);
-    }
-  }
-  if (POS_LDS)
-    for (int v = threadIdx.x; v < a.N; v += NT) pos_lds[v] = a.info[v] >> INFO_TIN_SHIFT;
-  if (LDS_TAB || POS_LDS) __syncthreads();
   const int lane = lane_id();
   const int64_t rows = a.R * (int64_t)a.I;
   const int64_t nwaves = (int64_t)gridDim.x * NW;
@@ -402,7 +418,7 @@ __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
         if (d < 0) errb |= ERRBIT_UNSORTED;
         const int32_t c = cv[j];
         if ((uint32_t)c < (uint32_t)a.N) {
-          pos = POS_LDS ? pos_lds[c] : a.info[c] >> INFO_TIN_SHIFT;
+          pos = a.info[c] >> INFO_TIN_SHIFT;
           keep = d > 0;
         } else {
           errb |= ERRBIT_CTX;
@@ -483,8 +499,8 @@ __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
         const int32_t prev = u > 0 ? (int32_t)ups[u - 1] : -1;
         int32_t x = pu;
         while (x >= 0) {
-          int32_t par, tz;
-          tree.at(x, par, tz);
+          const int4 t = a.ptab[x];
+          const int32_t par = t.y, tz = t.z;
           if (prev >= 0 && x <= prev && prev < tz) break;  // x is an ancestor of prev
           len++;
           x = par;
@@ -501,11 +517,11 @@ __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
         if (a.node_i) {
           int32_t x = pu;
           for (int t = 0; t < len; t++) {
-            int32_t par, tz;
-            tree.at(x, par, tz);
+            const int4 pt = a.ptab[x];
+            const int32_t par = pt.y, tz = pt.z;
             const int j = lower_bound_u32(ups, u, nu, (uint32_t)tz);
             const int64_t at = oi + n_incl + before + (len - 1 - t);
-            a.node_i[at] = a.ptab[x].x;
+            a.node_i[at] = pt.x;
             a.val_i[at] = L.q[j] - qu;
             x = par;
           }
@@ -518,6 +534,258 @@ __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
       a.cnt_i[q] = n_incl;
     }
     __builtin_amdgcn_wave_barrier();
+  }
+  if (errb) atomicOr(a.err, errb);
+}
+
+// The same for trees of up to SMALL_TAB_NODES nodes, without a sort.  The
+// wave's LDS holds one bit per preorder position: the row's positions are set,
+// a scan of the words' population counts numbers them in order, and a node's
+// number (and the number of nodes below any position, which the inclusive
+// costs need) is then one word's count.  Durations are added to the node's
+// accumulator by LDS atomics and scanned into Q.  The tree (parent + 1 and
+// subtree end) and the position of every caller id are staged as 16-bit pairs
+// and words.  A wave takes NMB consecutive rows of its
+// workgroup's share from a counter, reads their bounds at once and loads the next row's events while it works on one.
+// LO < events of a row <= CAP as above.
+//
+// Bound by the chain of LDS operations per row.  The radix sort (four phases of
+// ballots per 64 keys), the walks through L2 and a binary search per inclusive
+// entry took, on 750,000 rows of 4.7e7 events over 5,000 nodes, 1,450 + 2,480 us
+// (count and fill of the rows above 64 events) and 640 + 1,580 us (shorter
+// rows); this takes 353 + 826 and 310 + 636.  One counter of all workgroups for the
+// turns made each of the four kernels 300 us longer; the inclusive entries are
+// staged because written along the walks they cost the fills 170 to 260 us more.
+constexpr int NMB = 16;           // rows per turn
+constexpr int NM_STAGE = 192;     // 16 waves of them beside the tables of SMALL_TAB_NODES nodes
+constexpr int BM_WORDS = SMALL_TAB_NODES / 32;
+
+template <int CAP>
+struct BitLds {
+  alignas(16) uint32_t bm[BM_WORDS + 4];   // positions of the row's nodes; all zero between rows
+  alignas(16) uint16_t before[BM_WORDS + 4];  // nodes in the words before; [BM_WORDS]: all
+  int64_t q[CAP + 1];
+  uint16_t ups[CAP];  // positions of the unique nodes
+  uint16_t stage[NM_STAGE];  // positions of consecutive inclusive entries
+};
+
+__device__ __forceinline__ int dpp_next(int x, int edge) {  // lane + 1's x; lane 63: edge
+  return __builtin_amdgcn_update_dpp(edge, x, 0x130, 0xf, 0xf, false);
+}
+
+__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t x) {
+#define TA_STEP(ctrl, rows)                                                                       \
+  x += ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)(x >> 32), ctrl, rows, 0xf, false) << 32) | \
+       (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, false)
+  TA_STEP(0x111, 0xf);
+  TA_STEP(0x112, 0xf);
+  TA_STEP(0x114, 0xf);
+  TA_STEP(0x118, 0xf);
+  TA_STEP(0x142, 0xa);
+  TA_STEP(0x143, 0xc);
+#undef TA_STEP
+  return x;
+}
+
+template <bool FILL, int CAP, int LO, int NT>
+__global__ __launch_bounds__(NT) void nm_bits(NmArgs a) {
+  constexpr int NW = NT / 64, NCH = CAP / 64;
+  __shared__ BitLds<CAP> lds_all[NW];
+  __shared__ unsigned taken;  // turns that this workgroup's waves have taken
+  extern __shared__ uint32_t tab[];  // [N] (subtree end << 16 | parent + 1), then [N] positions (16 bit)
+  uint16_t *pos_of = reinterpret_cast<uint16_t *>(tab + a.N);
+  BitLds<CAP> &L = lds_all[threadIdx.x >> 6];
+  const int lane = lane_id(), N = a.N;
+  for (int p = (int)threadIdx.x; p < N; p += NT) {
+    const int4 t = a.ptab[p];
+    tab[p] = ((uint32_t)t.z << 16) | (uint32_t)(t.y + 1);
+    pos_of[p] = (uint16_t)(a.info[p] >> INFO_TIN_SHIFT);
+  }
+  for (int w = lane; w < BM_WORDS + 4; w += 64) L.bm[w] = 0;
+  if (threadIdx.x == 0) taken = 0;
+  __syncthreads();
+  auto sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  // the number of the row's nodes at positions below x (x <= N <= 8,192)
+  auto below = [&](uint32_t x) -> int {
+    const uint32_t w = x >> 5;
+    return (int)L.before[w] + __popc(L.bm[w] & ((1u << (x & 31)) - 1u));
+  };
+  const int64_t rows = a.R * (int64_t)a.I;
+  uint32_t errb = 0;
+  while (true) {
+    unsigned turn = 0;
+    if (lane == 0) turn = atomicAdd(&taken, 1u);
+    turn = (unsigned)__builtin_amdgcn_readfirstlane((int)turn);
+    const int64_t q0 = ((int64_t)turn * gridDim.x + blockIdx.x) * NMB;
+    if (q0 >= rows) break;
+    // lane l < NMB: the bounds of row q0 + l
+    int64_t s = 0, e = 0, re = 0;
+    bool have = false;
+    if (lane < NMB && q0 + lane < rows) {
+      have = row_range(a, q0 + lane, &s, &e, &re);
+      const int64_t n = e - s;
+      if (!have || n <= 0) {
+        if (LO == 0 && !FILL) {
+          a.cnt_x[q0 + lane] = 0;
+          a.cnt_i[q0 + lane] = 0;
+        }
+        have = false;
+      } else if (n > CAP) {
+        if (CAP == SHORT_CAP) {
+          const int64_t j = (int64_t)atomicAdd((unsigned long long *)a.n_long, 1ull);
+          if (j < a.long_cap) a.long_rows[j] = q0 + lane;
+        }
+        have = false;
+      } else if (n <= LO) {
+        have = false;
+      }
+    }
+    uint64_t todo = __ballot(have);
+    if (!todo) continue;
+    auto pick = [&](int64_t x, int l) -> int64_t {
+      return ((int64_t)__builtin_amdgcn_readlane((int)(x >> 32), l) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+    };
+    int64_t tv[NCH], tail;
+    int32_t cv[NCH];
+    auto load = [&](int l) {  // the events of row q0 + l
+      const int64_t rs = pick(s, l), rend = pick(e, l);
+#pragma unroll
+      for (int j = 0; j < NCH; j++) {
+        const int64_t k = rs + 64 * j + lane;
+        const bool in = k < rend;
+        tv[j] = in ? a.ts[k] : 0;
+        cv[j] = in ? a.ctx[k] : 0;
+      }
+      tail = rend < pick(re, l) ? a.ts[rend] : 0;
+    };
+    int l = __ffsll((long long)todo) - 1;
+    load(l);
+    while (true) {
+      todo &= todo - 1;
+      const int64_t q = q0 + l;
+      const int n = (int)(pick(e, l) - pick(s, l));
+      const bool ends = pick(e, l) >= pick(re, l);
+      // durations and positions (0xffff: no part in the row)
+      int64_t d[NCH];
+      uint32_t pos[NCH];
+#pragma unroll
+      for (int j = 0; j < NCH; j++) {
+        const int i = 64 * j + lane;
+        d[j] = 0;
+        pos[j] = 0xffffu;
+        if (64 * j < n) {
+          const int64_t t1 = j + 1 < NCH ? tv[j + 1 < NCH ? j + 1 : j] : 0;
+          const int64_t nx = ((int64_t)dpp_next((int)(tv[j] >> 32), __builtin_amdgcn_readlane((int)(t1 >> 32), 0)) << 32) |
+                             (uint32_t)dpp_next((int)tv[j], __builtin_amdgcn_readlane((int)t1, 0));
+          if (i < n) {
+            const int64_t dj = i + 1 < n ? nx - tv[j] : (ends ? 0 : tail - tv[j]);
+            if (dj < 0) errb |= ERRBIT_UNSORTED;
+            if ((uint32_t)cv[j] >= (uint32_t)N) {
+              errb |= ERRBIT_CTX;
+            } else if (dj > 0) {
+              d[j] = dj;
+              pos[j] = pos_of[cv[j]];
+            }
+          }
+        }
+      }
+      const int64_t ox = FILL ? a.off_x[q] : 0, oi = FILL ? a.off_i[q] : 0;
+      const int nl = todo ? __ffsll((long long)todo) - 1 : -1;
+      if (nl >= 0) load(nl);  // in flight during this row
+#pragma unroll
+      for (int j = 0; j < NCH; j++)
+        if (pos[j] != 0xffffu) atomicOr(&L.bm[pos[j] >> 5], 1u << (pos[j] & 31));
+      sync();
+      // number the positions: 4 words per lane
+      int nu;
+      {
+        const uint4 w = *reinterpret_cast<const uint4 *>(&L.bm[4 * lane]);
+        const uint32_t n0 = (uint32_t)__popc(w.x), n1 = n0 + (uint32_t)__popc(w.y), n2 = n1 + (uint32_t)__popc(w.z),
+                       n3 = n2 + (uint32_t)__popc(w.w);
+        const uint32_t in = wave_scan_u32(n3), b0 = in - n3;
+        nu = __builtin_amdgcn_readlane((int)in, 63);
+        const uint2 pk = {b0 | (b0 + n0) << 16, (b0 + n1) | (b0 + n2) << 16};
+        *reinterpret_cast<uint2 *>(&L.before[4 * lane]) = pk;
+        if (lane == 0) L.before[BM_WORDS] = (uint16_t)nu;
+      }
+      if (FILL)
+        for (int u = lane; u <= nu; u += 64) L.q[u] = 0;
+      sync();
+#pragma unroll
+      for (int j = 0; j < NCH; j++)
+        if (pos[j] != 0xffffu) {
+          const int u = below(pos[j]);
+          L.ups[u] = (uint16_t)pos[j];
+          if (FILL) atomicAdd((unsigned long long *)&L.q[u], (unsigned long long)d[j]);
+        }
+      sync();
+      if (FILL) {
+        // exclusive entries; accumulators -> running sums
+        uint64_t carry = 0;
+        for (int c0 = 0; c0 < nu; c0 += 64) {
+          const int u = c0 + lane;
+          const uint64_t v = u < nu ? (uint64_t)L.q[u] : 0;
+          if (u < nu && a.node_x) {
+            a.node_x[ox + u] = a.ptab[L.ups[u]].x;
+            a.val_x[ox + u] = (int64_t)v;
+          }
+          const uint64_t in = wave_scan_u64(v);
+          if (u < nu) L.q[u] = (int64_t)(carry + in - v);
+          carry += lane_value(in, 63);
+        }
+        if (lane == 0) L.q[nu] = (int64_t)carry;
+        sync();
+      }
+      // inclusive entries: the walks up the tree
+      int n_incl = 0;
+      for (int c0 = 0; c0 < nu; c0 += 64) {
+        const int u = c0 + lane;
+        const bool act = u < nu;
+        const int pu = act ? (int)L.ups[u] : -1;
+        const int prev = act && u > 0 ? (int)L.ups[u - 1] : -1;
+        int len = 0;
+        for (int x = pu; x >= 0;) {
+          const uint32_t t = tab[x];
+          if (prev >= 0 && x <= prev && prev < (int)(t >> 16)) break;  // x is an ancestor of prev
+          len++;
+          x = (int)(t & 0xffffu) - 1;
+        }
+        const int in = (int)wave_scan_u32((uint32_t)len);
+        const int tot = __builtin_amdgcn_readlane(in, 63);
+        if (FILL && a.node_i) {
+          // the walks again, their entries staged from the last to the first
+          int at = in - 1, x = pu;
+          for (int w0 = (tot - 1) / NM_STAGE * NM_STAGE; w0 >= 0 && tot > 0; w0 -= NM_STAGE) {
+            for (const int lo = max(w0, in - len); at >= lo; at--) {
+              L.stage[at - w0] = (uint16_t)x;
+              x = (int)(tab[x] & 0xffffu) - 1;
+            }
+            sync();
+            const int64_t o = oi + n_incl + w0;
+            for (int k = lane; k < NM_STAGE && w0 + k < tot; k += 64) {
+              const int y = L.stage[k];
+              a.node_i[o + k] = a.ptab[y].x;
+              a.val_i[o + k] = L.q[below(tab[y] >> 16)] - L.q[below((uint32_t)y)];
+            }
+            sync();
+          }
+        }
+        n_incl += tot;
+      }
+      if (!FILL && lane == 0) {
+        a.cnt_x[q] = nu;
+        a.cnt_i[q] = n_incl;
+      }
+      sync();
+      *reinterpret_cast<uint4 *>(&L.bm[4 * lane]) = uint4{0, 0, 0, 0};
+      sync();
+      if (nl < 0) break;
+      l = nl;
+    }
   }
   if (errb) atomicOr(a.err, errb);
 }
@@ -837,9 +1105,14 @@ hipError_t launch_node_model(const NodeModelArgs &m, bool fill, void *ws, int cu
   a.long_ws = w.long_ws;
   if (!fill) {
     if (m.R > 0)
-      hipLaunchKernelGGL(nm_rows, dim3(grid_for((m.R + NMW - 1) / NMW, cus, 8)), dim3(NMT), 0, s,
-                         m.off, m.ctx, m.R, m.E, m.I, m.info, m.N, m.row_start, m.iters_found,
-                         m.err);
+    {
+      auto go = [&](auto kern, size_t lds) {
+        hipLaunchKernelGGL(kern, dim3(grid_for(m.R, cus, 4)), dim3(RT), lds, s, m.off, m.ctx, m.R, m.E, m.I,
+                           m.info, m.N, m.row_start, m.iters_found, m.err);
+      };
+      if (m.N <= MARK_NODES) go(nm_rows<true>, (size_t)((m.N + 63) / 64) * 8);
+      else go(nm_rows<false>, 0);
+    }
     // counts go to the offset arrays, then scanned in place
     a.cnt_x = m.row_off_x;
     a.cnt_i = m.row_off_i;
@@ -856,30 +1129,41 @@ hipError_t launch_node_model(const NodeModelArgs &m, bool fill, void *ws, int cu
     hipLaunchKernelGGL(nm_zero, dim3(grid_for(1 << 20, cus, 4)), dim3(256), 0, s, w.long_ws,
                        (int64_t)(2 * (int64_t)m.N + (m.N + 31) / 32 + 1) * w.long_grid);
   if (rows > 0) {
-    // rows of up to 64 events: small per-wave buffers, the tree and the
-    // position map in LDS when they fit (two workgroups of eight waves per CU);
-    // 65..SHORT_CAP events: the LDS radix sort, the tree from L2 (three
-    // workgroups of four waves per CU: more waves in flight beat LDS walks)
+    // small trees: rows of up to 64 events in workgroups of eight waves, longer
+    // ones in workgroups of sixteen (one per CU beside its tables); large trees:
+    // the register and radix sorts with the tree read through L2
     static std::once_flag lds_once;
     std::call_once(lds_once, [] {
-      allow_dynamic_lds(&nm_short<true, 64, 0, 512, true, true>, 8 * sizeof(WaveLds<64>));
-      allow_dynamic_lds(&nm_short<false, 64, 0, 512, true, true>, 8 * sizeof(WaveLds<64>));
+      allow_dynamic_lds(&nm_bits<true, 64, 0, 512>, 8 * sizeof(BitLds<64>) + 64);
+      allow_dynamic_lds(&nm_bits<false, 64, 0, 512>, 8 * sizeof(BitLds<64>) + 64);
+      allow_dynamic_lds(&nm_bits<true, SHORT_CAP, 64, 1024>, 16 * sizeof(BitLds<SHORT_CAP>) + 64);
+      allow_dynamic_lds(&nm_bits<false, SHORT_CAP, 64, 1024>, 16 * sizeof(BitLds<SHORT_CAP>) + 64);
       allow_dynamic_lds(&nm_long<true, true>, 64);
       allow_dynamic_lds(&nm_long<false, true>, 64);
     });
-    const bool tab1 = m.N <= SMALL_TAB_NODES;
-    const size_t lds1 = tab1 ? (size_t)m.N * (sizeof(uint2) + sizeof(uint32_t)) : 0;
-    const int g1 = grid_for((rows + 7) / 8, cus, 2);
-    if (fill) {
-      if (tab1) hipLaunchKernelGGL((nm_short<true, 64, 0, 512, true, true>), dim3(g1), dim3(512), lds1, s, a);
-      else hipLaunchKernelGGL((nm_short<true, 64, 0, 512, false, false>), dim3(g1), dim3(512), 0, s, a);
+    if (m.N <= SMALL_TAB_NODES) {
+      const size_t tabs = ((size_t)m.N * 6 + 15) & ~(size_t)15;
+      const int64_t turns = (rows + NMB - 1) / NMB;
+      const int per1 = (int)std::max<size_t>(1, 160 * 1024 / (8 * sizeof(BitLds<64>) + tabs));
+      const int g1 = grid_for((turns + 7) / 8, cus, std::min(per1, 4));
+      const int g2 = grid_for((turns + 15) / 16, cus, 1);
+      if (fill) {
+        hipLaunchKernelGGL((nm_bits<true, 64, 0, 512>), dim3(g1), dim3(512), tabs, s, a);
+        hipLaunchKernelGGL((nm_bits<true, SHORT_CAP, 64, 1024>), dim3(g2), dim3(1024), tabs, s, a);
+      } else {
+        hipLaunchKernelGGL((nm_bits<false, 64, 0, 512>), dim3(g1), dim3(512), tabs, s, a);
+        hipLaunchKernelGGL((nm_bits<false, SHORT_CAP, 64, 1024>), dim3(g2), dim3(1024), tabs, s, a);
+      }
     } else {
-      if (tab1) hipLaunchKernelGGL((nm_short<false, 64, 0, 512, true, true>), dim3(g1), dim3(512), lds1, s, a);
-      else hipLaunchKernelGGL((nm_short<false, 64, 0, 512, false, false>), dim3(g1), dim3(512), 0, s, a);
+      const int g1 = grid_for((rows + 7) / 8, cus, 2), g2 = grid_for((rows + NMW - 1) / NMW, cus, 3);
+      if (fill) {
+        hipLaunchKernelGGL((nm_short<true, 64, 0, 512>), dim3(g1), dim3(512), 0, s, a);
+        hipLaunchKernelGGL((nm_short<true, SHORT_CAP, 64, NMT>), dim3(g2), dim3(NMT), 0, s, a);
+      } else {
+        hipLaunchKernelGGL((nm_short<false, 64, 0, 512>), dim3(g1), dim3(512), 0, s, a);
+        hipLaunchKernelGGL((nm_short<false, SHORT_CAP, 64, NMT>), dim3(g2), dim3(NMT), 0, s, a);
+      }
     }
-    const int g2 = grid_for((rows + NMW - 1) / NMW, cus, 3);
-    if (fill) hipLaunchKernelGGL((nm_short<true, SHORT_CAP, 64, NMT, false, false>), dim3(g2), dim3(NMT), 0, s, a);
-    else hipLaunchKernelGGL((nm_short<false, SHORT_CAP, 64, NMT, false, false>), dim3(g2), dim3(NMT), 0, s, a);
     const size_t lds = w.long_in_lds ? (size_t)(2 * m.N) * 8 + (size_t)((m.N + 31) / 32) * 8 : 0;
     if (w.long_in_lds) {
       if (fill) hipLaunchKernelGGL((nm_long<true, true>), dim3(w.long_grid), dim3(LONG_T), lds, s, a);
