@@ -438,59 +438,74 @@ __global__ __launch_bounds__(256) void ae_grad_f32_kernel(const float *__restric
   if (t == 0) P[AE_NP] = (float)ls;
 }
 
-// Entry p of the workgroup partials summed in workgroup order; the loads go
-// out 16 at a time (one round trip per 16 partials instead of one each), the
-// additions stay in order.
-__device__ inline float sum_partials(const float *part, int nwg, int p) {
-  constexpr int U = 16;
-  float g = 0.f;
-  for (int k0 = 0; k0 < nwg; k0 += U) {
-    float pv[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) pv[u] = k0 + u < nwg ? part[(int64_t)(k0 + u) * (AE_NP + 1) + p] : 0.f;
-#pragma unroll
-    for (int u = 0; u < U; u++)
-      if (k0 + u < nwg) g += pv[u];
-  }
-  return g;
-}
+// Sums the workgroup partials of every parameter (and of the loss) in workgroup
+// order; optionally takes one Adam step.  With epoch_loss, also epoch_loss[0] +=
+// loss * lfrac (the step's share of the epoch's rows), in the kernel rather than
+// a launch of its own.
+//
+// Bound by reading the partials (256 of them: 25.5 MB).  A workgroup takes AP
+// entries and brings their partials to LDS, 16 loads per thread in flight; one
+// thread per entry then adds them in order.  With a thread per entry reading
+// its own partials only 98 workgroups were in flight, 16 loads a turn each: 23
+// us, now 10.5.
+constexpr int AP = 32;          // entries per workgroup
+constexpr int ADT = 512;        // threads
+constexpr int ADU = 16;         // loads per thread and turn
+constexpr int ADK = ADT / AP * ADU;  // partials per turn
 
-// Parameter p: the sum of the workgroup partials in workgroup order, then
-// optionally one Adam step.
-__device__ inline void adam_param(int p, const float *part, int nwg, float *w, uint16_t *wb, float *m,
-                                  float *v, float lr, float bc1, float bc2, int update,
-                                  float *grad_out) {
-  const float g = sum_partials(part, nwg, p);
+__global__ __launch_bounds__(ADT) void ae_adam(const float *__restrict__ part, int nwg, float *w, uint16_t *wb,
+                                               float *m, float *v, float lr, float bc1, float bc2,
+                                               int update, float *grad_out, float *loss_out,
+                                               float loss_scale, float *epoch_loss, float lfrac) {
+  __shared__ float pl[ADK][AP];
+  const int e = (int)threadIdx.x % AP, k1 = (int)threadIdx.x / AP;
+  const int p = blockIdx.x * AP + e;
+  const bool mine = p <= AE_NP, sums = mine && threadIdx.x < AP;
+  float w0 = 0.f, m0 = 0.f, v0 = 0.f;
+  if (sums && update && p < AE_NP) {
+    w0 = w[p];
+    m0 = m[p];
+    v0 = v[p];
+  }
+  float g = 0.f;
+  for (int kb = 0; kb < nwg; kb += ADK) {
+    float x[ADU];
+#pragma unroll
+    for (int u = 0; u < ADU; u++) {
+      const int k = kb + u * (ADT / AP) + k1;
+      x[u] = mine && k < nwg ? part[(int64_t)k * (AE_NP + 1) + p] : 0.f;
+    }
+    if (kb) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < ADU; u++) pl[u * (ADT / AP) + k1][e] = x[u];
+    __syncthreads();
+    if (sums) {
+      const int nk = nwg - kb < ADK ? nwg - kb : ADK;
+#pragma unroll 16
+      for (int k = 0; k < nk; k++) g += pl[k][e];
+    }
+  }
+  if (!sums) return;
+  if (p == AE_NP) {
+    if (loss_out) {
+      const float l = g * loss_scale;
+      loss_out[0] = l;
+      if (epoch_loss) epoch_loss[0] += l * lfrac;
+    }
+    return;
+  }
   if (grad_out) grad_out[p] = g;
   if (update) {
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float mm = b1 * m[p] + (1.f - b1) * g;
-    const float vv = b2 * v[p] + (1.f - b2) * g * g;
+    const float mm = b1 * m0 + (1.f - b1) * g;
+    const float vv = b2 * v0 + (1.f - b2) * g * g;
     m[p] = mm;
     v[p] = vv;
-    const float wn = w[p] - lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
+    const float wn = w0 - lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
     w[p] = wn;
     if (p < AE_NW) wb[p] = f2bf(wn);
   }
 }
-
-__device__ inline float loss_sum(const float *part, int nwg) { return sum_partials(part, nwg, AE_NP); }
-
-// Sum the workgroup partials in workgroup order; optionally take one Adam step.
-// With epoch_loss, also epoch_loss[0] += loss * lfrac (the step's share of the
-// epoch's rows), in the kernel rather than a launch of its own.
-__global__ __launch_bounds__(256) void ae_adam(const float *part, int nwg, float *w, uint16_t *wb,
-                                               float *m, float *v, float lr, float bc1, float bc2,
-                                               int update, float *grad_out, float *loss_out,
-                                               float loss_scale, float *epoch_loss, float lfrac) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p < AE_NP) adam_param(p, part, nwg, w, wb, m, v, lr, bc1, bc2, update, grad_out);
-  if (p == 0 && loss_out) {
-    loss_out[0] = loss_sum(part, nwg) * loss_scale;
-    if (epoch_loss) epoch_loss[0] += loss_out[0] * lfrac;
-  }
-}
-
 
 // ---------------------------------------------------------------------------
 // Initialisation: Xavier-uniform weights from SplitMix64 counter draws.
@@ -1479,7 +1494,7 @@ hipError_t launch_ae_step(AeState &s, const float *rows, int64_t n, int64_t k0, 
     bc1 = (float)(1.0 - pow(0.9, (double)s.step));
     bc2 = (float)(1.0 - pow(0.999, (double)s.step));
   }
-  hipLaunchKernelGGL(ae_adam, dim3((AE_NP + 255) / 256), dim3(256), 0, st, s.part, AE_WG, s.w, s.wb,
+  hipLaunchKernelGGL(ae_adam, dim3(AE_NP / AP + 1), dim3(ADT), 0, st, s.part, AE_WG, s.w, s.wb,
                      s.m, s.v, lr, bc1, bc2, update ? 1 : 0, grad_out, loss_out ? loss_out : s.loss,
                      1.0f / (float)(bv * AE_IN), epoch_loss, lfrac);
   return hipGetLastError();
@@ -1491,7 +1506,7 @@ hipError_t launch_ae_grad_f32(AeState &s, const float *rows, int64_t n, float no
   const float scale = 2.0f / (float)(n * AE_IN);
   hipLaunchKernelGGL(ae_grad_f32_kernel, dim3(AE_WG), dim3(256), 0, st, rows, n, scale, noise_sd,
                      noise_key, s.w, s.part);
-  hipLaunchKernelGGL(ae_adam, dim3((AE_NP + 255) / 256), dim3(256), 0, st, s.part, AE_WG, s.w, s.wb,
+  hipLaunchKernelGGL(ae_adam, dim3(AE_NP / AP + 1), dim3(ADT), 0, st, s.part, AE_WG, s.w, s.wb,
                      s.m, s.v, 0.f, 1.f, 1.f, 0, grad_out, loss_out ? loss_out : s.loss,
                      1.0f / (float)(n * AE_IN), (float *)nullptr, 0.f);
   return hipGetLastError();
