@@ -15,7 +15,6 @@
 namespace ta {
 namespace {
 
-constexpr int AT = 256;       // threads per workgroup
 constexpr int TR = 16;        // rows per tile
 
 typedef short s4 __attribute__((ext_vector_type(4)));
@@ -26,30 +25,6 @@ __device__ inline uint16_t f2bf(float f) {
   return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
 }
 __device__ inline float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-// One 16x16 tile of D += A * B over K (a multiple of 16).  A(m, k) is
-// A[m*sam + k*sak], B(k, n) is B[k*sbk + n*sbn] (bfloat16 in LDS).  Operand
-// lane layout: lane l supplies row/column (l & 15) and k = 4*(l >> 4) + 0..3;
-// the result holds rows 4*(l >> 4) + 0..3 of column (l & 15).
-__device__ inline f4 mma_tile(const uint16_t *A, int sam, int sak, const uint16_t *B, int sbk,
-                              int sbn, int m0, int n0, int K, f4 acc) {
-  const int lane = threadIdx.x & 63;
-  const int mi = m0 + (lane & 15), ni = n0 + (lane & 15), kq = 4 * (lane >> 4);
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    s4 a, b;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int k = k0 + kq + j;
-      a[j] = (short)A[mi * sam + k * sak];
-      b[j] = (short)B[k * sbk + ni * sbn];
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-__device__ inline int out_row(int j) { return 4 * ((threadIdx.x & 63) >> 4) + j; }
-__device__ inline int out_col() { return threadIdx.x & 15; }
 
 // Sum of a value over the four lane groups that hold the same column.
 __device__ inline float col_sum(float v) {
@@ -62,81 +37,6 @@ __device__ inline double col_sum(double v) {
   v += __shfl_xor(v, 16, 64);
   v += __shfl_xor(v, 32, 64);
   return v;
-}
-
-struct AeLds {
-  uint16_t W[AE_NW];          // bf16 weights
-  float b[AE_NP - AE_NW];     // biases
-  float X[TR * AE_IN];        // targets (FP32)
-  uint16_t Xb[TR * AE_IN];
-  uint16_t H1[TR * AE_H1], H2[TR * AE_H2], H3[TR * AE_H3];
-  uint16_t D4[TR * AE_IN], D3[TR * AE_H3], D2[TR * AE_H2], D1[TR * AE_H1];
-  float red[AT];
-  double redd[AT];
-  int valid[TR];
-};
-
-// The bf16 weights (16-byte loads, all of a thread's loads issued before its
-// first LDS store: one round trip, not one per word) and the FP32 biases.
-__device__ void stage_weights(AeLds &L, const uint16_t *wb, const float *w) {
-  constexpr int NV = AE_NW * 2 / 16;     // 16-byte words of bf16 weights
-  constexpr int PER = NV / AT;
-  constexpr int NB = AE_NP - AE_NW;      // biases
-  constexpr int PB = (NB + AT - 1) / AT;
-  static_assert(NV % AT == 0, "the weights are staged in whole steps of the workgroup");
-  const int t = threadIdx.x;
-  const uint4 *src = reinterpret_cast<const uint4 *>(wb);
-  uint4 *dst = reinterpret_cast<uint4 *>(L.W);
-  uint4 v[PER];
-  float bv[PB];
-#pragma unroll
-  for (int u = 0; u < PER; u++) v[u] = src[u * AT + t];
-#pragma unroll
-  for (int u = 0; u < PB; u++) bv[u] = u * AT + t < NB ? w[AE_NW + u * AT + t] : 0.f;
-#pragma unroll
-  for (int u = 0; u < PER; u++) dst[u * AT + t] = v[u];
-#pragma unroll
-  for (int u = 0; u < PB; u++)
-    if (u * AT + t < NB) L.b[u * AT + t] = bv[u];
-}
-
-// Forward through the four layers for the tile in L.Xb.  Hidden activations
-// are stored as bf16 after ReLU; the output pre-activation tile of wave w
-// (columns 16w..16w+15) is returned in `y` (bias added).
-__device__ inline void forward(AeLds &L, f4 &y) {
-  const int wid = threadIdx.x >> 6;
-  const f4 z0 = {0.f, 0.f, 0.f, 0.f};
-  // L1: [16 x 64] * W1^T -> [16 x 128]
-  for (int t = wid; t < AE_H1 / 16; t += 4) {
-    f4 a = mma_tile(L.Xb, AE_IN, 1, L.W + AE_W1, 1, AE_IN, 0, 16 * t, AE_IN, z0);
-    const int c = 16 * t + out_col();
-#pragma unroll
-    for (int j = 0; j < 4; j++) L.H1[out_row(j) * AE_H1 + c] = f2bf(fmaxf(a[j] + L.b[c], 0.f));
-  }
-  __syncthreads();
-  // L2: [16 x 128] * W2^T -> [16 x 32]
-  for (int t = wid; t < AE_H2 / 16; t += 4) {
-    f4 a = mma_tile(L.H1, AE_H1, 1, L.W + AE_W2, 1, AE_H1, 0, 16 * t, AE_H1, z0);
-    const int c = 16 * t + out_col();
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-      L.H2[out_row(j) * AE_H2 + c] = f2bf(fmaxf(a[j] + L.b[AE_B2 - AE_B1 + c], 0.f));
-  }
-  __syncthreads();
-  // L3: [16 x 32] * W3^T -> [16 x 128]
-  for (int t = wid; t < AE_H3 / 16; t += 4) {
-    f4 a = mma_tile(L.H2, AE_H2, 1, L.W + AE_W3, 1, AE_H2, 0, 16 * t, AE_H2, z0);
-    const int c = 16 * t + out_col();
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-      L.H3[out_row(j) * AE_H3 + c] = f2bf(fmaxf(a[j] + L.b[AE_B3 - AE_B1 + c], 0.f));
-  }
-  __syncthreads();
-  // L4: [16 x 128] * W4^T -> [16 x 64]; wave w owns columns 16w..16w+15
-  y = mma_tile(L.H3, AE_H3, 1, L.W + AE_W4, 1, AE_H3, 0, 16 * wid, AE_H3, z0);
-  const int c = 16 * wid + out_col();
-#pragma unroll
-  for (int j = 0; j < 4; j++) y[j] += L.b[AE_B4 - AE_B1 + c];
 }
 
 // SplitMix64 finaliser (Steele, Lea & Flood 2014), used as a counter-based
@@ -159,195 +59,285 @@ __device__ inline float gauss_draw(uint64_t key, uint64_t row, int c) {
   return sqrtf(-2.0f * logf(u1)) * cosf(6.2831853071795864f * u2);
 }
 
-__device__ inline uint64_t perm_row(uint64_t k, uint64_t a, uint64_t c, uint64_t n) {
-  return (a * k + c) % n;
+// (a * k + c) % n for a, c, k < n <= 2^31 (n_inv = 1.0 / n): the FP64 quotient
+// is off by at most one.
+__device__ inline int64_t perm_row(int64_t k, int64_t a, int64_t c, int64_t n, double n_inv) {
+  const int64_t x = a * k + c;
+  int64_t r = x - (int64_t)((double)x * n_inv) * n;
+  r += r < 0 ? n : 0;
+  return r - (r >= n ? n : 0);
 }
 
 // ---------------------------------------------------------------------------
 // Training step: gradient partials of the mean squared error over the rows
-// perm(k), k in [k0, k_end), written per workgroup to part[wg][AE_NP + 1].
+// perm(k), k in [k0, k_end), written per workgroup to part[wg][AE_PS].
 // With noise_sd > 0 the network sees x + noise_sd * N(0, 1) (drawn for the
 // row's index and the feature under noise_key) and is scored against x
 // (denoising training).
+//
+// Bound by the chain of seven dependent products of one 16-row tile per
+// workgroup (4,096 rows: one tile per CU), so by latencies.  Eight waves; wave w
+// owns columns 16w..16w+15 of the 128-wide layers (waves 0-1 those of the
+// 32-wide one, 0-3 the outputs) and keeps its weight operands in registers,
+// read from global memory once, while the rows and the noise come in.  With q =
+// lane >> 4 and x = lane & 15 an operand of the 16x16x16 product is entries
+// (x, k = 4q..4q+3), and a product yields rows 4q..4q+3 of column x.  So
+// each tile is computed with its operands in both orders (the same products in
+// the same order: the same bits): rows-in-lanes ("T": row x, columns 4q..4q+3)
+// is the next product's operand, columns-in-lanes ("N": column x, rows 4q..4q+3)
+// is the operand of the weight gradients, which contract over rows.  Neither is
+// transposed: 8-byte LDS words by lane, without conflicts.  With the weights
+// staged in LDS, four waves and operands gathered by 2-byte reads 25 us at 4,096
+// rows, now 18.4, of which the stores of the partials (25.5 MB, past the caches:
+// 2 us less than through them) are about 9 and the weights about 3.
 // ---------------------------------------------------------------------------
+constexpr int AT = 512;  // threads per workgroup
+
+__device__ __forceinline__ f4 mma(s4 a, s4 b, f4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ s4 ld4(const uint16_t *p) { return *reinterpret_cast<const s4 *>(p); }
+
+__device__ __forceinline__ s4 relu_bf(f4 a, f4 b) {
+  s4 r;
+#pragma unroll
+  for (int j = 0; j < 4; j++) r[j] = (short)f2bf(fmaxf(a[j] + b[j], 0.f));
+  return r;
+}
+// The gradient where the ReLU was active.
+__device__ __forceinline__ f4 masked(f4 a, s4 h) {
+  f4 r;
+#pragma unroll
+  for (int j = 0; j < 4; j++) r[j] = h[j] > 0 ? a[j] : 0.f;
+  return r;
+}
+__device__ __forceinline__ s4 to_bf(f4 a) {
+  s4 r;
+#pragma unroll
+  for (int j = 0; j < 4; j++) r[j] = (short)f2bf(a[j]);
+  return r;
+}
+
 __global__ __launch_bounds__(AT) void ae_fwdbwd(const float *__restrict__ rows, int64_t n,
-                                                 int64_t k0, int64_t k_end, uint64_t pa,
-                                                 uint64_t pc, float scale, float noise_sd,
+                                                 int64_t k0, int64_t k_end, int64_t pa,
+                                                 int64_t pc, double n_inv, float scale, float noise_sd,
                                                  uint64_t noise_key,
                                                  const uint16_t *__restrict__ wb,
                                                  const float *__restrict__ w, float *part) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  AeLds &L = *reinterpret_cast<AeLds *>(smem);
-  const int tid = threadIdx.x, wid = tid >> 6;
-  stage_weights(L, wb, w);
+  constexpr int XS = AE_IN + 4;  // floats per staged row
+  __shared__ __align__(16) float X[TR * XS];
+  __shared__ s4 XT[4][64], XN[4][64], H1T[8][64], H2T[2][64], H2N[2][64], H3T[8][64];
+  __shared__ s4 D4T[4][64], D4N[4][64], D3T[8][64], D2T[2][64], D2N[2][64];
+  __shared__ double redd[AT];
+  const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int q4 = 4 * (lane >> 4), x = lane & 15;
   const int64_t tiles = (k_end - k0 + TR - 1) / TR;
   const int64_t t_lo = tiles * blockIdx.x / gridDim.x, t_hi = tiles * (blockIdx.x + 1) / gridDim.x;
 
+  // the rows of the first tile; two floats per thread
+  const int xr = tid >> 5, xc = (tid & 31) * 2;
+  int32_t row = 0;
+  float2 v = {0.f, 0.f};
+  auto load_rows = [&](int64_t t) {
+    const int64_t k = k0 + t * TR + xr;
+    v = float2{0.f, 0.f};
+    if (t < t_hi && k < k_end) {
+      row = (int32_t)perm_row(k, pa, pc, n, n_inv);
+      v = *reinterpret_cast<const float2 *>(rows + (int64_t)row * AE_IN + xc);
+    }
+  };
+  load_rows(t_lo);
+
+  // this wave's weights: operand entries (x, 4q..4q+3) of 16-wide pieces
+  const int c0 = 16 * wid + x;
+  const uint16_t *wt = wb + AE_NW - AE_W2;
+  s4 W1[4], W2[8], W3[2], W4[8], T4[4], T3[8], T2[2];
+#pragma unroll
+  for (int i = 0; i < 4; i++) W1[i] = ld4(wb + AE_W1 + c0 * AE_IN + 16 * i + q4);
+#pragma unroll
+  for (int i = 0; i < 2; i++) W3[i] = ld4(wb + AE_W3 + c0 * AE_H2 + 16 * i + q4);
+#pragma unroll
+  for (int i = 0; i < 4; i++) T4[i] = ld4(wt + AE_W4 + c0 * AE_IN + 16 * i + q4);
+#pragma unroll
+  for (int i = 0; i < 2; i++) T2[i] = ld4(wt + AE_W2 + c0 * AE_H2 + 16 * i + q4);
   const f4 z0 = {0.f, 0.f, 0.f, 0.f};
-  f4 gW1[8], gW4[8], gW2[4], gW3[4];
+  const float b1 = w[AE_B1 + c0], b3 = w[AE_B3 + c0];
+  const f4 b1n = {b1, b1, b1, b1}, b3n = {b3, b3, b3, b3};
+  const f4 b1t = *reinterpret_cast<const f4 *>(w + AE_B1 + 16 * wid + q4);
+  const f4 b3t = *reinterpret_cast<const f4 *>(w + AE_B3 + 16 * wid + q4);
+  float b2 = 0.f, b4 = 0.f;
+  f4 b2t = z0, b4t = z0;
+  if (wid < 2) {
 #pragma unroll
-  for (int q = 0; q < 8; q++) gW1[q] = gW4[q] = z0;
+    for (int i = 0; i < 8; i++) {
+      W2[i] = ld4(wb + AE_W2 + c0 * AE_H1 + 16 * i + q4);
+      T3[i] = ld4(wt + AE_W3 + c0 * AE_H3 + 16 * i + q4);
+    }
+    b2 = w[AE_B2 + c0];
+    b2t = *reinterpret_cast<const f4 *>(w + AE_B2 + 16 * wid + q4);
+  }
+  if (wid < 4) {
 #pragma unroll
-  for (int q = 0; q < 4; q++) gW2[q] = gW3[q] = z0;
-  float gb1[2] = {0.f, 0.f}, gb3[2] = {0.f, 0.f}, gb2 = 0.f, gb4 = 0.f, loss = 0.f;
+    for (int i = 0; i < 8; i++) W4[i] = ld4(wb + AE_W4 + c0 * AE_H3 + 16 * i + q4);
+    b4 = w[AE_B4 + c0];
+    b4t = *reinterpret_cast<const f4 *>(w + AE_B4 + 16 * wid + q4);
+  }
+
+  f4 gW1[4], gW4[4], gW2[2], gW3[2];
+#pragma unroll
+  for (int i = 0; i < 4; i++) gW1[i] = gW4[i] = z0;
+#pragma unroll
+  for (int i = 0; i < 2; i++) gW2[i] = gW3[i] = z0;
+  float gb1 = 0.f, gb2 = 0.f, gb3 = 0.f, gb4 = 0.f, loss = 0.f;
 
   for (int64_t t = t_lo; t < t_hi; t++) {
-    __syncthreads();
-    {  // load 16 rows (4 floats per thread)
-      const int r = tid >> 4, c4 = (tid & 15) * 4;
-      const int64_t k = k0 + t * TR + r;
-      const bool ok = k < k_end;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      const uint64_t row = ok ? perm_row((uint64_t)k, pa, pc, (uint64_t)n) : 0;
-      if (ok) v = *reinterpret_cast<const float4 *>(rows + row * AE_IN + c4);
-      L.X[r * AE_IN + c4 + 0] = v.x;
-      L.X[r * AE_IN + c4 + 1] = v.y;
-      L.X[r * AE_IN + c4 + 2] = v.z;
-      L.X[r * AE_IN + c4 + 3] = v.w;
-      float4 xin = v;
-      if (ok && noise_sd > 0.f) {
-        xin.x += noise_sd * gauss_draw(noise_key, row, c4 + 0);
-        xin.y += noise_sd * gauss_draw(noise_key, row, c4 + 1);
-        xin.z += noise_sd * gauss_draw(noise_key, row, c4 + 2);
-        xin.w += noise_sd * gauss_draw(noise_key, row, c4 + 3);
+    {
+      float2 in = v;
+      if (noise_sd > 0.f && k0 + t * TR + xr < k_end) {
+        in.x += noise_sd * gauss_draw(noise_key, (uint64_t)row, xc);
+        in.y += noise_sd * gauss_draw(noise_key, (uint64_t)row, xc + 1);
       }
-      L.Xb[r * AE_IN + c4 + 0] = f2bf(xin.x);
-      L.Xb[r * AE_IN + c4 + 1] = f2bf(xin.y);
-      L.Xb[r * AE_IN + c4 + 2] = f2bf(xin.z);
-      L.Xb[r * AE_IN + c4 + 3] = f2bf(xin.w);
-      if ((tid & 15) == 0) L.valid[r] = ok;
+      const uint16_t i0 = f2bf(in.x), i1 = f2bf(in.y);
+      *reinterpret_cast<float2 *>(&X[xr * XS + xc]) = v;
+      const int ft = xc >> 4, f = xc & 15;
+      uint16_t *xt = reinterpret_cast<uint16_t *>(&XT[ft][(f >> 2) * 16 + xr]) + (f & 3);
+      *reinterpret_cast<uint32_t *>(xt) = (uint32_t)i0 | (uint32_t)i1 << 16;
+      uint16_t *xn = reinterpret_cast<uint16_t *>(&XN[ft][(xr >> 2) * 16 + f]) + (xr & 3);
+      xn[0] = i0;
+      xn[4] = i1;
     }
     __syncthreads();
-    f4 y;
-    forward(L, y);
-    {  // output error -> D4 (dL/dy), loss, db4
-      const int c = 16 * wid + out_col();
+    f4 an = z0, at = z0;
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int r = out_row(j);
-        float d = 0.f;
-        if (L.valid[r]) {
-          const float e = y[j] - L.X[r * AE_IN + c];
-          loss += e * e;
-          d = scale * e;
-        }
-        gb4 += d;
-        L.D4[r * AE_IN + c] = f2bf(d);
-      }
+    for (int i = 0; i < 4; i++) {
+      const s4 xi = XT[i][lane];
+      an = mma(xi, W1[i], an);
+      at = mma(W1[i], xi, at);
     }
+    const s4 h1n = relu_bf(an, b1n);
+    H1T[wid][lane] = relu_bf(at, b1t);
     __syncthreads();
-    // dW4 [64 x 128] += D4^T H3 ; 32 tiles, 8 per wave
-#pragma unroll
-    for (int q = 0; q < 8; q++) {
-      const int tt = wid * 8 + q, mt = tt >> 3, nt = tt & 7;
-      gW4[q] = mma_tile(L.D4, 1, AE_IN, L.H3, AE_H3, 1, 16 * mt, 16 * nt, TR, gW4[q]);
-    }
-    // dH3 [16 x 128] = D4 W4 ; mask by H3 > 0 -> D3
-#pragma unroll
-    for (int q = 0; q < 2; q++) {
-      const int nt = wid + 4 * q;
-      f4 a = mma_tile(L.D4, AE_IN, 1, L.W + AE_W4, AE_H3, 1, 0, 16 * nt, AE_IN, z0);
-      const int c = 16 * nt + out_col();
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int r = out_row(j);
-        const float d = (int16_t)L.H3[r * AE_H3 + c] > 0 ? a[j] : 0.f;  // ReLU was active
-        gb3[q] += d;
-        L.D3[r * AE_H3 + c] = f2bf(d);
-      }
-    }
-    __syncthreads();
-    // dW3 [128 x 32] += D3^T H2 ; 16 tiles, 4 per wave
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int tt = wid * 4 + q, mt = tt >> 1, nt = tt & 1;
-      gW3[q] = mma_tile(L.D3, 1, AE_H3, L.H2, AE_H2, 1, 16 * mt, 16 * nt, TR, gW3[q]);
-    }
-    // dH2 [16 x 32] = D3 W3 -> D2
+    s4 h2n, h2t;
     if (wid < 2) {
-      f4 a = mma_tile(L.D3, AE_H3, 1, L.W + AE_W3, AE_H2, 1, 0, 16 * wid, AE_H3, z0);
-      const int c = 16 * wid + out_col();
+      an = at = z0;
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int r = out_row(j);
-        const float d = (int16_t)L.H2[r * AE_H2 + c] > 0 ? a[j] : 0.f;
-        gb2 += d;
-        L.D2[r * AE_H2 + c] = f2bf(d);
+      for (int i = 0; i < 8; i++) {
+        const s4 hi = H1T[i][lane];
+        an = mma(hi, W2[i], an);
+        at = mma(W2[i], hi, at);
       }
+      const f4 b2n = {b2, b2, b2, b2};
+      H2N[wid][lane] = h2n = relu_bf(an, b2n);
+      H2T[wid][lane] = h2t = relu_bf(at, b2t);
     }
     __syncthreads();
-    // dW2 [32 x 128] += D2^T H1 ; 16 tiles, 4 per wave
+    an = at = z0;
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int tt = wid * 4 + q, mt = tt >> 3, nt = tt & 7;
-      gW2[q] = mma_tile(L.D2, 1, AE_H2, L.H1, AE_H1, 1, 16 * mt, 16 * nt, TR, gW2[q]);
+    for (int i = 0; i < 2; i++) {
+      const s4 hi = H2T[i][lane];
+      an = mma(hi, W3[i], an);
+      at = mma(W3[i], hi, at);
     }
-    // dH1 [16 x 128] = D2 W2 -> D1
+    const s4 h3n = relu_bf(an, b3n), h3t = relu_bf(at, b3t);
+    H3T[wid][lane] = h3t;
+    __syncthreads();
+    if (wid < 4) {  // outputs -> dL/dy, loss, db4
+      an = at = z0;
 #pragma unroll
-    for (int q = 0; q < 2; q++) {
-      const int nt = wid + 4 * q;
-      f4 a = mma_tile(L.D2, AE_H2, 1, L.W + AE_W2, AE_H1, 1, 0, 16 * nt, AE_H2, z0);
-      const int c = 16 * nt + out_col();
+      for (int i = 0; i < 8; i++) {
+        const s4 hi = H3T[i][lane];
+        an = mma(hi, W4[i], an);
+        at = mma(W4[i], hi, at);
+      }
+      const f4 xt = *reinterpret_cast<const f4 *>(&X[x * XS + 16 * wid + q4]);
+      const int64_t left = k_end - (k0 + t * TR);  // rows of this tile
+      f4 dn, dt;
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        const int r = out_row(j);
-        const float d = (int16_t)L.H1[r * AE_H1 + c] > 0 ? a[j] : 0.f;
-        gb1[q] += d;
-        L.D1[r * AE_H1 + c] = f2bf(d);
+        const float e = an[j] + b4 - X[(q4 + j) * XS + c0];
+        const bool ok = q4 + j < left;
+        if (ok) loss += e * e;
+        dn[j] = ok ? scale * e : 0.f;
+        gb4 += dn[j];
+        dt[j] = x < left ? scale * (at[j] + b4t[j] - xt[j]) : 0.f;
       }
+      D4N[wid][lane] = to_bf(dn);
+      D4T[wid][lane] = to_bf(dt);
     }
+    load_rows(t + 1);
     __syncthreads();
-    // dW1 [128 x 64] += D1^T Xb ; 32 tiles, 8 per wave
+    // dW4 += D4^T H3; dH3 = D4 W4
+    an = at = z0;
 #pragma unroll
-    for (int q = 0; q < 8; q++) {
-      const int tt = wid * 8 + q, mt = tt >> 2, nt = tt & 3;
-      gW1[q] = mma_tile(L.D1, 1, AE_H1, L.Xb, AE_IN, 1, 16 * mt, 16 * nt, TR, gW1[q]);
+    for (int i = 0; i < 4; i++) {
+      const s4 di = D4T[i][lane];
+      an = mma(di, T4[i], an);
+      at = mma(T4[i], di, at);
+      gW4[i] = mma(h3n, D4N[i][lane], gW4[i]);
     }
+    an = masked(an, h3n);
+#pragma unroll
+    for (int j = 0; j < 4; j++) gb3 += an[j];
+    const s4 d3n = to_bf(an);
+    D3T[wid][lane] = to_bf(masked(at, h3t));
+    __syncthreads();
+    // dW3 += D3^T H2; dH2 = D3 W3
+    if (wid < 2) {
+      an = at = z0;
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const s4 di = D3T[i][lane];
+        an = mma(di, T3[i], an);
+        at = mma(T3[i], di, at);
+      }
+      an = masked(an, h2n);
+#pragma unroll
+      for (int j = 0; j < 4; j++) gb2 += an[j];
+      D2N[wid][lane] = to_bf(an);
+      D2T[wid][lane] = to_bf(masked(at, h2t));
+    }
+#pragma unroll
+    for (int i = 0; i < 2; i++) gW3[i] = mma(H2N[i][lane], d3n, gW3[i]);
+    __syncthreads();
+    // dW2 += D2^T H1; dH1 = D2 W2; dW1 += D1^T X
+    an = z0;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      an = mma(D2T[i][lane], T2[i], an);
+      gW2[i] = mma(h1n, D2N[i][lane], gW2[i]);
+    }
+    an = masked(an, h1n);
+#pragma unroll
+    for (int j = 0; j < 4; j++) gb1 += an[j];
+    const s4 d1n = to_bf(an);
+#pragma unroll
+    for (int i = 0; i < 4; i++) gW1[i] = mma(XN[i][lane], d1n, gW1[i]);
+    __syncthreads();
   }
 
   // Write this workgroup's partials (every element exactly once).
-  float *P = part + (int64_t)blockIdx.x * (AE_NP + 1);
-  const int cc = out_col();
+  float *P = part + (int64_t)blockIdx.x * AE_PS;
 #pragma unroll
-  for (int q = 0; q < 8; q++) {
-    {
-      const int tt = wid * 8 + q, mt = tt >> 2, nt = tt & 3;
-#pragma unroll
-      for (int j = 0; j < 4; j++) P[AE_W1 + (16 * mt + out_row(j)) * AE_IN + 16 * nt + cc] = gW1[q][j];
-    }
-    {
-      const int tt = wid * 8 + q, mt = tt >> 3, nt = tt & 7;
-#pragma unroll
-      for (int j = 0; j < 4; j++) P[AE_W4 + (16 * mt + out_row(j)) * AE_H3 + 16 * nt + cc] = gW4[q][j];
-    }
+  for (int i = 0; i < 4; i++) {
+    __builtin_nontemporal_store(gW1[i], reinterpret_cast<f4 *>(P + AE_W1 + c0 * AE_IN + 16 * i + q4));
+    __builtin_nontemporal_store(gW4[i], reinterpret_cast<f4 *>(P + AE_W4 + (16 * i + x) * AE_H3 + 16 * wid + q4));
   }
 #pragma unroll
-  for (int q = 0; q < 4; q++) {
-    {
-      const int tt = wid * 4 + q, mt = tt >> 3, nt = tt & 7;
-#pragma unroll
-      for (int j = 0; j < 4; j++) P[AE_W2 + (16 * mt + out_row(j)) * AE_H1 + 16 * nt + cc] = gW2[q][j];
-    }
-    {
-      const int tt = wid * 4 + q, mt = tt >> 1, nt = tt & 1;
-#pragma unroll
-      for (int j = 0; j < 4; j++) P[AE_W3 + (16 * mt + out_row(j)) * AE_H2 + 16 * nt + cc] = gW3[q][j];
-    }
+  for (int i = 0; i < 2; i++) {
+    __builtin_nontemporal_store(gW2[i], reinterpret_cast<f4 *>(P + AE_W2 + (16 * i + x) * AE_H1 + 16 * wid + q4));
+    __builtin_nontemporal_store(gW3[i], reinterpret_cast<f4 *>(P + AE_W3 + c0 * AE_H2 + 16 * i + q4));
   }
-  const int lane = tid & 63;
-  const float b4s = col_sum(gb4);
-  const float b3s0 = col_sum(gb3[0]), b3s1 = col_sum(gb3[1]);
-  const float b1s0 = col_sum(gb1[0]), b1s1 = col_sum(gb1[1]);
-  const float b2s = col_sum(gb2);
+  gb1 = col_sum(gb1);
+  gb2 = col_sum(gb2);
+  gb3 = col_sum(gb3);
+  gb4 = col_sum(gb4);
   if (lane < 16) {
-    P[AE_B4 + 16 * wid + lane] = b4s;
-    P[AE_B3 + 16 * wid + lane] = b3s0;
-    P[AE_B3 + 16 * (wid + 4) + lane] = b3s1;
-    P[AE_B1 + 16 * wid + lane] = b1s0;
-    P[AE_B1 + 16 * (wid + 4) + lane] = b1s1;
-    if (wid < 2) P[AE_B2 + 16 * wid + lane] = b2s;
+    P[AE_B1 + c0] = gb1;
+    P[AE_B3 + c0] = gb3;
+    if (wid < 4) P[AE_B4 + c0] = gb4;
+    if (wid < 2) P[AE_B2 + c0] = gb2;
   }
-  const double ls = block_sum_f64<AT>((double)loss, L.redd);
+  const double ls = block_sum_f64<AT>((double)loss, redd);
   if (tid == 0) P[AE_NP] = (float)ls;
 }
 
@@ -367,7 +357,7 @@ __global__ __launch_bounds__(256) void ae_grad_f32_kernel(const float *__restric
   __shared__ float d4[AE_IN], d3[AE_H3], d2[AE_H2], d1[AE_H1];
   __shared__ double red[256];
   const int t = threadIdx.x;
-  float *P = part + (int64_t)blockIdx.x * (AE_NP + 1);
+  float *P = part + (int64_t)blockIdx.x * AE_PS;
   for (int p = t; p < AE_NP; p += 256) P[p] = 0.f;
   double loss = 0.0;
   for (int64_t r = blockIdx.x; r < n; r += gridDim.x) {
@@ -447,7 +437,7 @@ __global__ __launch_bounds__(256) void ae_grad_f32_kernel(const float *__restric
 // entries and brings their partials to LDS, 16 loads per thread in flight; one
 // thread per entry then adds them in order.  With a thread per entry reading
 // its own partials only 98 workgroups were in flight, 16 loads a turn each: 23
-// us, now 10.5.
+// us, now 8.
 constexpr int AP = 32;          // entries per workgroup
 constexpr int ADT = 512;        // threads
 constexpr int ADU = 16;         // loads per thread and turn
@@ -473,7 +463,7 @@ __global__ __launch_bounds__(ADT) void ae_adam(const float *__restrict__ part, i
 #pragma unroll
     for (int u = 0; u < ADU; u++) {
       const int k = kb + u * (ADT / AP) + k1;
-      x[u] = mine && k < nwg ? part[(int64_t)k * (AE_NP + 1) + p] : 0.f;
+      x[u] = mine && k < nwg ? __builtin_nontemporal_load(&part[(int64_t)k * AE_PS + p]) : 0.f;
     }
     if (kb) __syncthreads();
 #pragma unroll
@@ -503,7 +493,11 @@ __global__ __launch_bounds__(ADT) void ae_adam(const float *__restrict__ part, i
     v[p] = vv;
     const float wn = w0 - lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
     w[p] = wn;
-    if (p < AE_NW) wb[p] = f2bf(wn);
+    if (p < AE_NW) {
+      const uint16_t b = f2bf(wn);
+      wb[p] = b;
+      if (p >= AE_W2) wb[ae_transposed(p)] = b;
+    }
   }
 }
 
@@ -529,6 +523,7 @@ __global__ void ae_init_kernel(uint64_t seed, float *w, uint16_t *wb, float *m, 
     const double a = sqrt(6.0 / (double)(fin + fout));
     val = (float)((2.0 * u - 1.0) * a);
     wb[p] = f2bf(val);
+    if (p >= AE_W2) wb[ae_transposed(p)] = wb[p];
   }
   w[p] = val;
   m[p] = 0.f;
@@ -1404,7 +1399,7 @@ hipError_t ae_alloc(AeState &s) {
     if (e == hipSuccess) e = hipMalloc(p, b);
   };
   A((void **)&s.w, AE_NP * 4);
-  A((void **)&s.wb, AE_NW * 2);
+  A((void **)&s.wb, AE_NB16 * 2);
   A((void **)&s.m, AE_NP * 4);
   A((void **)&s.v, AE_NP * 4);
   A((void **)&s.mu, 64 * 4);
@@ -1412,7 +1407,7 @@ hipError_t ae_alloc(AeState &s) {
   A((void **)&s.nsum, 64 * 8);
   A((void **)&s.nsq, 128 * 8);
   A((void **)&s.ncnt, 8 * 8);
-  A((void **)&s.part, (size_t)AE_WG * (AE_NP + 1) * 4);
+  A((void **)&s.part, (size_t)AE_WG * AE_PS * 4);
   A((void **)&s.loss, 16);
   return e;
 }
@@ -1467,16 +1462,6 @@ hipError_t launch_ae_rows(const AeState &s, const int64_t *T, int64_t R, int I, 
   return e;
 }
 
-template <class K>
-void allow_lds(K k) {
-  static bool done = false;
-  if (!done) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                        (int)sizeof(AeLds));
-    done = true;
-  }
-}
-
 hipError_t launch_ae_step(AeState &s, const float *rows, int64_t n, int64_t k0, int batch,
                           uint64_t a, uint64_t c, float lr, bool update, float noise_sd,
                           uint64_t noise_key, hipStream_t st, float *grad_out, float *loss_out,
@@ -1485,9 +1470,8 @@ hipError_t launch_ae_step(AeState &s, const float *rows, int64_t n, int64_t k0, 
   const int64_t bv = k_end - k0;
   if (bv <= 0) return hipErrorInvalidValue;
   const float scale = 2.0f / (float)(bv * AE_IN);
-  allow_lds(&ae_fwdbwd);
-  hipLaunchKernelGGL(ae_fwdbwd, dim3(AE_WG), dim3(AT), sizeof(AeLds), st, rows, n, k0, k_end, a, c,
-                     scale, noise_sd, noise_key, s.wb, s.w, s.part);
+  hipLaunchKernelGGL(ae_fwdbwd, dim3(AE_WG), dim3(AT), 0, st, rows, n, k0, k_end, (int64_t)a, (int64_t)c,
+                     1.0 / (double)n, scale, noise_sd, noise_key, s.wb, s.w, s.part);
   float bc1 = 1.f, bc2 = 1.f;
   if (update) {
     s.step++;

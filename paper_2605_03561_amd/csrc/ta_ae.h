@@ -26,10 +26,25 @@ constexpr int AE_B2 = AE_B1 + AE_H1;
 constexpr int AE_B3 = AE_B2 + AE_H2;
 constexpr int AE_B4 = AE_B3 + AE_H3;
 constexpr int AE_NP = AE_B4 + AE_IN;           // 24928 parameters
+// bfloat16 weights: the four matrices, then W2, W3 and W4 transposed, which the
+// backward products read 8 bytes at a time along their rows.
+constexpr int AE_NB16 = AE_NW + (AE_NW - AE_W2);
+// Where weight p >= AE_W2 stands in the transposed part.
+__host__ __device__ inline int ae_transposed(int p) {
+  const int rows = p < AE_W3 ? AE_H2 : (p < AE_W4 ? AE_H3 : AE_IN);
+  const int cols = p < AE_W3 ? AE_H1 : (p < AE_W4 ? AE_H2 : AE_H3);
+  const int base = p < AE_W3 ? AE_W2 : (p < AE_W4 ? AE_W3 : AE_W4);
+  const int r = (p - base) / cols, c = (p - base) % cols;
+  return AE_NW - AE_W2 + base + c * rows + r;
+}
+// Entries per workgroup of the gradient partials: the parameters and the loss,
+// rows of whole 128-byte lines.
+constexpr int AE_PS = AE_NP + 32;
+static_assert(AE_PS % 32 == 0, "partials start on lines");
 
 struct AeState {
   float *w = nullptr;        // [AE_NP] FP32 master parameters
-  uint16_t *wb = nullptr;    // [AE_NW] bfloat16 copy of the weights
+  uint16_t *wb = nullptr;    // [AE_NB16] bfloat16 copies of the weights
   float *m = nullptr;        // [AE_NP] Adam first moment
   float *v = nullptr;        // [AE_NP] Adam second moment
   float *mu = nullptr;       // [64] region mean
@@ -37,7 +52,7 @@ struct AeState {
   int64_t *nsum = nullptr;   // [64] running sum of cell values   (normalisation fit)
   uint64_t *nsq = nullptr;   // [64][2] running 128-bit sum of squares
   int64_t *ncnt = nullptr;   // [1] running cell count per region
-  float *part = nullptr;     // [AE_WG][AE_NP + 1] per-workgroup gradient partials (+ loss)
+  float *part = nullptr;     // [AE_WG][AE_PS] per-workgroup gradient partials (+ loss)
   float *loss = nullptr;     // [1] loss of the last step / batch
   int64_t step = 0;          // Adam step counter
   bool ready = false;        // weights initialised

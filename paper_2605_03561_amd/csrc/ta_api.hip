@@ -1957,15 +1957,16 @@ ta_status ta_ae_set_state(ta_handle h, const void *buf_host, size_t bytes) {
   if (st) return st;
   TA_HIP(h, hipDeviceSynchronize());
   const char *p = (const char *)buf_host + sizeof hd;
-  std::vector<uint16_t> wb(ta::AE_NW);
+  std::vector<uint16_t> wb(ta::AE_NB16);
   const float *wf = (const float *)p;
   for (int i = 0; i < ta::AE_NW; i++) {
     uint32_t u;
     memcpy(&u, wf + i, 4);
     wb[i] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    if (i >= ta::AE_W2) wb[ta::ae_transposed(i)] = wb[i];
   }
   TA_HIP(h, hipMemcpy(h->ae.w, p, ta::AE_NP * 4, hipMemcpyHostToDevice));
-  TA_HIP(h, hipMemcpy(h->ae.wb, wb.data(), ta::AE_NW * 2, hipMemcpyHostToDevice));
+  TA_HIP(h, hipMemcpy(h->ae.wb, wb.data(), wb.size() * 2, hipMemcpyHostToDevice));
   p += ta::AE_NP * 4;
   TA_HIP(h, hipMemcpy(h->ae.m, p, ta::AE_NP * 4, hipMemcpyHostToDevice));
   p += ta::AE_NP * 4;
