@@ -49,21 +49,15 @@ __device__ inline EvQuad load_quad(const int64_t *__restrict__ ts, const int32_t
   return q;
 }
 
+// The same, four events at a time: f(k0, quad of events k0..k0+3); those
+// outside [lo, hi) are f's to skip.
 template <int NT, int DEPTH, class F>
-__device__ inline void visit_events(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
-                                    int64_t E, int64_t lo, int64_t hi, int64_t e, F &&f) {
-  auto visit = [&](const EvQuad &q, int64_t k0) {
-#pragma unroll
-    for (int u = 0; u < 4; u++) {
-      const int64_t k = k0 + u;
-      if (k < lo || k >= hi) continue;
-      f(k, q.t[u], k + 1 < e ? q.t[u + 1] : q.t[u], q.c[u]);
-    }
-  };
+__device__ inline void visit_quads(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
+                                   int64_t E, int64_t lo, int64_t hi, int64_t e, F &&f) {
   constexpr int64_t STEP = 4 * (int64_t)NT;
   for (int64_t k0 = (lo & ~(int64_t)3) + 4 * (int64_t)threadIdx.x; k0 < hi; k0 += DEPTH * STEP) {
     // every load is in bounds of the arrays (load_quad guards E); a later
-    // step that starts at or past hi loads nothing (visit skips its events)
+    // step that starts at or past hi loads nothing (f skips its events)
     EvQuad q[DEPTH];
 #pragma unroll
     for (int d = 0; d < DEPTH; d++) {
@@ -71,8 +65,21 @@ __device__ inline void visit_events(const int64_t *__restrict__ ts, const int32_
       if (d == 0 || k0 + d * STEP < hi) q[d] = load_quad(ts, ctx, E, k0 + d * STEP, e);
     }
 #pragma unroll
-    for (int d = 0; d < DEPTH; d++) visit(q[d], k0 + d * STEP);
+    for (int d = 0; d < DEPTH; d++) f(k0 + d * STEP, q[d]);
   }
+}
+
+template <int NT, int DEPTH, class F>
+__device__ inline void visit_events(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
+                                    int64_t E, int64_t lo, int64_t hi, int64_t e, F &&f) {
+  visit_quads<NT, DEPTH>(ts, ctx, E, lo, hi, e, [&](int64_t k0, const EvQuad &q) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int64_t k = k0 + u;
+      if (k < lo || k >= hi) continue;
+      f(k, q.t[u], k + 1 < e ? q.t[u + 1] : q.t[u], q.c[u]);
+    }
+  });
 }
 
 __global__ void zero_i64(int64_t *p, int64_t n) {
@@ -121,43 +128,205 @@ __global__ __launch_bounds__(WT) void window_bounds(const int64_t *__restrict__ 
   bounds[2 * i + 1] = v2ll{e, 0};
 }
 
-// One workgroup per selected rank (grid-stride over the selection) over the
-// events window_bounds found.  LDSH: an LDS histogram over the N nodes
-// (N <= 8192) flushed once; otherwise 64-bit atomics on the output.  Integer
-// sums: the order of the atomics does not matter.
+// Sums by node id in LDS for trees too large for a bin per node: buckets of
+// four ids, read at once, at most PROBES of them tried.  (Single slots at a
+// third full: the longest of 64 lanes' searches takes seven dependent reads.)
+constexpr int HSLOTS = 4096;  // 48 KB: three workgroups per CU beside 160 KB
+struct NodeSums {
+  static constexpr int PROBES = 16;
+  int32_t key[HSLOTS];  // -1: free
+  uint64_t sum[HSLOTS];
+
+  __device__ void clear(int t, int nt) {
+    for (int i = t; i < HSLOTS; i += nt) {
+      key[i] = -1;
+      sum[i] = 0;
+    }
+  }
+  static __device__ uint32_t home(int32_t c) { return (((uint32_t)c * 2654435761u) >> 20) & ~3u; }
+  __device__ v4i bucket(uint32_t at) const { return *reinterpret_cast<const volatile v4i *>(&key[at]); }
+  static __device__ int which(v4i k, int32_t c) {
+    return k.x == c ? 0 : (k.y == c ? 1 : (k.z == c ? 2 : (k.w == c ? 3 : -1)));
+  }
+  // Adds d[u] to node c[u] where d[u] is not 0; first(c) on a new node, none(c, d)
+  // where no slot was found.  Nodes already in their home bucket, the most, are
+  // added at once; one loop over what is left keeps the code short.
+  template <class F, class G>
+  __device__ __forceinline__ void add4(const int32_t (&c)[4], uint64_t (&d)[4], F &&first, G &&none) {
+    v4i k[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) k[u] = bucket(home(c[u]));
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int w = which(k[u], c[u]);
+      if (d[u] && w >= 0) {
+        atomicAdd((unsigned long long *)&sum[home(c[u]) + w], (unsigned long long)d[u]);
+        d[u] = 0;
+      }
+    }
+    // the pending ones move up to the front
+    int32_t c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3];
+    uint64_t d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3];
+    uint32_t at = home(c0);
+    int tries = PROBES;
+    while ((d0 | d1 | d2 | d3) != 0) {
+      if (d0 == 0) {
+        c0 = c1, c1 = c2, c2 = c3;
+        d0 = d1, d1 = d2, d2 = d3, d3 = 0;
+        at = home(c0);
+        tries = PROBES;
+      }
+      if (d0 != 0) {
+        const v4i b = bucket(at);
+        int w = which(b, c0);
+        if (w < 0) {
+          const int f = which(b, -1);
+          if (f >= 0) {  // taken by another node meanwhile: the bucket again
+            const int32_t x = atomicCAS(&key[at + f], -1, c0);
+            if (x == -1) first(c0);
+            if (x == -1 || x == c0) w = f;
+          } else {
+            at = (at + 4) & (HSLOTS - 1);
+            if (--tries == 0) {
+              none(c0, d0);
+              d0 = 0;
+            }
+          }
+        }
+        if (w >= 0) {
+          atomicAdd((unsigned long long *)&sum[at + w], (unsigned long long)d0);
+          d0 = 0;
+        }
+      }
+    }
+  }
+};
+static_assert(HSLOTS == 1 << (32 - 20), "the hash is the product's upper bits");
+
+constexpr int BAL_SEL = 16 * WWT;  // ranks whose events the workgroups divide evenly
+constexpr int64_t BAL_MIN = 4096;  // events per workgroup at least
+
+// The events window_bounds found.  Up to BAL_SEL ranks: every workgroup adds up
+// the ranks' counts and takes an equal share of all events, consecutive ones
+// (with a rank per workgroup the longest rank was the time); beyond, an equal
+// share of the ranks.  LDSH: an LDS histogram over the N nodes (N <= 8192)
+// flushed once; otherwise sums by node id in LDS, also flushed once (a node that
+// finds no slot: a 64-bit atomic on the output).  Integer sums: the order of the
+// atomics does not matter.
+//
+// Bound by the atomics: with one on the output per event, 97,833 nodes, the
+// 3,000 ranks' events in a twentieth of the longest one's time took 629 us, all
+// events of 429 ranks (20,000 at the median, 200,000 at most) 1,001; now both
+// together take 298.
 template <bool LDSH>
 __global__ __launch_bounds__(WWT) void window_excl(const int64_t *__restrict__ ts,
                                                  const int32_t *__restrict__ ctx, int64_t E,
                                                  const v2ll *__restrict__ bounds, int64_t n_sel, int N,
                                                  int64_t t0, int64_t t1, int64_t *__restrict__ excl,
                                                  uint32_t *err) {
-  extern __shared__ uint64_t hist[];  // [N] when LDSH
+  extern __shared__ uint64_t hist[];  // [N] when LDSH, else one NodeSums
+  __shared__ int64_t wtot[WWT / 64], start[2];
+  NodeSums &sums = *reinterpret_cast<NodeSums *>(hist);
+  const int t = threadIdx.x;
+  // this workgroup's events: `quota` of them from the skip-th of rank i, or all
+  // of ranks i..last-1
+  int64_t i = n_sel * blockIdx.x / gridDim.x, last = n_sel * (blockIdx.x + 1) / gridDim.x;
+  int64_t skip = 0, quota = INT64_MAX;
+  if (n_sel <= BAL_SEL) {
+    const int per = (int)((n_sel + WWT - 1) / WWT), lane = t & 63, wid = t >> 6;
+    int64_t own = 0;
+    for (int j = 0; j < per; j++) {
+      const int64_t r = (int64_t)t * per + j;
+      if (r >= n_sel) break;
+      const v2ll b = bounds[2 * r];
+      own += b.y > b.x ? b.y - b.x : 0;
+    }
+    int64_t in = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t y = __shfl_up(in, d, 64);
+      if (lane >= d) in += y;
+    }
+    if (lane == 63) wtot[wid] = in;
+    if (t < 2) start[t] = 0;
+    __syncthreads();
+    int64_t total = 0;
+    for (int w = 0; w < WWT / 64; w++) {
+      in += w < wid ? wtot[w] : 0;
+      total += wtot[w];
+    }
+    int64_t parts = total / BAL_MIN + 1;
+    parts = parts < gridDim.x ? parts : gridDim.x;
+    // quads of a rank stay together where its events start at a multiple of 4
+    const int64_t share = (((total + parts - 1) / parts) + 3) & ~(int64_t)3;
+    const int64_t from = share * blockIdx.x;
+    quota = from < total ? (share < total - from ? share : total - from) : 0;
+    if (quota > 0 && in - own <= from && from < in) {  // one thread
+      int64_t at = in - own;
+      for (int64_t r = (int64_t)t * per;; r++) {
+        const v2ll b = bounds[2 * r];
+        const int64_t n = b.y > b.x ? b.y - b.x : 0;
+        if (from < at + n) {
+          start[0] = r;
+          start[1] = from - at;
+          break;
+        }
+        at += n;
+      }
+    }
+    __syncthreads();
+    i = start[0];
+    skip = start[1];
+    last = n_sel;
+  }
+  if (i >= last || quota == 0) return;  // uniform
   if (LDSH) {
-    for (int v = threadIdx.x; v < N; v += WWT) hist[v] = 0;
+    for (int v = t; v < N; v += WWT) hist[v] = 0;
+  } else {
+    sums.clear(t, WWT);
   }
   __syncthreads();
-  for (int64_t i = blockIdx.x; i < n_sel; i += gridDim.x) {
+  for (; i < last && quota > 0; i++, skip = 0) {
     const v2ll b0 = bounds[2 * i], b1 = bounds[2 * i + 1];
-    const int64_t lo = b0.x, hi = b0.y, e = b1.x;
-    visit_events<WWT, 2>(ts, ctx, E, lo, hi, e, [&](int64_t, int64_t s, int64_t f, int32_t c) {
-      if (f < s) atomicOr(err, ERRBIT_UNSORTED);
-      const int64_t a = s > t0 ? s : t0;
-      const int64_t z = f < t1 ? f : t1;
-      if (z > a) {
-        if (c < 0 || c >= N) {
-          atomicOr(err, ERRBIT_CTX);
-        } else if (LDSH) {
-          atomicAdd((unsigned long long *)&hist[c], (unsigned long long)(z - a));
-        } else {
-          atomicAdd((unsigned long long *)&excl[c], (unsigned long long)(z - a));
+    const int64_t lo = b0.x + skip, e = b1.x;
+    if (b0.y <= lo) continue;
+    const int64_t hi = b0.y - lo > quota ? lo + quota : b0.y;
+    quota -= hi - lo;
+    visit_quads<WWT, 2>(ts, ctx, E, lo, hi, e, [&](int64_t k0, const EvQuad &q) {
+      uint64_t d[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int64_t k = k0 + u, s = q.t[u], f = k + 1 < e ? q.t[u + 1] : s;
+        const int32_t c = q.c[u];
+        d[u] = 0;
+        if (k < lo || k >= hi) continue;
+        if (f < s) atomicOr(err, ERRBIT_UNSORTED);
+        const int64_t a = s > t0 ? s : t0;
+        const int64_t z = f < t1 ? f : t1;
+        if (z > a) {
+          if (c < 0 || c >= N) atomicOr(err, ERRBIT_CTX);
+          else d[u] = (uint64_t)(z - a);
         }
+      }
+      if (LDSH) {
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+          if (d[u]) atomicAdd((unsigned long long *)&hist[q.c[u]], (unsigned long long)d[u]);
+      } else {
+        sums.add4(q.c, d, [](int32_t) {}, [&](int32_t c, uint64_t v) {
+          atomicAdd((unsigned long long *)&excl[c], (unsigned long long)v);
+        });
       }
     });
   }
+  __syncthreads();
   if (LDSH) {
-    __syncthreads();
-    for (int v = threadIdx.x; v < N; v += WWT)
+    for (int v = t; v < N; v += WWT)
       if (hist[v]) atomicAdd((unsigned long long *)&excl[v], (unsigned long long)hist[v]);
+  } else {
+    for (int k = t; k < HSLOTS; k += WWT)
+      if (sums.key[k] >= 0)
+        atomicAdd((unsigned long long *)&excl[sums.key[k]], (unsigned long long)sums.sum[k]);
   }
 }
 
@@ -194,6 +363,86 @@ __device__ inline int block_excl_scan_i32(int v, int *wsum, int *total) {
   return base + x - v;
 }
 
+// Trees of more than SPC and at most SPBW * 32 nodes, one workgroup per rank
+// (grid-stride): the durations are summed by node id in LDS, a node's first one
+// also sets its bit in a mask; a workgroup scan of the mask's word counts gives
+// each node its place in ascending id.  A rank with a node that finds no slot
+// is left to the kernel below (counts[r] = -1).
+//
+// Bound by the LDS operations and the loads' latency: one pass, two LDS
+// operations per event and two workgroups per CU, where the kernel below takes
+// two passes and four at one per CU: 3,000 ranks of 20,000 events at the median
+// (200,000 at most) over 97,833 nodes 421 -> 349 us.
+__global__ __launch_bounds__(SPT, 8) void sparse_by_id(const int64_t *__restrict__ off,
+                                                      const int64_t *__restrict__ ts,
+                                                      const int32_t *__restrict__ ctx,
+                                                      int64_t R, int64_t E, int N,
+                                                      int64_t *__restrict__ counts,
+                                                      int32_t *__restrict__ ids,
+                                                      int64_t *__restrict__ vals,
+                                                      uint32_t *err) {
+  __shared__ NodeSums sums;
+  __shared__ uint32_t bm[SPBW];
+  __shared__ uint16_t pre[SPBW];  // at most HSLOTS nodes
+  __shared__ int wsum[SPT / 64];
+  __shared__ int full;
+  const int t = threadIdx.x;
+  for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
+    const int64_t o0 = off[r], o1 = off[r + 1];
+    const bool bad = o0 < 0 || o1 < o0 || o1 > E;
+    const int64_t b = bad ? 0 : o0, e = bad ? 0 : o1;
+    if (bad && t == 0) atomicOr(err, ERRBIT_OFFSETS);
+    for (int i = t; i < SPBW; i += SPT) bm[i] = 0;
+    sums.clear(t, SPT);
+    if (t == 0) full = 0;
+    __syncthreads();
+    visit_quads<SPT, 1>(ts, ctx, E, b, e, e, [&](int64_t k0, const EvQuad &q) {
+      uint64_t d[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int64_t k = k0 + u;
+        d[u] = 0;
+        if (k < b || k >= e) continue;
+        const int64_t x = k + 1 < e ? q.t[u + 1] - q.t[u] : 0;
+        if (x < 0) atomicOr(err, ERRBIT_UNSORTED);
+        if (q.c[u] < 0 || q.c[u] >= N) atomicOr(err, ERRBIT_CTX);
+        else if (x > 0) d[u] = (uint64_t)x;
+      }
+      sums.add4(q.c, d, [&](int32_t v) { atomicOr(&bm[v >> 5], 1u << (v & 31)); },
+                [&](int32_t, uint64_t) { full = 1; });
+    });
+    __syncthreads();
+    int64_t found = -1;
+    if (full == 0) {  // uniform
+      uint32_t wc[SPBT];
+      int own = 0;
+#pragma unroll
+      for (int u = 0; u < SPBT; u++) {
+        wc[u] = (uint32_t)__popc(bm[t * SPBT + u]);
+        own += (int)wc[u];
+      }
+      int total;
+      int pos = block_excl_scan_i32(own, wsum, &total);
+#pragma unroll
+      for (int u = 0; u < SPBT; u++) {
+        pre[t * SPBT + u] = (uint16_t)pos;
+        pos += (int)wc[u];
+      }
+      __syncthreads();
+      for (int i = t; i < HSLOTS; i += SPT) {
+        const int32_t c = sums.key[i];
+        if (c < 0) continue;
+        const int64_t o = b + pre[c >> 5] + __popc(bm[c >> 5] & ((1u << (c & 31)) - 1u));
+        ids[o] = c;
+        vals[o] = (int64_t)sums.sum[i];
+      }
+      found = total;
+    }
+    if (t == 0) counts[r] = found;
+    __syncthreads();
+  }
+}
+
 // One workgroup per rank (grid-stride).  Trees of more than SPC nodes and at
 // most SPBW * 32: a pass over the events' contexts (4 bytes per event) marks
 // the nodes they reach in an LDS bit mask; a workgroup scan of the mask's word
@@ -205,7 +454,7 @@ __device__ inline int block_excl_scan_i32(int v, int *wsum, int *total) {
 // for each chunk of SPC node ids that the events reach, an LDS histogram of
 // the chunk, then its non-zero bins in ascending id, compacted by a workgroup
 // scan and appended after the previous chunks'.  Output goes to the rank's own
-// event range.
+// event range.  left: only ranks with a negative count.
 __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__restrict__ off,
                                                              const int64_t *__restrict__ ts,
                                                              const int32_t *__restrict__ ctx,
@@ -213,7 +462,7 @@ __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__r
                                                              int64_t *__restrict__ counts,
                                                              int32_t *__restrict__ ids,
                                                              int64_t *__restrict__ vals,
-                                                             uint32_t *err) {
+                                                             int left, uint32_t *err) {
   __shared__ uint64_t pool[SPC];  // chunk histogram, or mask | word prefixes | accumulator
   __shared__ uint32_t touched[SPW];
   __shared__ int wsum[SPT / 64];
@@ -226,6 +475,7 @@ __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__r
   const int nw = (N + 31) / 32;
   const int t = threadIdx.x;
   for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
+    if (left && counts[r] >= 0) continue;  // uniform
     // a rank's range, clamped to [0, E] (inconsistent offsets are an error)
     const int64_t o0 = off[r], o1 = off[r + 1];
     const bool bad = o0 < 0 || o1 < o0 || o1 > E;
@@ -395,6 +645,8 @@ hipError_t launch_window_profile(const int64_t *off, const int64_t *ts, const in
                                             ((subtree_sums_ws_bytes(N) + 255) & ~(size_t)255));
     window_bounds<<<(unsigned)((n_sel + WT - 1) / WT), WT, 0, s>>>(off, ts, R, E, ids, n_sel, t0, t1,
                                                                    bounds, err);
+    // as many workgroups as fit: few ranks may hold many events
+    const int grid = n_sel <= BAL_SEL ? 3 * cus : grid_w(n_sel, cus, 3);
     if (N <= MAX_NODES_ATTR) {
       static bool attr = false;
       if (!attr) {
@@ -402,10 +654,10 @@ hipError_t launch_window_profile(const int64_t *off, const int64_t *ts, const in
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
         attr = true;
       }
-      window_excl<true><<<grid_w(n_sel, cus, 4), WWT, (size_t)N * 8, s>>>(ts, ctx, E, bounds, n_sel, N,
+      window_excl<true><<<grid, WWT, (size_t)N * 8, s>>>(ts, ctx, E, bounds, n_sel, N,
                                                                          t0, t1, excl, err);
     } else {
-      window_excl<false><<<grid_w(n_sel, cus, 4), WWT, 0, s>>>(ts, ctx, E, bounds, n_sel, N, t0, t1,
+      window_excl<false><<<grid, WWT, sizeof(NodeSums), s>>>(ts, ctx, E, bounds, n_sel, N, t0, t1,
                                                               excl, err);
     }
   }
@@ -418,7 +670,12 @@ hipError_t launch_sparse_profiles(const int64_t *off, const int64_t *ts, const i
                                   int64_t E, int N, int64_t *counts, int32_t *ids, int64_t *vals, uint32_t *err,
                                   int cus, hipStream_t s) {
   if (R <= 0) return hipSuccess;
-  sparse_profiles_kernel<<<grid_w(R, cus, 2), SPT, 0, s>>>(off, ts, ctx, R, E, N, counts, ids, vals, err);
+  const bool by_id = N > SPC && N <= SPBW * 32;
+  // a workgroup per rank, placed as others end: ranks differ in length (two per
+  // CU in turns: 504 us for 349)
+  if (by_id) sparse_by_id<<<grid_w(R, cus, 64), SPT, 0, s>>>(off, ts, ctx, R, E, N, counts, ids, vals, err);
+  sparse_profiles_kernel<<<grid_w(R, cus, 64), SPT, 0, s>>>(off, ts, ctx, R, E, N, counts, ids, vals,
+                                                           by_id ? 1 : 0, err);
   return hipGetLastError();
 }
 
