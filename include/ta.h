@@ -228,7 +228,7 @@ ta_status ta_imbalance_noalloc(ta_handle h, const int64_t *tensor, int64_t n_ran
  * above, a 32-bit copy and a slot of 256 cells per column and chunk of 1,024
  * ranks for the bracket interiors (a quarter of the tensor), plus the column
  * samples and one gathered column per selection workgroup; for the plain
- * z-score a column-major copy of the tensor. */
+ * z-score four sums per column and chunk of ranks (at most 64 chunks). */
 enum { TA_SCAN_FULL = 0, TA_SCAN_TOTALS = 1 };
 enum { TA_SCORE_MAD = 0, TA_SCORE_Z = 1 };
 ta_status ta_outliers(ta_handle h, const int64_t *tensor, int64_t n_ranks, int32_t n_iters,

@@ -492,7 +492,7 @@ __global__ __launch_bounds__(512) void col_select_direct(const int64_t *__restri
 // after which the second gives the correctly rounded quotient (Markstein 1990,
 // "Computation of elementary functions on the IBM RISC System/6000 processor").
 // No step can underflow or overflow here: |a| is 0 or in [1, 2^96], b in
-// [1, 2^66].  Five operations instead of the division's full sequence.
+// [1, 2^96].  Five operations instead of the division's full sequence.
 __device__ __forceinline__ double div_by(double a, double b, double y) {
   double q = a * y;
   q = fma(fma(-b, q, a), y, q);
@@ -643,7 +643,76 @@ __global__ __launch_bounds__(256) void score_rank(const int64_t *__restrict__ T,
       if (r0 + q < R) m_t[(int64_t)tid * R + r0 + q] = ni[q] > 0 ? acc[q] / (double)ni[q] : 0.0;
 }
 
-// The same from the row-major tensor for many regions or ranks.  A lane owns a
+// m(r,g) with plain z scores, from the row-major tensor: a workgroup scores NR
+// ranks' rows, every cell by a thread of its own, into LDS, and a thread per
+// (rank, region) adds the scores in ascending iteration.  Regions beyond 256 by
+// blockIdx.y.  Bound by the row's and the moments' loads: a wave per 64 ranks of
+// one region over a column-major copy, one load at a time, took 3,001 ranks of
+// 217 x 37 cells 187 us and the copy and the moments from it 205; this takes 74
+// and the moments from the tensor 44.
+template <int NR>
+__global__ __launch_bounds__(256) void score_plain(const int64_t *__restrict__ T, int64_t R, int I, int G,
+                                                   const int32_t *__restrict__ it,
+                                                   const ColMom *__restrict__ cm, double *m_t) {
+  __shared__ double sc[SC_CELLS];
+  constexpr int CELLS = SC_CELLS / NR, U = CELLS / 256;
+  const int tid = (int)threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * NR, IG = (int64_t)I * G;
+  const int g0 = (int)blockIdx.y * 256, gc = G - g0 < 256 ? G - g0 : 256;
+  int ni[NR], nmax = 0;
+#pragma unroll
+  for (int q = 0; q < NR; q++) {
+    ni[q] = r0 + q < R ? rank_iters(it, r0 + q, I) : 0;
+    nmax = ni[q] > nmax ? ni[q] : nmax;
+  }
+  // this thread's sums: entries tid, tid + 256, ... of (rank, region)
+  int eq[NR], eg[NR], en[NR];
+  double acc[NR];
+#pragma unroll
+  for (int j = 0; j < NR; j++) {
+    const int e = tid + 256 * j;
+    eq[j] = e / gc;
+    eg[j] = e - eq[j] * gc;
+    acc[j] = 0.0;
+    en[j] = 0;
+#pragma unroll
+    for (int q = 0; q < NR; q++) en[j] = eq[j] == q ? ni[q] : en[j];
+  }
+  const int ic = CELLS / gc;  // iterations per turn
+  for (int i0 = 0; i0 < nmax; i0 += ic) {
+    const int in = nmax - i0 < ic ? nmax - i0 : ic, cells = in * gc;
+    __syncthreads();  // the previous scores are added
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int k = u * 256 + tid;
+      if (k < cells) {
+        const int64_t c = (int64_t)i0 * G + g0 + (gc == G ? k : (k / gc) * G + k % gc);
+        const ColMom z = cm[c];
+#pragma unroll
+        for (int q = 0; q < NR; q++) {
+          const int64_t x = r0 + q < R ? T[(r0 + q) * IG + c] : 0;
+          const i128 num = (i128)z.n * x - z.s1;
+          const int64_t lo = (int64_t)num;
+          sc[q * CELLS + k] = div_by(num == (i128)lo ? (double)lo : i128_to_f64(num), z.zd, z.zy);
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NR; j++) {
+      const int n = en[j] - i0 < in ? en[j] - i0 : in;
+      const double *s = sc + eq[j] * CELLS + eg[j];
+#pragma unroll 8
+      for (int i = 0; i < n; i++) acc[j] += s[i * gc];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NR; j++)
+    if (eq[j] < NR && r0 + eq[j] < R)
+      m_t[(int64_t)(g0 + eg[j]) * R + r0 + eq[j]] = en[j] > 0 ? acc[j] / (double)en[j] : 0.0;
+}
+
+// Robust scores from the row-major tensor for many regions or ranks.  A lane owns a
 // region of RPL consecutive ranks; with fewer than 64 regions a wave takes 64
 // >> lgp ranks' rows side by side.
 template <int RPL, int IU>
@@ -727,6 +796,18 @@ size_t col_scan_ws_bytes(int64_t R, int IG) {
   size_t used = 0;
   carve((void *)0x100, R, IG, &used);
   return used;
+}
+
+hipError_t launch_score_plain(const int64_t *T, int64_t R, int I, int G, const int32_t *it,
+                              const ColMom *cm, double *m_t, hipStream_t s) {
+  const unsigned gb = (unsigned)((G + 255) / 256);
+  // four ranks share a column's moments once they still fill the chip
+  if (R >= 2048)
+    hipLaunchKernelGGL(score_plain<4>, dim3((unsigned)((R + 3) / 4), gb), dim3(256), 0, s, T, R, I, G, it, cm,
+                       m_t);
+  else
+    hipLaunchKernelGGL(score_plain<1>, dim3((unsigned)R, gb), dim3(256), 0, s, T, R, I, G, it, cm, m_t);
+  return hipGetLastError();
 }
 
 hipError_t launch_score_tensor(const int64_t *T, int64_t R, int I, int G, const int32_t *it,

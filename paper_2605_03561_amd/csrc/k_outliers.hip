@@ -38,13 +38,11 @@ struct ColSel {
 };
 
 // ----------------------------------------------------------------------------
-// Column-major path for the plain z-score, and for the robust FULL scan with
-// more ranks than the row-major path takes.
+// Column-major path for the robust FULL scan with more ranks than the row-major
+// path takes.
 //   transpose_kernel  T[R][IG] -> Tt[IG][Rp] (Rp = R rounded up to 64) through
 //                     64 x 64 LDS tiles; a cell of an iteration the rank does
 //                     not have, and the padding, hold the sentinel INT64_MIN
-//   col_moments, score_cols  plain z: one workgroup per column for the moments,
-//                     then a wave = 64 consecutive ranks of one region
 //   col_select_bracket  robust: sampled brackets, two streaming passes over the
 //                     contiguous column, exact selection over the interior
 //                     (then score_tensor)
@@ -675,76 +673,32 @@ __global__ __launch_bounds__(CS, SEL_WGS_PER_CU) void col_select_bracket(const i
 }
 
 // ----------------------------------------------------------------------------
-// Plain moments per column (TA_SCORE_Z) over the column-major tensor:
-// n, sum, 128-bit sum of squares -> std (ddof 1).
+// Plain moments per column (TA_SCORE_Z) from the chunks' partial sums: std with
+// ddof 1.
 // ----------------------------------------------------------------------------
-struct ColMom {
-  int64_t *n, *s1;
-  double *sd;
-};
-
-__global__ __launch_bounds__(CS) void col_moments(const int64_t *__restrict__ Tt, int64_t R,
-                                                  ColMom out) {
-  __shared__ u128 q[CS];
-  __shared__ int64_t red[CS];
-  const int c = blockIdx.x, t = threadIdx.x;
-  const int64_t Rp = pad_ranks(R);
+__global__ __launch_bounds__(256) void plain_moments(ColPartials p, int IG, ColMom *out) {
+  const int c = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (c >= IG) return;
   int64_t n = 0, s1 = 0;
   u128 s2 = 0;
-  sweep(Tt + (int64_t)c * Rp, Rp, [&](int64_t x) {
-    if (x == SENT) return;
-    n++;
-    s1 += x;
-    s2 += (u128)((i128)x * x);
-  });
-  n = block_sum_i64<CS>(n, red);
-  s1 = block_sum_i64<CS>(s1, red);
-  q[t] = s2;
-  __syncthreads();
-  for (int st = CS / 2; st > 0; st >>= 1) {
-    if (t < st) q[t] += q[t + st];
-    __syncthreads();
+#pragma unroll 8
+  for (int k = 0; k < p.rc; k++) {
+    const int64_t j = (int64_t)k * IG + c;
+    n += p.n[j];
+    s1 += p.s1[j];
+    s2 += ((u128)p.hi[j] << 64) | p.lo[j];
   }
-  if (t == 0) {
-    double sd = 0.0;
-    if (n > 1)
-      sd = sqrt(i128_to_f64((i128)((u128)n * q[0]) - (i128)s1 * s1) / ((double)n * (double)(n - 1)));
-    out.n[c] = n;
-    out.s1[c] = s1;
-    out.sd[c] = sd;
+  double sd = 0.0;
+  if (n > 1)
+    sd = sqrt(i128_to_f64((i128)((u128)n * s2) - (i128)s1 * s1) / ((double)n * (double)(n - 1)));
+  ColMom m{0, 0, 1.0, 1.0};
+  if (sd > 0.0) {
+    m.n = n;
+    m.s1 = s1;
+    m.zd = (double)n * sd;
+    m.zy = 1.0 / m.zd;
   }
-}
-
-// m(r,g) = (1/n_r) sum_{i < n_r} z(r,i,g) (ascending i) from the column-major
-// tensor, written [G][R]; one wave = 64 consecutive ranks of region g, so the
-// column parameters are uniform across the wave.
-__global__ __launch_bounds__(256) void score_cols(const int64_t *__restrict__ Tt, int64_t R, int I,
-                                                  int G, const int32_t *it, ColMom cm,
-                                                  double *m_t) {
-  const int lane = threadIdx.x & 63;
-  const int64_t rblocks = (R + 63) / 64;
-  const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int g = (int)(wave / rblocks);
-  if (g >= G) return;
-  const int64_t Rp = pad_ranks(R);
-  const int64_t r = (wave % rblocks) * 64 + lane;
-  int ni = 0;
-  if (r < R) {
-    ni = it ? it[r] : I;
-    ni = ni > I ? I : (ni < 0 ? 0 : ni);
-  }
-  double acc = 0.0;
-  const int64_t *p = Tt + (int64_t)g * Rp + (r < R ? r : 0);
-  for (int i = 0; i < I; i++) {
-    const int c = i * G + g;
-    if (i < ni) {
-      const int64_t x = p[(int64_t)i * G * Rp];
-      const double sd = cm.sd[c];
-      const int64_t n = cm.n[c];
-      acc += sd > 0.0 ? i128_to_f64((i128)n * x - cm.s1[c]) / ((double)n * sd) : 0.0;
-    }
-  }
-  if (r < R) m_t[(int64_t)g * R + r] = ni > 0 ? acc / (double)ni : 0.0;
+  out[c] = m;
 }
 
 // ----------------------------------------------------------------------------
@@ -1419,19 +1373,13 @@ __global__ __launch_bounds__(256) void score_rows(const int64_t *__restrict__ T,
   }
 }
 
-// Rank totals S(r,g), transposed [G][R].
+// Rank totals S(r,g), transposed [G][R].  A thread per (rank, region) walked its
+// iterations one load at a time: 3,001 ranks of 217 x 37 cells 71 us, now 29.
+template <int TPR>
 __global__ __launch_bounds__(256) void rank_totals_t(const int64_t *__restrict__ T, int64_t R, int I,
                                                      int G, const int32_t *it, int64_t *S_t) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= R * G) return;
-  const int64_t r = p / G;
-  const int g = (int)(p % G);
-  int ni = it ? it[r] : I;
-  if (ni > I) ni = I;
-  const int64_t *row = T + r * (int64_t)I * G + g;
-  int64_t s = 0;
-  for (int i = 0; i < ni; i++) s += row[(int64_t)i * G];
-  S_t[(int64_t)g * R + r] = s;
+  rank_region_sums<TPR, false>(T, R, I, G, it,
+                               [&](int64_t r, int g, int64_t s, u128) { S_t[(int64_t)g * R + r] = s; });
 }
 
 // ----------------------------------------------------------------------------
@@ -2212,7 +2160,8 @@ struct OWs {
   ColSel cs;        // row-major path
   ColZ *cz;         // column-major robust scan: [IG]
   void *cols;       // columns in registers: col_scan_ws_bytes
-  ColMom cm;
+  ColMom *cm;
+  ColPartials zp;  // plain z without imbalance partials to share: n, s1, lo, hi
   double *m_t;      // [G][R] doubles (FULL) -- also reused as z_t
   int64_t *S_t;     // [G][R] (TOTALS)
   double *z_t;      // [G][R]
@@ -2229,6 +2178,9 @@ inline bool row_major_path(int64_t R, int mode, int kind) {
   return mode == TA_SCAN_FULL && kind == TA_SCORE_MAD && R > COL_REG_MAX &&
          transpose_groups_of(R) <= SEG_MAX;
 }
+
+// Chunks of ranks of the plain z-score's column sums: at least 64 ranks each.
+int plain_chunks(int64_t R) { return (int)std::min<int64_t>(64, (R + 63) / 64 + (R == 0)); }
 
 OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
   size_t off = 0;
@@ -2261,10 +2213,9 @@ OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
       w.cs.zd = (double *)take(IG * 8);
     } else if (reg_path(R, mode, kind)) {
       w.cols = take(col_scan_ws_bytes(R, (int)IG));
-    } else {
+    } else if (kind == TA_SCORE_MAD) {
       w.Tt = (int64_t *)take((size_t)pad_ranks(R) * IG * 8);
-      if (kind == TA_SCORE_MAD)
-        w.scr = (int64_t *)take((size_t)std::min<size_t>(IG, SEL_GRID_MAX) * sel_cap(R) * 8);
+      w.scr = (int64_t *)take((size_t)std::min<size_t>(IG, SEL_GRID_MAX) * sel_cap(R) * 8);
     }
     if (reg_path(R, mode, kind)) {
     } else if (kind == TA_SCORE_MAD && !row_major_path(R, mode, kind)) {
@@ -2275,9 +2226,12 @@ OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
       w.cs.sumdev = (int64_t *)take(IG * 8);
       w.cs.n = (int64_t *)take(IG * 8);
     } else {
-      w.cm.n = (int64_t *)take(IG * 8);
-      w.cm.s1 = (int64_t *)take(IG * 8);
-      w.cm.sd = (double *)take(IG * 8);
+      w.cm = (ColMom *)take(IG * sizeof(ColMom));
+      w.zp.rc = plain_chunks(R);
+      w.zp.n = (int64_t *)take(IG * w.zp.rc * 8);
+      w.zp.s1 = (int64_t *)take(IG * w.zp.rc * 8);
+      w.zp.lo = (uint64_t *)take(IG * w.zp.rc * 8);
+      w.zp.hi = (uint64_t *)take(IG * w.zp.rc * 8);
     }
     w.m_t = (double *)take((size_t)R * G * 8);
   } else {
@@ -2484,7 +2438,6 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
   if (used > ws_bytes) return hipErrorInvalidValue;
   const int IG = a.I * a.G;
   if ((IG + TT - 1) / TT > 65535) return hipErrorInvalidValue;
-  const unsigned nb = (unsigned)((a.R * a.G + 255) / 256);
   const bool mad = a.kind == TA_SCORE_MAD;
   if (a.R > 0) {
     if (row_major_path(a.R, a.mode, a.kind)) {
@@ -2509,7 +2462,7 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
       const bool reg = reg_path(a.R, a.mode, a.kind);
       if (reg && IG > 0) {
         e = launch_col_scan(a.T, a.R, a.I, a.G, a.it, a.stats, a.stats_ready, w.m_t, w.cols, cus, s);
-      } else if (IG > 0) {
+      } else if (IG > 0 && mad) {
         const dim3 tg((unsigned)transpose_groups_of(a.R), (IG + TT - 1) / TT);
         if (a.stats.rc > 0) {
           hipLaunchKernelGGL(transpose_kernel<true>, tg, dim3(256), 0, s, a.T, a.R, IG, a.G, a.it, w.Tt,
@@ -2519,19 +2472,19 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
           hipLaunchKernelGGL(transpose_kernel<false>, tg, dim3(256), 0, s, a.T, a.R, IG, a.G, a.it, w.Tt,
                              a.stats);
         }
-        if (mad) {
-          const int grid = std::min(IG, std::min(SEL_GRID_MAX, SEL_WGS_PER_CU * cus));
-          hipLaunchKernelGGL(col_select_bracket, dim3(grid), dim3(CS), 0, s, w.Tt, a.R, IG, w.scr,
-                             sel_cap(a.R), w.cz);
-        } else {
-          hipLaunchKernelGGL(col_moments, dim3(IG), dim3(CS), 0, s, w.Tt, a.R, w.cm);
-        }
+        const int grid = std::min(IG, std::min(SEL_GRID_MAX, SEL_WGS_PER_CU * cus));
+        hipLaunchKernelGGL(col_select_bracket, dim3(grid), dim3(CS), 0, s, w.Tt, a.R, IG, w.scr,
+                           sel_cap(a.R), w.cz);
+      } else if (IG > 0) {
+        const ColPartials &p = a.stats.rc > 0 ? a.stats : w.zp;
+        e = launch_col_partials(a.T, a.R, IG, a.G, a.it, p, s);
+        if (e == hipSuccess && a.stats.rc > 0 && a.stats_ready) e = hipEventRecord(a.stats_ready, s);
+        hipLaunchKernelGGL(plain_moments, dim3((IG + 255) / 256), dim3(256), 0, s, p, IG, w.cm);
       }
       if (e == hipSuccess && mad && !reg) e = launch_score_tensor(a.T, a.R, a.I, a.G, a.it, w.cz, w.m_t, cus, s);
       if (e != hipSuccess) return e;
-      const unsigned nw = (unsigned)((a.G * ((a.R + 63) / 64) + 3) / 4);
-      if (!mad)
-        hipLaunchKernelGGL(score_cols, dim3(nw), dim3(256), 0, s, w.Tt, a.R, a.I, a.G, a.it, w.cm, w.m_t);
+      if (!mad) e = launch_score_plain(a.T, a.R, a.I, a.G, a.it, w.cm, w.m_t, s);
+      if (e != hipSuccess) return e;
       if (mad)
         launch_sel_regions<true, true>((const void *)w.m_t, a.R, a.G, a.it, a.I, w.z_t, a.region_score,
                                        s);
@@ -2539,7 +2492,12 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
         launch_sel_regions<true, false>((const void *)w.m_t, a.R, a.G, a.it, a.I, w.z_t,
                                          a.region_score, s);
     } else {
-      hipLaunchKernelGGL(rank_totals_t, dim3(nb), dim3(256), 0, s, a.T, a.R, a.I, a.G, a.it, w.S_t);
+      if (rank_sums_by_wave(IG))
+        hipLaunchKernelGGL(rank_totals_t<64>, dim3((unsigned)((a.R + 3) / 4)), dim3(256), 0, s, a.T, a.R, a.I,
+                           a.G, a.it, w.S_t);
+      else
+        hipLaunchKernelGGL(rank_totals_t<256>, dim3((unsigned)a.R), dim3(256), 0, s, a.T, a.R, a.I, a.G, a.it,
+                           w.S_t);
       if (mad)
         launch_sel_regions<false, true>((const void *)w.S_t, a.R, a.G, a.it, a.I, w.z_t,
                                          a.region_score, s);
@@ -2557,6 +2515,7 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
 }
 
 int scan_stat_chunks(int64_t R, int32_t kind) {
+  if (kind != TA_SCORE_MAD) return plain_chunks(R);
   return reg_path(R, TA_SCAN_FULL, kind) ? col_stat_chunks(R) : transpose_groups_of(R);
 }
 

@@ -234,4 +234,59 @@ __device__ inline double xsum_block_result(int64_t *acc, uint32_t *nonfinite, do
   return r;
 }
 
+// Per-region totals (SQ: and 128-bit sums of squares) of ranks' rows [I][G] over
+// their valid iterations, f(r, g, sum, squares): TPR of a workgroup's 256 threads
+// per rank, thread t of them on region t mod G' (G' regions at a time) of
+// every (TPR / G')-th iteration, so a row is read in its order with eight loads
+// in flight; the phases are added in LDS (integers: any order).
+template <int TPR, bool SQ, class F>
+__device__ __forceinline__ void rank_region_sums(const int64_t *__restrict__ T, int64_t R, int I, int G,
+                                                 const int32_t *__restrict__ it, F &&f) {
+  constexpr int U = 8;
+  __shared__ int64_t ls[256];
+  __shared__ uint64_t lq[SQ ? 256 : 1][2];
+  const int t = (int)threadIdx.x % TPR, base = (int)threadIdx.x - t;
+  const int64_t r = (int64_t)blockIdx.x * (256 / TPR) + base / TPR;
+  int ni = 0;
+  if (r < R) {
+    ni = it ? it[r] : I;
+    ni = ni > I ? I : ni;
+  }
+  for (int g0 = 0; g0 < G; g0 += TPR) {
+    const int gc = G - g0 < TPR ? G - g0 : TPR, ph = TPR / gc;
+    const int p = t / gc, g = t - p * gc;
+    int64_t s = 0;
+    u128 q = 0;
+    if (p < ph) {
+      const int64_t *row = T + (r < R ? r : 0) * (int64_t)I * G + g0 + g;
+      for (int i = p; i < ni; i += U * ph) {
+        int64_t x[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) x[u] = i + u * ph < ni ? row[(int64_t)(i + u * ph) * G] : 0;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          s += x[u];
+          if (SQ) q += (u128)((i128)x[u] * x[u]);
+        }
+      }
+    }
+    ls[threadIdx.x] = s;
+    if (SQ) {
+      lq[threadIdx.x][0] = (uint64_t)q;
+      lq[threadIdx.x][1] = (uint64_t)(q >> 64);
+    }
+    __syncthreads();
+    if (t < gc && r < R) {
+      for (int k = 1; k < ph; k++) {
+        s += ls[base + k * gc + t];
+        if (SQ) q += ((u128)lq[base + k * gc + t][1] << 64) | lq[base + k * gc + t][0];
+      }
+      f(r, g0 + g, s, q);
+    }
+    __syncthreads();
+  }
+}
+// Threads per rank: a wave while a row is no more than some 16 loads of it.
+inline bool rank_sums_by_wave(int64_t IG) { return IG <= 1024; }
+
 }  // namespace ta

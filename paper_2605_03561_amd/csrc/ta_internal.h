@@ -109,9 +109,12 @@ struct ColPartials {
   uint64_t *lo, *hi;
   int rc;  // 0: none
 };
+// Writes them: R ranks in p.rc chunks (min and max where p.mn is set).
+hipError_t launch_col_partials(const int64_t *T, int64_t R, int IG, int G, const int32_t *it,
+                               const ColPartials &p, hipStream_t s);
 // rc_ext > 0: the partials ([rc_ext] chunks, in the workspace as
-// imbalance_partials() places them) were written by another kernel (the FULL
-// outlier scan's transpose), so the column pass over the tensor is skipped.
+// imbalance_partials() places them) were written by the FULL outlier scan's
+// first pass, so the column pass over the tensor is skipped.
 hipError_t launch_imbalance(const ImbArgs &a, void *ws, size_t ws_bytes, hipStream_t s,
                             int rc_ext = 0);
 size_t imbalance_ws_bytes(int64_t R, int32_t I, int32_t G, bool need_rank_stats, int rc_ext = 0);

@@ -45,4 +45,14 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
 hipError_t launch_score_tensor(const int64_t *T, int64_t R, int I, int G, const int32_t *it,
                                const ColZ *cz, double *m_t, int cus, hipStream_t s);
 
+// Plain z of a cell: (n x - s1) / zd (zy = 1 / zd); (0, 0, 1, 1) where the
+// column's deviation is 0.
+struct alignas(32) ColMom {
+  int64_t n, s1;
+  double zd, zy;
+};
+// m_t from the row-major tensor and the columns' moments.
+hipError_t launch_score_plain(const int64_t *T, int64_t R, int I, int G, const int32_t *it,
+                              const ColMom *cm, double *m_t, hipStream_t s);
+
 }  // namespace ta

@@ -129,3 +129,36 @@ def test_prescreen_selection_edges(ta, h, R):
         assert np.array_equal(top.cpu().numpy(), np.sort(np.lexsort((np.arange(R), -s))[:k]))
     np.testing.assert_allclose(s, ref, rtol=1e-4, atol=1e-5)
     h2.close()
+
+
+@pytest.mark.parametrize("R", [1, 2, 63, 65, 257, 2047, 2048, 2051])
+@pytest.mark.parametrize("I,G", [(3, 5), (27, 37), (5, 257), (1, 300), (2, 1), (17, 64), (9, 127)])
+def test_plain_scores_and_rank_sums(ta, h, oracle, R, I, G):
+    """Plain z-scores, totals and imbalance from a tensor, with rows above and
+    below 1,024 cells, regions below, at and above a wave and a workgroup, and
+    rank counts around the chunks of the column sums and the ranks per
+    workgroup.  Selections, sums and totals bit for bit; the plain z-score's
+    second stage sums R values in another order than the oracle: R * 2^-53
+    relative on the mean and deviation, and as much of the largest value on the
+    score."""
+    import torch
+    if R > 300 and I * G > 1000:
+        I = max(1, 1000 // G + 1)
+    T, it = tensor(np.random.default_rng([R, I, G]), R, I, G)
+    dT, dit = torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda()
+    o = h.outliers(dT, dit, kind=ta.SCORE_Z, region=True)
+    st, score, flag, nf, reg = oracle.outliers(T, it, kind=1)
+    assert st == 0
+    np.testing.assert_allclose(o["region_score"].cpu().numpy(), reg, rtol=1e-9, atol=1e-9)
+    np.testing.assert_allclose(o["rank_score"].cpu().numpy(), score, rtol=1e-9, atol=1e-9)
+    o = h.outliers(dT, dit, mode=ta.SCAN_TOTALS, region=True)
+    st, score, flag, nf, reg = oracle.outliers(T, it, mode=1)
+    assert st == 0
+    assert np.array_equal(o["region_score"].cpu().numpy(), reg)
+    assert np.array_equal(o["rank_flag"].cpu().numpy(), flag)
+    g = h.imbalance(dT, dit)
+    _, ref = oracle.imbalance(T, it)
+    for k in ("min", "max"):
+        assert np.array_equal(g[k].cpu().numpy(), ref[k])
+    for k in ("mean", "std", "max_minus_mean", "savings_per_iter", "cv_across", "cv_within"):
+        np.testing.assert_allclose(g[k].cpu().numpy(), ref[k], rtol=1e-9, atol=1e-9)
