@@ -162,3 +162,19 @@ def test_plain_scores_and_rank_sums(ta, h, oracle, R, I, G):
         assert np.array_equal(g[k].cpu().numpy(), ref[k])
     for k in ("mean", "std", "max_minus_mean", "savings_per_iter", "cv_across", "cv_within"):
         np.testing.assert_allclose(g[k].cpu().numpy(), ref[k], rtol=1e-9, atol=1e-9)
+
+
+@pytest.mark.parametrize("R", [0, 1, 255, 256, 257, 40000])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_flag_count(ta, h, R, mode):
+    """The number of flags from none to all but a few, on several calls and
+    without any rank."""
+    import torch
+    rng = np.random.default_rng([R, mode])
+    T, it = rng.integers(0, 10**6, (R, 3, 5)).astype(np.int64), np.full(R, 3, np.int32)
+    for tau in (1e9, 0.5, 0.0):
+        for kind in (ta.SCORE_MAD, ta.SCORE_Z):
+            o = h.outliers(torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda(), mode=mode, kind=kind, tau=tau)
+            flag = o["rank_flag"].cpu().numpy()
+            assert np.array_equal(flag, o["rank_score"].cpu().numpy() > tau)
+            assert int(o["n_flagged"].item()) == int(flag.sum())
