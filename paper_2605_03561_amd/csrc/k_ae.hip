@@ -662,7 +662,9 @@ __global__ __launch_bounds__(256) void ae_rows_fill(const int64_t *__restrict__ 
 // by hand of six instructions and four 2-byte LDS writes bound the kernel), and
 // row swaps turn them into the next layer's operand, so the hidden layers stay
 // in registers.  10,000 ranks x 300 rows (1.54 GB): 394 us with the rows on the
-// left, 327 us with the hidden layers through LDS, 306 us now.
+// left, 327 us with the hidden layers through LDS, 306 with them in registers,
+// 299 with the weights staged by 16-byte loads and a rank's length read during
+// the rank before.
 //   kind 0: score = max_g mean_i (y - x)^2     kind 1: max_g |mean_i (y - x)|
 // ---------------------------------------------------------------------------
 constexpr int SW = 8;                  // waves per workgroup
@@ -764,12 +766,22 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
   extern __shared__ __align__(16) unsigned char smem[];
   ScoreLds &L = *reinterpret_cast<ScoreLds *>(smem);
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  for (int k = tid; k < AE_NW; k += SW * 64) {
-    uint16_t v = wb[k];
-    if (k < AE_W2) L.W1[(k / AE_IN) * P_W1 + k % AE_IN] = v;
-    else if (k < AE_W3) L.W2[((k - AE_W2) / AE_H1) * P_W2 + (k - AE_W2) % AE_H1] = v;
-    else if (k < AE_W4) L.W3[((k - AE_W3) / AE_H2) * P_W3 + (k - AE_W3) % AE_H2] = v;
-    else L.W4[((k - AE_W4) / AE_H3) * P_W4 + (k - AE_W4) % AE_H3] = v;
+  {  // the weights, eight of a row at a time, all loads in flight
+    constexpr int PER = AE_NW / 8 / (SW * 64);
+    static_assert(AE_NW % (8 * SW * 64) == 0 && (P_W1 | P_W2 | P_W3 | P_W4) % 8 == 0, "whole 16-byte words");
+    uint4 v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; u++) v[u] = reinterpret_cast<const uint4 *>(wb)[u * (SW * 64) + tid];
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+      const int k = 8 * (u * (SW * 64) + tid);
+      uint16_t *d;
+      if (k < AE_W2) d = &L.W1[(k / AE_IN) * P_W1 + k % AE_IN];
+      else if (k < AE_W3) d = &L.W2[((k - AE_W2) / AE_H1) * P_W2 + (k - AE_W2) % AE_H1];
+      else if (k < AE_W4) d = &L.W3[((k - AE_W3) / AE_H2) * P_W3 + (k - AE_W3) % AE_H2];
+      else d = &L.W4[((k - AE_W4) / AE_H3) * P_W4 + (k - AE_W4) % AE_H3];
+      *reinterpret_cast<uint4 *>(d) = v[u];
+    }
   }
   for (int k = tid; k < AE_NP - AE_NW; k += SW * 64) L.b[k] = w[AE_NW + k];
   for (int k = tid; k < AE_IN; k += SW * 64) {
@@ -788,8 +800,14 @@ __global__ __launch_bounds__(SW * 64) void ae_score_kernel(const int64_t *__rest
   const float m0 = L.mu[lc], m1 = L.mu[lc + 1], s0 = L.isd[lc], s1 = L.isd[lc + 1];
   const float *bias = L.b;
   const int64_t nw = (int64_t)gridDim.x * SW;
+  int n_next = 0;
+  {
+    const int64_t r = (int64_t)blockIdx.x * SW + wid;
+    if (r < R) n_next = it ? it[r] : I;
+  }
   for (int64_t r = (int64_t)blockIdx.x * SW + wid; r < R; r += nw) {
-    int n = it ? it[r] : I;
+    int n = n_next;
+    if (r + nw < R) n_next = it ? it[r + nw] : I;  // arrives during this rank
     if (n > I) n = I;
     if (n < 0) n = 0;
     const int64_t *src = T + r * (int64_t)I * AE_IN;
@@ -1533,6 +1551,7 @@ hipError_t launch_ae_score(const AeState &s, const int64_t *T, int64_t R, int I,
     if (R <= 1024) go(region_robust_reg<1>);
     else if (R <= 4096) go(region_robust_reg<4>);
     else if (R <= 8192) go(region_robust_reg<8>);
+    else if (R <= 12288) go(region_robust_reg<12>);
     else if (R <= 16384) go(region_robust_reg<16>);
     else if (R <= 32768) go(region_robust_reg<32>);
     else go(region_robust_f32);
@@ -1550,6 +1569,7 @@ hipError_t launch_topk(const float *score, int64_t R, int64_t k, int32_t *idx, i
   };
   if (R <= 4096) go(topk_reg<4>);
   else if (R <= 8192) go(topk_reg<8>);
+  else if (R <= 12288) go(topk_reg<12>);
   else if (R <= 16384) go(topk_reg<16>);
   else if (R <= 32768) go(topk_reg<32>);
   else go(topk_kernel);
