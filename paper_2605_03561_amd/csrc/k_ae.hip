@@ -2,7 +2,7 @@
 //
 // Dense layers run on the matrix cores (v_mfma_f32_16x16x16_bf16): operands
 // are bfloat16 (round to nearest even), accumulation is FP32.  A workgroup
-// (4 waves) processes row tiles of 16 profile rows; every wave owns a fixed set
+// (8 waves) processes row tiles of 16 profile rows; every wave owns a fixed set
 // of 16x16 output tiles per layer, so weight-gradient tiles stay in the MFMA
 // accumulators across all row tiles of a training step and are written once
 // per workgroup.  Partials are summed in workgroup order by the Adam kernel, so

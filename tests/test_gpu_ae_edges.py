@@ -44,3 +44,13 @@ def test_gradient_tiles(n, origin):
         for a, b in zip(np.split(g, cuts), np.split(rg, cuts)):
             assert np.linalg.norm(a - b) <= 1e-2 * np.linalg.norm(b)
     h.close()
+
+
+@pytest.mark.parametrize("R", [12288, 12289])
+def test_prescreen_twelve_keys(R):
+    """The pre-screen's selections on both sides of twelve keys per lane."""
+    from paper_2605_03561_amd import ta
+    from test_gpu_select import test_prescreen_selection_edges as check
+    h = ta.Handle(0)
+    check(ta, h, R)
+    h.close()
