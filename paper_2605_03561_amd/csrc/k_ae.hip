@@ -88,10 +88,27 @@ __device__ inline int64_t perm_row(int64_t k, int64_t a, int64_t c, int64_t n, d
 // is the operand of the weight gradients, which contract over rows.  Neither is
 // transposed: 8-byte LDS words by lane, without conflicts.  With the weights
 // staged in LDS, four waves and operands gathered by 2-byte reads 25 us at 4,096
-// rows, now 18.4, of which the stores of the partials (25.5 MB, past the caches:
-// 2 us less than through them) are about 9 and the weights about 3.
+// rows, now 17, of which the stores of the partials (25.5 MB, past the caches: 2 us
+// less than through them) are about 7 and the weights about 3.
 // ---------------------------------------------------------------------------
 constexpr int AT = 512;  // threads per workgroup
+
+// The partials of the weights stand as the waves hold them, 16x16 tiles of 64
+// lanes x 4 entries: a store instruction writes 1 KB in order.  (At the weights'
+// own places it wrote sixteen pieces of 64 bytes: 18.4 us
+// per step of 4,096 rows, now 17.)
+constexpr int PT_W1 = 0, PT_W4 = 32, PT_W2 = 64, PT_W3 = 80;  // first tiles
+static_assert((PT_W3 + 16) * 256 == AE_NW, "the tiles cover the weights");
+
+// The parameter whose partials are at entry e of a workgroup's.
+__device__ inline int tiled_param(int e) {
+  if (e >= AE_NW) return e;
+  const int t = e >> 8, lane = (e >> 2) & 63, x = lane & 15, k = 4 * (lane >> 4) + (e & 3);
+  if (t < PT_W4) return AE_W1 + (16 * (t >> 2) + x) * AE_IN + 16 * (t & 3) + k;
+  if (t < PT_W2) return AE_W4 + (16 * (t & 3) + x) * AE_H3 + 16 * ((t - PT_W4) >> 2) + k;
+  if (t < PT_W3) return AE_W2 + (16 * (t & 1) + x) * AE_H1 + 16 * ((t - PT_W2) >> 1) + k;
+  return AE_W3 + (16 * ((t - PT_W3) >> 1) + x) * AE_H2 + 16 * (t & 1) + k;
+}
 
 __device__ __forceinline__ f4 mma(s4 a, s4 b, f4 acc) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
@@ -317,15 +334,18 @@ __global__ __launch_bounds__(AT) void ae_fwdbwd(const float *__restrict__ rows, 
 
   // Write this workgroup's partials (every element exactly once).
   float *P = part + (int64_t)blockIdx.x * AE_PS;
+  auto put = [&](int tile, f4 g) {
+    __builtin_nontemporal_store(g, reinterpret_cast<f4 *>(P + tile * 256 + lane * 4));
+  };
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    __builtin_nontemporal_store(gW1[i], reinterpret_cast<f4 *>(P + AE_W1 + c0 * AE_IN + 16 * i + q4));
-    __builtin_nontemporal_store(gW4[i], reinterpret_cast<f4 *>(P + AE_W4 + (16 * i + x) * AE_H3 + 16 * wid + q4));
+    put(PT_W1 + 4 * wid + i, gW1[i]);
+    put(PT_W4 + 4 * wid + i, gW4[i]);
   }
 #pragma unroll
   for (int i = 0; i < 2; i++) {
-    __builtin_nontemporal_store(gW2[i], reinterpret_cast<f4 *>(P + AE_W2 + (16 * i + x) * AE_H1 + 16 * wid + q4));
-    __builtin_nontemporal_store(gW3[i], reinterpret_cast<f4 *>(P + AE_W3 + c0 * AE_H2 + 16 * i + q4));
+    put(PT_W2 + 2 * wid + i, gW2[i]);
+    put(PT_W3 + 2 * wid + i, gW3[i]);
   }
   gb1 = col_sum(gb1);
   gb2 = col_sum(gb2);
@@ -443,14 +463,15 @@ constexpr int ADT = 512;        // threads
 constexpr int ADU = 16;         // loads per thread and turn
 constexpr int ADK = ADT / AP * ADU;  // partials per turn
 
+template <bool TILED>  // partials in tiles, as ae_fwdbwd writes them, or by parameter
 __global__ __launch_bounds__(ADT) void ae_adam(const float *__restrict__ part, int nwg, float *w, uint16_t *wb,
                                                float *m, float *v, float lr, float bc1, float bc2,
                                                int update, float *grad_out, float *loss_out,
                                                float loss_scale, float *epoch_loss, float lfrac) {
   __shared__ float pl[ADK][AP];
   const int e = (int)threadIdx.x % AP, k1 = (int)threadIdx.x / AP;
-  const int p = blockIdx.x * AP + e;
-  const bool mine = p <= AE_NP, sums = mine && threadIdx.x < AP;
+  const int at = blockIdx.x * AP + e, p = TILED ? tiled_param(at) : at;
+  const bool mine = at <= AE_NP, sums = mine && threadIdx.x < AP;
   float w0 = 0.f, m0 = 0.f, v0 = 0.f;
   if (sums && update && p < AE_NP) {
     w0 = w[p];
@@ -463,7 +484,7 @@ __global__ __launch_bounds__(ADT) void ae_adam(const float *__restrict__ part, i
 #pragma unroll
     for (int u = 0; u < ADU; u++) {
       const int k = kb + u * (ADT / AP) + k1;
-      x[u] = mine && k < nwg ? __builtin_nontemporal_load(&part[(int64_t)k * AE_PS + p]) : 0.f;
+      x[u] = mine && k < nwg ? __builtin_nontemporal_load(&part[(int64_t)k * AE_PS + at]) : 0.f;
     }
     if (kb) __syncthreads();
 #pragma unroll
@@ -1496,7 +1517,7 @@ hipError_t launch_ae_step(AeState &s, const float *rows, int64_t n, int64_t k0, 
     bc1 = (float)(1.0 - pow(0.9, (double)s.step));
     bc2 = (float)(1.0 - pow(0.999, (double)s.step));
   }
-  hipLaunchKernelGGL(ae_adam, dim3(AE_NP / AP + 1), dim3(ADT), 0, st, s.part, AE_WG, s.w, s.wb,
+  hipLaunchKernelGGL(ae_adam<true>, dim3(AE_NP / AP + 1), dim3(ADT), 0, st, s.part, AE_WG, s.w, s.wb,
                      s.m, s.v, lr, bc1, bc2, update ? 1 : 0, grad_out, loss_out ? loss_out : s.loss,
                      1.0f / (float)(bv * AE_IN), epoch_loss, lfrac);
   return hipGetLastError();
@@ -1508,7 +1529,7 @@ hipError_t launch_ae_grad_f32(AeState &s, const float *rows, int64_t n, float no
   const float scale = 2.0f / (float)(n * AE_IN);
   hipLaunchKernelGGL(ae_grad_f32_kernel, dim3(AE_WG), dim3(256), 0, st, rows, n, scale, noise_sd,
                      noise_key, s.w, s.part);
-  hipLaunchKernelGGL(ae_adam, dim3(AE_NP / AP + 1), dim3(ADT), 0, st, s.part, AE_WG, s.w, s.wb,
+  hipLaunchKernelGGL(ae_adam<false>, dim3(AE_NP / AP + 1), dim3(ADT), 0, st, s.part, AE_WG, s.w, s.wb,
                      s.m, s.v, 0.f, 1.f, 1.f, 0, grad_out, loss_out ? loss_out : s.loss,
                      1.0f / (float)(n * AE_IN), (float *)nullptr, 0.f);
   return hipGetLastError();
