@@ -181,6 +181,7 @@ __global__ __launch_bounds__(NT, EPT <= 4 ? 4 : 1) void seg_kernel(SegArgs a) {
   o += ((size_t)N * 4 + 15) & ~(size_t)15;
   int *wsum = reinterpret_cast<int *>(smem + o);                    // [2][NWAVE]
   int64_t *wsum64 = reinterpret_cast<int64_t *>(smem + o + 2 * NWAVE * sizeof(int));
+  int64_t *dropped = wsum64 + NWAVE;  // the rank's time in regions past the last stored iteration
   // Rank-end reductions alias the ring area (the ring is cleared after).
   int64_t *redS = ring;                                             // [NT]
   uint64_t *redQ = reinterpret_cast<uint64_t *>(ring + NT);         // [NT][2]
@@ -190,6 +191,7 @@ __global__ __launch_bounds__(NT, EPT <= 4 ? 4 : 1) void seg_kernel(SegArgs a) {
   if (ATTR)
     for (int v = tid; v <= N; v += NT) hist[v] = 0;
   for (size_t v = tid; v < ring_area / 8; v += NT) ring[v] = 0;
+  if (tid == 0) *dropped = 0;
   __syncthreads();
 
   // Region-row flush mapping: thread -> (row offset, region) with a fixed
@@ -382,7 +384,11 @@ __global__ __launch_bounds__(NT, EPT <= 4 ? 4 : 1) void seg_kernel(SegArgs a) {
         if (w_last >= I) {
 #pragma unroll
           for (int j = 0; j < EPT; j++)
-            if (itj[j] >= I && c0 + j >= b && c0 + j < e) errb |= ERRBIT_OVERFLOW;
+            if (itj[j] >= I && c0 + j >= b && c0 + j < e) {
+              errb |= ERRBIT_OVERFLOW;
+              if ((inf[j] & INFO_REGION_MASK) != 0 && d[j] != 0)
+                atomicAdd(reinterpret_cast<unsigned long long *>(dropped), (unsigned long long)d[j]);
+            }
         }
         int lo = it_first > 0 ? it_first : 0;
         while (true) {
@@ -473,8 +479,10 @@ __global__ __launch_bounds__(NT, EPT <= 4 ? 4 : 1) void seg_kernel(SegArgs a) {
         }
       }
       if (tid == 0) {
-        // the durations add up to the span: what is in no cell is outside
-        int64_t s = (e > b) ? T.ts[e - 1] - T.ts[b] : 0;
+        // the durations add up to the span: what is in no cell, nor was dropped
+        // with an iteration that the tensor does not hold, is outside
+        int64_t s = ((e > b) ? T.ts[e - 1] - T.ts[b] : 0) - *dropped;
+        *dropped = 0;
         for (int w = 0; w < NWAVE; w++) s -= wsum64[w];
         if (TA_OUT(outside)) TA_OUT(outside)[r] = s;
         if (TA_OUT(iters_found)) TA_OUT(iters_found)[r] = carry + 1;
@@ -525,7 +533,7 @@ size_t segment_lds_bytes(int N, int G, bool attr, bool seg, int *W, int *log2W) 
   size_t fixed = 0;
   if (attr) fixed += ((size_t)(N + 1) * 8 + 15) & ~(size_t)15;
   fixed += ((size_t)N * 4 + 15) & ~(size_t)15;
-  fixed += 2 * (NT_MAX / 64) * sizeof(int) + (NT_MAX / 64) * sizeof(int64_t);
+  fixed += 2 * (NT_MAX / 64) * sizeof(int) + (NT_MAX / 64 + 1) * sizeof(int64_t);
   int w = 2, lw = 1;
   if (seg) {
     // Largest power-of-two ring within 16 KiB, and within what leaves room for
