@@ -312,7 +312,11 @@ __global__ __launch_bounds__(NT, EPT <= 4 ? 4 : 1) void seg_kernel(SegArgs a) {
           inf[j] = info[c < last ? c : last];
         }
         if (neg < 0) errb |= ERRBIT_UNSORTED;
-        if (far >= (uint32_t)N) errb |= ERRBIT_CTX;
+        if (far >= (uint32_t)N) {  // such an event belongs to no node
+          errb |= ERRBIT_CTX;
+#pragma unroll
+          for (int j = 0; j < EPT; j++) inf[j] = (uint32_t)cv[j] < (uint32_t)N ? inf[j] : 0;
+        }
       } else {
 #pragma unroll
         for (int j = 0; j < EPT; j++) {

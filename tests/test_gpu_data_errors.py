@@ -55,3 +55,41 @@ def test_outside_when_iterations_overflow(oracle, every):
         assert ei.value.status == ta.ITER_OVERFLOW
     p.close()
     h.close()
+
+
+@pytest.mark.parametrize("bad", [60, 2**31 - 1, -1])
+def test_context_out_of_range(oracle, bad):
+    """A context outside [0, N), also in tiles that lie inside a rank, on both
+    sides of a boundary and as the last event of a tile: the event is in no
+    region and not in the marker's subtree, as if it were in the tree's root,
+    which is neither here."""
+    from paper_2605_03561_amd import ta
+    rng = np.random.default_rng([3, bad & 0xffff])
+    N, lens, every = 60, [5, 9000, 0, 1, 20000, 2048, 6145], 50
+    parent, marker, regions, off, ts, ctx = _traces(rng, N, 5, lens, every)
+    assert parent[0] == -1 and marker != 0 and 0 not in regions
+    at = rng.random(len(ctx)) < 0.02
+    at[off[1] + every // 2 - 1::every * 7] = True
+    at[off[1] + every // 2 + 1::every * 11] = True
+    at[4095] = at[8191] = at[8192] = True
+    fixed, ctx = np.where(at, 0, ctx).astype(np.int32), np.where(at, bad, ctx).astype(np.int32)
+    I = 500
+    st, T, it, outside, span = oracle.segment(off, ts, fixed, parent, marker, regions, I)
+    assert st == 0
+    st, ex, inc = oracle.attribute(off, ts, fixed, parent)
+    assert st == 0
+    h = ta.Handle(0)
+    h.set_tree(parent)
+    h.set_regions(marker, regions)
+    tr = ta.DeviceTraces(off, ts, ctx)
+    p = h.plan(tr, I, off, imbalance=False, outliers=False, autotune=0)
+    p.launch()
+    for o in (p.seg, h.attribute_segment(tr, I)):
+        for k, ref in (("tensor", T), ("iters_found", it), ("outside", outside), ("span", span),
+                       ("excl", ex), ("incl", inc)):
+            assert np.array_equal(o[k].cpu().numpy(), ref), k
+    with pytest.raises(ta.TAError) as ei:
+        h.sync_status()
+    assert ei.value.status == ta.CTX_RANGE
+    p.close()
+    h.close()
