@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256, 4) void col_copy(const int64_t *__restrict__ T
       const uint32_t w = (d >= HALF32 || d <= -HALF32) ? WIDE : (uint32_t)(d + HALF32);
       L.tile[(p2 + h) * LD + k0 + 8 * k] = in ? w : none<uint32_t>();
       if (STATS) {
-        far |= in && (w == WIDE || (uint32_t)((int32_t)d + (1 << 29)) > (1u << 30));
+        far |= in && (w == WIDE || (uint32_t)d + (1u << 29) > (1u << 30));
         const int32_t e = in ? (int32_t)d : 0;
         const uint32_t m = (uint32_t)(e < 0 ? -e : e);
         n += in ? 1u : 0u;
