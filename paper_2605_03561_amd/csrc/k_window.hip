@@ -134,7 +134,7 @@ __global__ __launch_bounds__(WT) void window_bounds(const int64_t *__restrict__ 
 constexpr int HSLOTS = 4096;  // 48 KB: three workgroups per CU beside 160 KB
 struct NodeSums {
   static constexpr int PROBES = 16;
-  int32_t key[HSLOTS];  // -1: free
+  alignas(16) int32_t key[HSLOTS];  // -1: free; buckets are read as 16-byte words
   uint64_t sum[HSLOTS];
 
   __device__ void clear(int t, int nt) {
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(WWT) void window_excl(const int64_t *__restrict__ t
                                                  const v2ll *__restrict__ bounds, int64_t n_sel, int N,
                                                  int64_t t0, int64_t t1, int64_t *__restrict__ excl,
                                                  uint32_t *err) {
-  extern __shared__ uint64_t hist[];  // [N] when LDSH, else one NodeSums
+  extern __shared__ __align__(16) uint64_t hist[];  // [N] when LDSH, else one NodeSums
   __shared__ int64_t wtot[WWT / 64], start[2];
   NodeSums &sums = *reinterpret_cast<NodeSums *>(hist);
   const int t = threadIdx.x;
