@@ -3,6 +3,7 @@
 // [t_k, t_{k+1}) (a rank's last event lasts 0) is clipped to [t0, t1) and added
 // to its context node; inclusive costs are subtree sums of the result.
 #include "ta_internal.h"
+#include "ta_select.h"
 
 namespace ta {
 namespace {
@@ -51,11 +52,12 @@ __device__ inline EvQuad load_quad(const int64_t *__restrict__ ts, const int32_t
 
 // The same, four events at a time: f(k0, quad of events k0..k0+3); those
 // outside [lo, hi) are f's to skip.
-template <int NT, int DEPTH, class F>
-__device__ inline void visit_quads(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
-                                   int64_t E, int64_t lo, int64_t hi, int64_t e, F &&f) {
-  constexpr int64_t STEP = 4 * (int64_t)NT;
-  for (int64_t k0 = (lo & ~(int64_t)3) + 4 * (int64_t)threadIdx.x; k0 < hi; k0 += DEPTH * STEP) {
+// Thread t of nt.
+template <int DEPTH, class F>
+__device__ __forceinline__ void visit_quads(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
+                                            int64_t E, int64_t lo, int64_t hi, int64_t e, int t, int nt, F &&f) {
+  const int64_t STEP = 4 * (int64_t)nt;
+  for (int64_t k0 = (lo & ~(int64_t)3) + 4 * (int64_t)t; k0 < hi; k0 += DEPTH * STEP) {
     // every load is in bounds of the arrays (load_quad guards E); a later
     // step that starts at or past hi loads nothing (f skips its events)
     EvQuad q[DEPTH];
@@ -69,10 +71,10 @@ __device__ inline void visit_quads(const int64_t *__restrict__ ts, const int32_t
   }
 }
 
-template <int NT, int DEPTH, class F>
-__device__ inline void visit_events(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
-                                    int64_t E, int64_t lo, int64_t hi, int64_t e, F &&f) {
-  visit_quads<NT, DEPTH>(ts, ctx, E, lo, hi, e, [&](int64_t k0, const EvQuad &q) {
+template <int DEPTH, class F>
+__device__ __forceinline__ void visit_events(const int64_t *__restrict__ ts, const int32_t *__restrict__ ctx,
+                                             int64_t E, int64_t lo, int64_t hi, int64_t e, int t, int nt, F &&f) {
+  visit_quads<DEPTH>(ts, ctx, E, lo, hi, e, t, nt, [&](int64_t k0, const EvQuad &q) {
 #pragma unroll
     for (int u = 0; u < 4; u++) {
       const int64_t k = k0 + u;
@@ -82,10 +84,16 @@ __device__ inline void visit_events(const int64_t *__restrict__ ts, const int32_
   });
 }
 
-__global__ void zero_i64(int64_t *p, int64_t n) {
+// What window_bounds adds up over the selected ranks' events in the window.
+struct WinCounts {
+  unsigned long long total, longest, ranks;  // ranks: that have any
+};
+
+__global__ void zero_i64(int64_t *p, int64_t n, WinCounts *wc) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0;
+  if (wc && blockIdx.x == 0 && threadIdx.x == 0) *wc = WinCounts{0, 0, 0};
 }
 
 // First index in [a, z) whose timestamp satisfies a monotone predicate (false
@@ -110,12 +118,14 @@ __global__ __launch_bounds__(WT) void window_bounds(const int64_t *__restrict__ 
                                                    const int64_t *__restrict__ ts, int64_t R, int64_t E,
                                                    const int32_t *__restrict__ ids, int64_t n_sel,
                                                    int64_t t0, int64_t t1, v2ll *__restrict__ bounds,
-                                                   uint32_t *err) {
+                                                   WinCounts *wc, uint32_t *err) {
+  __shared__ uint64_t sum[WT / 64], top[WT / 64];
+  __shared__ int some[WT / 64];
   const int64_t i = (int64_t)blockIdx.x * WT + threadIdx.x;
-  if (i >= n_sel) return;
-  const int64_t r = ids ? (int64_t)ids[i] : i;
+  const int64_t r = i >= n_sel ? 0 : (ids ? (int64_t)ids[i] : i);
   int64_t lo = 0, hi = 0, e = 0;
-  if (r < 0 || r >= R || off[r] < 0 || off[r + 1] < off[r] || off[r + 1] > E) {
+  if (i >= n_sel) {
+  } else if (r < 0 || r >= R || off[r] < 0 || off[r + 1] < off[r] || off[r + 1] > E) {
     atomicOr(err, ERRBIT_OFFSETS);
   } else {
     const int64_t b = off[r];
@@ -124,8 +134,32 @@ __global__ __launch_bounds__(WT) void window_bounds(const int64_t *__restrict__ 
     lo = a > b ? a - 1 : b;
     hi = first_true(ts, b, e, [&](int64_t v) { return v >= t1; });
   }
-  bounds[2 * i] = v2ll{lo, hi};
-  bounds[2 * i + 1] = v2ll{e, 0};
+  if (i < n_sel) {
+    bounds[2 * i] = v2ll{lo, hi};
+    bounds[2 * i + 1] = v2ll{e, 0};
+  }
+  if (!wc) return;
+  const uint64_t own = hi > lo ? (uint64_t)(hi - lo) : 0;
+  uint64_t n = wave_sum(own), m = wave_max(own);
+  int have = (int)__popcll(__ballot(own > 0));
+  if ((threadIdx.x & 63) == 0) {
+    sum[threadIdx.x >> 6] = n;
+    top[threadIdx.x >> 6] = m;
+    some[threadIdx.x >> 6] = have;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < WT / 64; w++) {
+      n += sum[w];
+      m = top[w] > m ? top[w] : m;
+      have += some[w];
+    }
+    if (n) {
+      atomicAdd(&wc->total, (unsigned long long)n);
+      atomicMax(&wc->longest, (unsigned long long)m);
+      atomicAdd(&wc->ranks, (unsigned long long)have);
+    }
+  }
 }
 
 // Sums by node id in LDS for trees too large for a bin per node: buckets of
@@ -152,7 +186,7 @@ struct NodeSums {
   // where no slot was found.  Nodes already in their home bucket, the most, are
   // added at once; one loop over what is left keeps the code short.
   template <class F, class G>
-  __device__ __forceinline__ void add4(const int32_t (&c)[4], uint64_t (&d)[4], F &&first, G &&none) {
+  __device__ __forceinline__ void add4(const int32_t (&c)[4], uint64_t (&d)[4], int probes, F &&first, G &&none) {
     v4i k[4];
 #pragma unroll
     for (int u = 0; u < 4; u++) k[u] = bucket(home(c[u]));
@@ -168,13 +202,13 @@ struct NodeSums {
     int32_t c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3];
     uint64_t d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3];
     uint32_t at = home(c0);
-    int tries = PROBES;
+    int tries = probes;
     while ((d0 | d1 | d2 | d3) != 0) {
       if (d0 == 0) {
         c0 = c1, c1 = c2, c2 = c3;
         d0 = d1, d1 = d2, d2 = d3, d3 = 0;
         at = home(c0);
-        tries = PROBES;
+        tries = probes;
       }
       if (d0 != 0) {
         const v4i b = bucket(at);
@@ -203,16 +237,40 @@ struct NodeSums {
 };
 static_assert(HSLOTS == 1 << (32 - 20), "the hash is the product's upper bits");
 
-constexpr int BAL_SEL = 16 * WWT;  // ranks whose events the workgroups divide evenly
-constexpr int64_t BAL_MIN = 4096;  // events per workgroup at least
+// How the events of a window are divided over the workgroups and added up;
+// `total` and `longest` (window_bounds) count the selected ranks' events in it
+// (not for traces of fewer than COUNT_MIN events: a workgroup per rank, atomics).
+//   table   trees above 8,192 nodes, sums by node id in LDS: from 2,048 events per
+//           rank and 524,288 in all.  Below, a 64-bit atomic on the output per
+//           event costs less than clearing, searching and flushing the table
+//           (97,833 nodes; atomics, table: 200 ranks of 2,400 events 49, 64 us; of
+//           4,800 72, 58; 2,000 ranks of 1,200 136, 139; of 2,400 239, 186).
+//   split   an equal share of events, consecutive ones, per workgroup: with the
+//           table (neighbouring ranks share nodes), and when the longest rank
+//           is more than twice an equal share (3,000 ranks, lognormal lengths, over
+//           5,000 nodes: by rank 431 us, split 267; 200 ranks of 9,600 events
+//           alike: 38 and 46).  A rank counts as RANK_W events more, which is what a
+//           workgroup takes to go on to the next one.  Up to BAL_SEL ranks: each
+//           workgroup adds up the ranks' counts.
+//   by wave below 512 events per rank, a wave takes a rank: most windows are short
+//           (8,192 ranks with two events each split into equal shares: 3,821 us, as one
+//           workgroup went from rank to rank).
+// The same value in every lane, to a scalar register.
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  return ((int64_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
 
-// The events window_bounds found.  Up to BAL_SEL ranks: every workgroup adds up
-// the ranks' counts and takes an equal share of all events, consecutive ones
-// (with a rank per workgroup the longest rank was the time); beyond, an equal
-// share of the ranks.  LDSH: an LDS histogram over the N nodes (N <= 8192)
-// flushed once; otherwise sums by node id in LDS, also flushed once (a node that
-// finds no slot: a 64-bit atomic on the output).  Integer sums: the order of the
-// atomics does not matter.
+constexpr int BAL_SEL = 16 * WWT;
+constexpr int RANK_W = 1024;
+constexpr int64_t TABLE_MEAN = 2048, TABLE_MIN = 1 << 19, WAVE_MEAN = 512, COUNT_MIN = 1 << 16;
+
+// The events window_bounds found.  LDSH: an LDS histogram over the N nodes
+// (N <= 8192) flushed once; otherwise sums by node id in LDS (the table), also
+// flushed once (a node that finds no slot: a 64-bit atomic on the output; after
+// the first one a node is looked for in its home bucket alone), or 64-bit
+// atomics on the output.  Integer sums: the order of the atomics does not matter.
+// `fit`: workgroups with a table that fit on the chip.
 //
 // Bound by the atomics: with one on the output per event, 97,833 nodes, the
 // 3,000 ranks' events in a twentieth of the longest one's time took 629 us, all
@@ -222,24 +280,39 @@ template <bool LDSH>
 __global__ __launch_bounds__(WWT) void window_excl(const int64_t *__restrict__ ts,
                                                  const int32_t *__restrict__ ctx, int64_t E,
                                                  const v2ll *__restrict__ bounds, int64_t n_sel, int N,
-                                                 int64_t t0, int64_t t1, int64_t *__restrict__ excl,
-                                                 uint32_t *err) {
+                                                 int64_t t0, int64_t t1, const WinCounts *__restrict__ wc,
+                                                 int fit, int64_t *__restrict__ excl, uint32_t *err) {
   extern __shared__ __align__(16) uint64_t hist[];  // [N] when LDSH, else one NodeSums
-  __shared__ int64_t wtot[WWT / 64], start[2];
+  __shared__ int64_t wtot[WWT / 64], cut[4];
+  __shared__ int full;  // a node found no slot
   NodeSums &sums = *reinterpret_cast<NodeSums *>(hist);
   const int t = threadIdx.x;
-  // this workgroup's events: `quota` of them from the skip-th of rank i, or all
-  // of ranks i..last-1
-  int64_t i = n_sel * blockIdx.x / gridDim.x, last = n_sel * (blockIdx.x + 1) / gridDim.x;
-  int64_t skip = 0, quota = INT64_MAX;
-  if (n_sel <= BAL_SEL) {
+  // uniform over the grid
+  constexpr int64_t MIN_SHARE = LDSH ? 32768 : 4096;  // a histogram's flush costs more
+  const WinCounts n = wc ? *wc : WinCounts{0, 0, 0};
+  const int64_t total = (int64_t)n.total, longest = (int64_t)n.longest, have = (int64_t)n.ranks;
+  const bool table = !LDSH && total >= TABLE_MIN && total >= have * TABLE_MEAN;
+  const int64_t wgs = table && fit < (int)gridDim.x ? fit : gridDim.x;
+  const bool split = n_sel <= BAL_SEL && (table || (longest > 2 * MIN_SHARE && longest * wgs > 2 * total));
+  const bool by_wave = !table && !split && total < have * WAVE_MEAN;
+  // this workgroup's ranks i, i + next, ... below `last`; split: of rank i from its
+  // event cut[1] on, of rank last - 1 up to its event cut[3]
+  int64_t i = blockIdx.x, last = n_sel, next = gridDim.x;
+  if (split) {
+    const int64_t all = total + n_sel * RANK_W;
+    int64_t parts = all / MIN_SHARE + 1;
+    parts = parts < wgs ? parts : wgs;
+    // quads of a rank stay together where its events start at a multiple of 4
+    const int64_t share = (((all + parts - 1) / parts) + 3) & ~(int64_t)3;
+    const int64_t from = share * blockIdx.x, to = from + share < all ? from + share : all;
+    if (from >= all) return;
     const int per = (int)((n_sel + WWT - 1) / WWT), lane = t & 63, wid = t >> 6;
     int64_t own = 0;
     for (int j = 0; j < per; j++) {
       const int64_t r = (int64_t)t * per + j;
       if (r >= n_sel) break;
       const v2ll b = bounds[2 * r];
-      own += b.y > b.x ? b.y - b.x : 0;
+      own += RANK_W + (b.y > b.x ? b.y - b.x : 0);
     }
     int64_t in = own;
 #pragma unroll
@@ -248,77 +321,96 @@ __global__ __launch_bounds__(WWT) void window_excl(const int64_t *__restrict__ t
       if (lane >= d) in += y;
     }
     if (lane == 63) wtot[wid] = in;
-    if (t < 2) start[t] = 0;
     __syncthreads();
-    int64_t total = 0;
-    for (int w = 0; w < WWT / 64; w++) {
-      in += w < wid ? wtot[w] : 0;
-      total += wtot[w];
-    }
-    int64_t parts = total / BAL_MIN + 1;
-    parts = parts < gridDim.x ? parts : gridDim.x;
-    // quads of a rank stay together where its events start at a multiple of 4
-    const int64_t share = (((total + parts - 1) / parts) + 3) & ~(int64_t)3;
-    const int64_t from = share * blockIdx.x;
-    quota = from < total ? (share < total - from ? share : total - from) : 0;
-    if (quota > 0 && in - own <= from && from < in) {  // one thread
+    for (int w = 0; w < WWT / 64; w++) in += w < wid ? wtot[w] : 0;
+    // the ranks that hold places `from` and `to - 1`: one thread each
+    auto find = [&](int64_t x, int64_t *c) {
+      if (in - own > x || x >= in) return;
       int64_t at = in - own;
       for (int64_t r = (int64_t)t * per;; r++) {
         const v2ll b = bounds[2 * r];
-        const int64_t n = b.y > b.x ? b.y - b.x : 0;
-        if (from < at + n) {
-          start[0] = r;
-          start[1] = from - at;
+        const int64_t n = RANK_W + (b.y > b.x ? b.y - b.x : 0);
+        if (x < at + n) {
+          c[0] = r;
+          c[1] = x - at;
           break;
         }
         at += n;
       }
-    }
+    };
+    find(from, cut);
+    find(to - 1, cut + 2);
     __syncthreads();
-    i = start[0];
-    skip = start[1];
-    last = n_sel;
+    i = uniform(cut[0]);
+    last = uniform(cut[2]) + 1;
+    next = 1;
+  } else if (table) {  // many ranks: neighbouring ones
+    if ((int64_t)blockIdx.x >= wgs) return;
+    i = n_sel * blockIdx.x / wgs;
+    last = n_sel * (blockIdx.x + 1) / wgs;
+    next = 1;
+  } else if (by_wave) {
+    if (i * (WWT / 64) >= n_sel) return;
+    i = i * (WWT / 64) + __builtin_amdgcn_readfirstlane(t >> 6);
+    next *= WWT / 64;
   }
-  if (i >= last || quota == 0) return;  // uniform
+  if (!by_wave && i >= last) return;  // uniform
   if (LDSH) {
     for (int v = t; v < N; v += WWT) hist[v] = 0;
-  } else {
+  } else if (table) {
     sums.clear(t, WWT);
+    if (t == 0) full = 0;
   }
-  __syncthreads();
-  for (; i < last && quota > 0; i++, skip = 0) {
-    const v2ll b0 = bounds[2 * i], b1 = bounds[2 * i + 1];
-    const int64_t lo = b0.x + skip, e = b1.x;
-    if (b0.y <= lo) continue;
-    const int64_t hi = b0.y - lo > quota ? lo + quota : b0.y;
-    quota -= hi - lo;
-    visit_quads<WWT, 2>(ts, ctx, E, lo, hi, e, [&](int64_t k0, const EvQuad &q) {
-      uint64_t d[4];
+  if (LDSH || table) __syncthreads();
+  // visit(lo, hi, e) for the events of each rank
+  auto ranks = [&](auto &&visit) {
+    for (; i < last; i += next) {
+      const v2ll b0 = bounds[2 * i], b1 = bounds[2 * i + 1];
+      int64_t lo = b0.x, hi = b0.y;
+      if (split) {
+        if (i == uniform(cut[0])) lo += uniform(cut[1]);
+        const int64_t end = b0.x + uniform(cut[3]) + 1;
+        if (i == last - 1 && hi > end) hi = end;
+      }
+      visit(lo, hi, b1.x);
+    }
+  };
+  auto part = [&](int64_t s, int64_t f, int32_t c) -> uint64_t {  // of an event, in the window
+    if (f < s) atomicOr(err, ERRBIT_UNSORTED);
+    const int64_t a = s > t0 ? s : t0;
+    const int64_t z = f < t1 ? f : t1;
+    if (z <= a) return 0;
+    if (c >= 0 && c < N) return (uint64_t)(z - a);
+    atomicOr(err, ERRBIT_CTX);
+    return 0;
+  };
+  if (table) {
+    ranks([&](int64_t lo, int64_t hi, int64_t e) {
+      visit_quads<2>(ts, ctx, E, lo, hi, e, t, WWT, [&](int64_t k0, const EvQuad &q) {
+        uint64_t d[4];
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const int64_t k = k0 + u, s = q.t[u], f = k + 1 < e ? q.t[u + 1] : s;
-        const int32_t c = q.c[u];
-        d[u] = 0;
-        if (k < lo || k >= hi) continue;
-        if (f < s) atomicOr(err, ERRBIT_UNSORTED);
-        const int64_t a = s > t0 ? s : t0;
-        const int64_t z = f < t1 ? f : t1;
-        if (z > a) {
-          if (c < 0 || c >= N) atomicOr(err, ERRBIT_CTX);
-          else d[u] = (uint64_t)(z - a);
+        for (int u = 0; u < 4; u++) {
+          const int64_t k = k0 + u;
+          d[u] = k >= lo && k < hi ? part(q.t[u], k + 1 < e ? q.t[u + 1] : q.t[u], q.c[u]) : 0;
         }
-      }
-      if (LDSH) {
-#pragma unroll
-        for (int u = 0; u < 4; u++)
-          if (d[u]) atomicAdd((unsigned long long *)&hist[q.c[u]], (unsigned long long)d[u]);
-      } else {
-        sums.add4(q.c, d, [](int32_t) {}, [&](int32_t c, uint64_t v) {
-          atomicAdd((unsigned long long *)&excl[c], (unsigned long long)v);
-        });
-      }
+        sums.add4(q.c, d, *(volatile int *)&full ? 1 : NodeSums::PROBES, [](int32_t) {},
+                  [&](int32_t c, uint64_t v) {
+                    full = 1;
+                    atomicAdd((unsigned long long *)&excl[c], (unsigned long long)v);
+                  });
+      });
     });
+  } else {
+    auto add = [&](int64_t, int64_t s, int64_t f, int32_t c) {
+      const uint64_t d = part(s, f, c);
+      if (d) atomicAdd((unsigned long long *)(LDSH ? &hist[c] : (uint64_t *)&excl[c]), (unsigned long long)d);
+    };
+    if (by_wave)
+      ranks([&](int64_t lo, int64_t hi, int64_t e) { visit_events<1>(ts, ctx, E, lo, hi, e, t & 63, 64, add); });
+    else
+      ranks([&](int64_t lo, int64_t hi, int64_t e) { visit_events<2>(ts, ctx, E, lo, hi, e, t, WWT, add); });
   }
+  if (!LDSH && !table) return;
   __syncthreads();
   if (LDSH) {
     for (int v = t; v < N; v += WWT)
@@ -396,7 +488,7 @@ __global__ __launch_bounds__(SPT, 8) void sparse_by_id(const int64_t *__restrict
     sums.clear(t, SPT);
     if (t == 0) full = 0;
     __syncthreads();
-    visit_quads<SPT, 1>(ts, ctx, E, b, e, e, [&](int64_t k0, const EvQuad &q) {
+    visit_quads<1>(ts, ctx, E, b, e, e, t, SPT, [&](int64_t k0, const EvQuad &q) {
       uint64_t d[4];
 #pragma unroll
       for (int u = 0; u < 4; u++) {
@@ -408,7 +500,7 @@ __global__ __launch_bounds__(SPT, 8) void sparse_by_id(const int64_t *__restrict
         if (q.c[u] < 0 || q.c[u] >= N) atomicOr(err, ERRBIT_CTX);
         else if (x > 0) d[u] = (uint64_t)x;
       }
-      sums.add4(q.c, d, [&](int32_t v) { atomicOr(&bm[v >> 5], 1u << (v & 31)); },
+      sums.add4(q.c, d, NodeSums::PROBES, [&](int32_t v) { atomicOr(&bm[v >> 5], 1u << (v & 31)); },
                 [&](int32_t, uint64_t) { full = 1; });
     });
     __syncthreads();
@@ -529,7 +621,7 @@ __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__r
       if (total <= SPACC) {  // uniform
         for (int i = t; i < total; i += SPT) acc[i] = 0;
         __syncthreads();
-        visit_events<SPT, 1>(ts, ctx, E, b, e, e, [&](int64_t, int64_t s, int64_t f, int32_t c) {
+        visit_events<1>(ts, ctx, E, b, e, e, t, SPT, [&](int64_t, int64_t s, int64_t f, int32_t c) {
           const int64_t d = f - s;
           if (d < 0) atomicOr(err, ERRBIT_UNSORTED);
           if (c >= 0 && c < N && d > 0) {
@@ -588,7 +680,7 @@ __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__r
         const int lo = ch * SPC;
         for (int i = t; i < SPC; i += SPT) hist[i] = 0;
         __syncthreads();
-        visit_events<SPT, 1>(ts, ctx, E, b, e, e, [&](int64_t, int64_t s, int64_t f, int32_t c) {
+        visit_events<1>(ts, ctx, E, b, e, e, t, SPT, [&](int64_t, int64_t s, int64_t f, int32_t c) {
           const int64_t d = f - s;
           if (d < 0) atomicOr(err, ERRBIT_UNSORTED);
           if (c < 0 || c >= N) {
@@ -630,23 +722,26 @@ int grid_w(int64_t n, int cus, int per_cu) {
 
 }  // namespace
 
-// The subtree-sum workspace, then 32 bytes of event bounds per selected rank.
+// The subtree-sum workspace, then the window's counts and 32 bytes of event
+// bounds per selected rank.
 size_t window_ws_bytes(int N, int64_t n_sel) {
-  return ((subtree_sums_ws_bytes(N) + 255) & ~(size_t)255) + (size_t)(n_sel > 0 ? n_sel : 0) * 32;
+  return ((subtree_sums_ws_bytes(N) + 255) & ~(size_t)255) + 32 + (size_t)(n_sel > 0 ? n_sel : 0) * 32;
 }
 
 hipError_t launch_window_profile(const int64_t *off, const int64_t *ts, const int32_t *ctx, int64_t R,
                                  int64_t E, const int32_t *ids, int64_t n_sel, int N, const int2 *tin_tout,
                                  int64_t t0, int64_t t1, int64_t *excl, int64_t *incl, void *ws,
                                  uint32_t *err, int cus, hipStream_t s) {
-  zero_i64<<<grid_w((N + WT - 1) / WT, cus, 4), WT, 0, s>>>(excl, N);
+  WinCounts *wc = reinterpret_cast<WinCounts *>(static_cast<char *>(ws) +
+                                                ((subtree_sums_ws_bytes(N) + 255) & ~(size_t)255));
+  v2ll *bounds = reinterpret_cast<v2ll *>(reinterpret_cast<char *>(wc) + 32);
+  if (E < COUNT_MIN) wc = nullptr;
+  zero_i64<<<grid_w((N + WT - 1) / WT, cus, 4), WT, 0, s>>>(excl, N, n_sel > 0 ? wc : nullptr);
   if (n_sel > 0) {
-    v2ll *bounds = reinterpret_cast<v2ll *>(static_cast<char *>(ws) +
-                                            ((subtree_sums_ws_bytes(N) + 255) & ~(size_t)255));
     window_bounds<<<(unsigned)((n_sel + WT - 1) / WT), WT, 0, s>>>(off, ts, R, E, ids, n_sel, t0, t1,
-                                                                   bounds, err);
-    // as many workgroups as fit: few ranks may hold many events
-    const int grid = n_sel <= BAL_SEL ? 3 * cus : grid_w(n_sel, cus, 3);
+                                                                   bounds, wc, err);
+    // a workgroup per rank, or more where few ranks may hold many events
+    const int grid = grid_w(n_sel > E / 4096 ? n_sel : E / 4096, cus, 4);
     if (N <= MAX_NODES_ATTR) {
       static bool attr = false;
       if (!attr) {
@@ -654,11 +749,11 @@ hipError_t launch_window_profile(const int64_t *off, const int64_t *ts, const in
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
         attr = true;
       }
-      window_excl<true><<<grid, WWT, (size_t)N * 8, s>>>(ts, ctx, E, bounds, n_sel, N,
-                                                                         t0, t1, excl, err);
+      window_excl<true><<<grid, WWT, (size_t)N * 8, s>>>(ts, ctx, E, bounds, n_sel, N, t0, t1, wc, 3 * cus,
+                                                         excl, err);
     } else {
-      window_excl<false><<<grid, WWT, sizeof(NodeSums), s>>>(ts, ctx, E, bounds, n_sel, N, t0, t1,
-                                                              excl, err);
+      window_excl<false><<<grid, WWT, sizeof(NodeSums), s>>>(ts, ctx, E, bounds, n_sel, N, t0, t1, wc,
+                                                             3 * cus, excl, err);
     }
   }
   hipError_t e = hipGetLastError();
