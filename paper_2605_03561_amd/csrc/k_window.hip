@@ -182,11 +182,11 @@ struct NodeSums {
   static __device__ int which(v4i k, int32_t c) {
     return k.x == c ? 0 : (k.y == c ? 1 : (k.z == c ? 2 : (k.w == c ? 3 : -1)));
   }
-  // Adds d[u] to node c[u] where d[u] is not 0; first(c) on a new node, none(c, d)
-  // where no slot was found.  Nodes already in their home bucket, the most, are
+  // Adds d[u] to node c[u] where d[u] is not 0; none(c, d) where no slot was found
+  // in `probes` buckets.  Nodes already in their home bucket, the most, are
   // added at once; one loop over what is left keeps the code short.
-  template <class F, class G>
-  __device__ __forceinline__ void add4(const int32_t (&c)[4], uint64_t (&d)[4], int probes, F &&first, G &&none) {
+  template <class G>
+  __device__ __forceinline__ void add4(const int32_t (&c)[4], uint64_t (&d)[4], int probes, G &&none) {
     v4i k[4];
 #pragma unroll
     for (int u = 0; u < 4; u++) k[u] = bucket(home(c[u]));
@@ -217,7 +217,6 @@ struct NodeSums {
           const int f = which(b, -1);
           if (f >= 0) {  // taken by another node meanwhile: the bucket again
             const int32_t x = atomicCAS(&key[at + f], -1, c0);
-            if (x == -1) first(c0);
             if (x == -1 || x == c0) w = f;
           } else {
             at = (at + 4) & (HSLOTS - 1);
@@ -393,11 +392,10 @@ __global__ __launch_bounds__(WWT) void window_excl(const int64_t *__restrict__ t
           const int64_t k = k0 + u;
           d[u] = k >= lo && k < hi ? part(q.t[u], k + 1 < e ? q.t[u + 1] : q.t[u], q.c[u]) : 0;
         }
-        sums.add4(q.c, d, *(volatile int *)&full ? 1 : NodeSums::PROBES, [](int32_t) {},
-                  [&](int32_t c, uint64_t v) {
-                    full = 1;
-                    atomicAdd((unsigned long long *)&excl[c], (unsigned long long)v);
-                  });
+        sums.add4(q.c, d, *(volatile int *)&full ? 1 : NodeSums::PROBES, [&](int32_t c, uint64_t v) {
+          full = 1;
+          atomicAdd((unsigned long long *)&excl[c], (unsigned long long)v);
+        });
       });
     });
   } else {
@@ -455,86 +453,6 @@ __device__ inline int block_excl_scan_i32(int v, int *wsum, int *total) {
   return base + x - v;
 }
 
-// Trees of more than SPC and at most SPBW * 32 nodes, one workgroup per rank
-// (grid-stride): the durations are summed by node id in LDS, a node's first one
-// also sets its bit in a mask; a workgroup scan of the mask's word counts gives
-// each node its place in ascending id.  A rank with a node that finds no slot
-// is left to the kernel below (counts[r] = -1).
-//
-// Bound by the LDS operations and the loads' latency: one pass, two LDS
-// operations per event and two workgroups per CU, where the kernel below takes
-// two passes and four at one per CU: 3,000 ranks of 20,000 events at the median
-// (200,000 at most) over 97,833 nodes 421 -> 349 us.
-__global__ __launch_bounds__(SPT, 8) void sparse_by_id(const int64_t *__restrict__ off,
-                                                      const int64_t *__restrict__ ts,
-                                                      const int32_t *__restrict__ ctx,
-                                                      int64_t R, int64_t E, int N,
-                                                      int64_t *__restrict__ counts,
-                                                      int32_t *__restrict__ ids,
-                                                      int64_t *__restrict__ vals,
-                                                      uint32_t *err) {
-  __shared__ NodeSums sums;
-  __shared__ uint32_t bm[SPBW];
-  __shared__ uint16_t pre[SPBW];  // at most HSLOTS nodes
-  __shared__ int wsum[SPT / 64];
-  __shared__ int full;
-  const int t = threadIdx.x;
-  for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
-    const int64_t o0 = off[r], o1 = off[r + 1];
-    const bool bad = o0 < 0 || o1 < o0 || o1 > E;
-    const int64_t b = bad ? 0 : o0, e = bad ? 0 : o1;
-    if (bad && t == 0) atomicOr(err, ERRBIT_OFFSETS);
-    for (int i = t; i < SPBW; i += SPT) bm[i] = 0;
-    sums.clear(t, SPT);
-    if (t == 0) full = 0;
-    __syncthreads();
-    visit_quads<1>(ts, ctx, E, b, e, e, t, SPT, [&](int64_t k0, const EvQuad &q) {
-      uint64_t d[4];
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const int64_t k = k0 + u;
-        d[u] = 0;
-        if (k < b || k >= e) continue;
-        const int64_t x = k + 1 < e ? q.t[u + 1] - q.t[u] : 0;
-        if (x < 0) atomicOr(err, ERRBIT_UNSORTED);
-        if (q.c[u] < 0 || q.c[u] >= N) atomicOr(err, ERRBIT_CTX);
-        else if (x > 0) d[u] = (uint64_t)x;
-      }
-      sums.add4(q.c, d, NodeSums::PROBES, [&](int32_t v) { atomicOr(&bm[v >> 5], 1u << (v & 31)); },
-                [&](int32_t, uint64_t) { full = 1; });
-    });
-    __syncthreads();
-    int64_t found = -1;
-    if (full == 0) {  // uniform
-      uint32_t wc[SPBT];
-      int own = 0;
-#pragma unroll
-      for (int u = 0; u < SPBT; u++) {
-        wc[u] = (uint32_t)__popc(bm[t * SPBT + u]);
-        own += (int)wc[u];
-      }
-      int total;
-      int pos = block_excl_scan_i32(own, wsum, &total);
-#pragma unroll
-      for (int u = 0; u < SPBT; u++) {
-        pre[t * SPBT + u] = (uint16_t)pos;
-        pos += (int)wc[u];
-      }
-      __syncthreads();
-      for (int i = t; i < HSLOTS; i += SPT) {
-        const int32_t c = sums.key[i];
-        if (c < 0) continue;
-        const int64_t o = b + pre[c >> 5] + __popc(bm[c >> 5] & ((1u << (c & 31)) - 1u));
-        ids[o] = c;
-        vals[o] = (int64_t)sums.sum[i];
-      }
-      found = total;
-    }
-    if (t == 0) counts[r] = found;
-    __syncthreads();
-  }
-}
-
 // One workgroup per rank (grid-stride).  Trees of more than SPC nodes and at
 // most SPBW * 32: a pass over the events' contexts (4 bytes per event) marks
 // the nodes they reach in an LDS bit mask; a workgroup scan of the mask's word
@@ -546,7 +464,7 @@ __global__ __launch_bounds__(SPT, 8) void sparse_by_id(const int64_t *__restrict
 // for each chunk of SPC node ids that the events reach, an LDS histogram of
 // the chunk, then its non-zero bins in ascending id, compacted by a workgroup
 // scan and appended after the previous chunks'.  Output goes to the rank's own
-// event range.  left: only ranks with a negative count.
+// event range.
 __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__restrict__ off,
                                                              const int64_t *__restrict__ ts,
                                                              const int32_t *__restrict__ ctx,
@@ -554,7 +472,7 @@ __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__r
                                                              int64_t *__restrict__ counts,
                                                              int32_t *__restrict__ ids,
                                                              int64_t *__restrict__ vals,
-                                                             int left, uint32_t *err) {
+                                                             uint32_t *err) {
   __shared__ uint64_t pool[SPC];  // chunk histogram, or mask | word prefixes | accumulator
   __shared__ uint32_t touched[SPW];
   __shared__ int wsum[SPT / 64];
@@ -567,7 +485,6 @@ __global__ __launch_bounds__(SPT) void sparse_profiles_kernel(const int64_t *__r
   const int nw = (N + 31) / 32;
   const int t = threadIdx.x;
   for (int64_t r = blockIdx.x; r < R; r += gridDim.x) {
-    if (left && counts[r] >= 0) continue;  // uniform
     // a rank's range, clamped to [0, E] (inconsistent offsets are an error)
     const int64_t o0 = off[r], o1 = off[r + 1];
     const bool bad = o0 < 0 || o1 < o0 || o1 > E;
@@ -765,12 +682,14 @@ hipError_t launch_sparse_profiles(const int64_t *off, const int64_t *ts, const i
                                   int64_t E, int N, int64_t *counts, int32_t *ids, int64_t *vals, uint32_t *err,
                                   int cus, hipStream_t s) {
   if (R <= 0) return hipSuccess;
-  const bool by_id = N > SPC && N <= SPBW * 32;
-  // a workgroup per rank, placed as others end: ranks differ in length (two per
-  // CU in turns: 504 us for 349)
-  if (by_id) sparse_by_id<<<grid_w(R, cus, 64), SPT, 0, s>>>(off, ts, ctx, R, E, N, counts, ids, vals, err);
-  sparse_profiles_kernel<<<grid_w(R, cus, 64), SPT, 0, s>>>(off, ts, ctx, R, E, N, counts, ids, vals,
-                                                           by_id ? 1 : 0, err);
+  // Ranks that take more than a step of the workgroup on average differ in how
+  // many: a workgroup per rank, placed as others end (3,000 ranks of 20,000 events
+  // at the median, lognormal, over 97,833 nodes: 398 us, two workgroups per CU in
+  // turns 474; all of 20,000 events: 218 and 209).  Shorter ranks: in turns, which
+  // saves the launch of a workgroup (100,000 ranks of 20 events over 5,000 nodes: 1,329
+  // and 1,270 us).
+  const int per_cu = E / R >= 4 * SPT ? 64 : 2;
+  sparse_profiles_kernel<<<grid_w(R, cus, per_cu), SPT, 0, s>>>(off, ts, ctx, R, E, N, counts, ids, vals, err);
   return hipGetLastError();
 }
 

@@ -89,3 +89,51 @@ def test_short_window_costs_less_than_the_whole(nodes):
     print(f"whole {whole * 1e3:.0f} us, short {short * 1e3:.0f} us")
     assert short < whole
     h.close()
+
+
+@pytest.mark.parametrize("nodes", [5000, 97833, 131073])
+@pytest.mark.parametrize("reach", [300, 4096, 5000, 97833])
+def test_sparse_profiles_by_reach(oracle, nodes, reach):
+    """Sparse profiles of ranks that reach few nodes, the most that one pass
+    holds and more, with ranks above and below a workgroup's step on average."""
+    from paper_2605_03561_amd import ta
+    rng = np.random.default_rng([nodes, reach])
+    parent = synth.make_tree(rng, nodes, 12)
+    for lens in ([20000, 3, 0, 12000, 4097], [30, 4000, 0, 1, 700] * 8):
+        off, ts, ctx = traces(rng, lens, nodes, reach)
+        h = ta.Handle(0)
+        h.set_tree(parent)
+        tr = ta.DeviceTraces(off, ts, ctx)
+        st, cnt, ids, ex = oracle.sparse_profiles(off, ts, ctx, nodes)
+        assert st == 0
+        g = [x.cpu().numpy() for x in h.sparse_profiles(tr)]
+        assert np.array_equal(g[0][:len(lens)], cnt)
+        for r in range(len(lens)):
+            s = slice(off[r], off[r] + cnt[r])
+            assert np.array_equal(g[1][s], ids[s]) and np.array_equal(g[2][s], ex[s])
+        h.sync_status()
+        h.close()
+
+
+def test_many_nodes_cost_no_second_attempt():
+    """Ranks of 20,000 events that reach up to 4,000 nodes (which one pass holds)
+    against 300: the same passes over the events, so well below twice the time."""
+    import torch
+
+    from paper_2605_03561_amd import ta
+    nodes, R, n = 97833, 300, 20000
+    rng = np.random.default_rng(1)
+    parent = synth.make_tree(rng, nodes, 12)
+    t = []
+    for width in (300, 4000):
+        off, ts, ctx = traces(rng, [n] * R, nodes, width)
+        h = ta.Handle(0)
+        h.set_tree(parent)
+        tr = ta.DeviceTraces(off, ts, ctx)
+        out = (torch.zeros(R, dtype=torch.int64, device="cuda"),
+               torch.zeros(R * n, dtype=torch.int32, device="cuda"),
+               torch.zeros(R * n, dtype=torch.int64, device="cuda"))
+        t.append(best_time(lambda: h.sparse_profiles(tr, out=out)))
+        h.close()
+    print(f"300 nodes {t[0] * 1e3:.0f} us, 4,000 nodes {t[1] * 1e3:.0f} us")
+    assert t[1] < 2 * t[0]
