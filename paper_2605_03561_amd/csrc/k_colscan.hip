@@ -8,9 +8,9 @@
 //                 score_tensor reads it again
 //   more ranks    col_copy writes a column-major copy in 32-bit offsets,
 //                 col_select reads a column of it into the registers of a
-//                 workgroup, score_copy reads it again; a column whose cells
-//                 do not fit in 32 bits is selected by col_select_wide and
-//                 scored from the tensor
+//                 workgroup, score_copy reads it again; the columns whose cells
+//                 do not fit in 32 bits are listed there, copied in two 32-bit
+//                 halves by col_copy_wide and selected by col_select_wide
 // Everything between the count of a column and its MAD happens on registers
 // (ta_select.h).  The row-major passes of longer columns (k_outliers.hip) took
 // 10.0 ms for 32,000 columns of 40,000 ranks where this takes 7.1.
@@ -30,11 +30,12 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int64_t COL_DIRECT_MAX = 1024;
 
 // Key words.  64 bits: cell + HALF64.  32 bits: cell - base + HALF32, base the
-// cell of rank 0 in that column (whatever it holds), or WIDE when that does
-// not fit.  NONE: a cell that the rank does not have.
+// cell of rank 0 in that column (whatever it holds), or a mark when that does
+// not fit: FAR_LOW below every key, FAR_HIGH above.  NONE: a cell that the rank
+// does not have.
 constexpr int64_t HALF64 = (int64_t)1 << 62;
 constexpr int64_t HALF32 = 0x7fffffffll;
-constexpr uint32_t WIDE = 0xfffffffeu;
+constexpr uint32_t FAR_LOW = 0, FAR_HIGH = 0xfffffffeu;
 template <typename K>
 constexpr K none() {
   return ~(K)0;
@@ -71,7 +72,7 @@ struct ColSum {  // exact, over any cells of one column
 template <bool STATS>
 __global__ __launch_bounds__(256, 4) void col_copy(const int64_t *__restrict__ T, int64_t R, int IG, int G,
                                                 const int32_t *__restrict__ it, uint32_t *__restrict__ cp,
-                                                ColPartials ps) {
+                                                uint32_t *n_wide, uint8_t *group, ColPartials ps) {
   constexpr int LD = CT + 4;  // 16-byte rows, columns four banks apart
   union Lds {
     uint32_t tile[64 * LD];
@@ -79,6 +80,10 @@ __global__ __launch_bounds__(256, 4) void col_copy(const int64_t *__restrict__ T
     __device__ Lds() {}
   };
   __shared__ Lds L;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {  // col_select adds to them
+    group[blockIdx.y] = 0;
+    if (blockIdx.y == 0) *n_wide = 0;
+  }
   const int c0 = (int)blockIdx.y * 64;
   const int64_t Rp = copy_ranks(R);
   const int p2 = 2 * (threadIdx.x & 31), k0 = threadIdx.x >> 5;
@@ -119,10 +124,10 @@ __global__ __launch_bounds__(256, 4) void col_copy(const int64_t *__restrict__ T
     for (int k = 0; k < U; k++) {
       const bool in = h == 0 ? ha && ia < nit[k] : hb && ib < nit[k];
       const int64_t d = (int64_t)(h == 0 ? x[k].x : x[k].y) - base[h];
-      const uint32_t w = (d >= HALF32 || d <= -HALF32) ? WIDE : (uint32_t)(d + HALF32);
+      const uint32_t w = d >= HALF32 ? FAR_HIGH : d <= -HALF32 ? FAR_LOW : (uint32_t)(d + HALF32);
       L.tile[(p2 + h) * LD + k0 + 8 * k] = in ? w : none<uint32_t>();
       if (STATS) {
-        far |= in && (w == WIDE || (uint32_t)d + (1u << 29) > (1u << 30));
+        far |= in && w - (uint32_t)(HALF32 - (1 << 29)) > 1u << 30;  // marks too
         const int32_t e = in ? (int32_t)d : 0;
         const uint32_t m = (uint32_t)(e < 0 ? -e : e);
         n += in ? 1u : 0u;
@@ -183,19 +188,25 @@ __global__ __launch_bounds__(256, 4) void col_copy(const int64_t *__restrict__ T
 // What the waves of a column exchange.
 struct ColRed {
   uint64_t mn, mx, a;
-  uint32_t n, m;
+  uint32_t n, m, low;
 };
 
 struct ColOut {
   ColZ *cz;
-  double *mu;     // 32-bit form: the median in doubled key words, as a double; NaN for a wide column
-  uint8_t *wide;  // 32-bit form: 1 for a wide column, else 0
+  double *mu;      // 32-bit form: the median in doubled key words, as a double; negative where the
+                   // column has far cells; NaN for a wide column
+  uint32_t *wide;  // 32-bit form: the number of wide columns, then the columns
+  uint8_t *group;  // 32-bit form: 1 where any of 64 columns is wide
   ColPartials ps;
 };
 
 // From a column's key words in the registers of a group of W waves (u[V] per
 // lane) to its coefficients, and with STATS its imbalance statistics.  `off` is
-// what a key word of 0 stands for.  A wide column is left to col_select_wide.
+// what a key word of 0 stands for.  32-bit form: cells marked as far count below
+// or above the others, which is all that the median needs while it is not one of
+// them, and the MAD while it does not exceed their smallest possible deviation
+// (so a few stalled ranks cost nothing).  A column of which that does not hold, or
+// whose other cells span 2^31 and more, is listed for col_select_wide.
 template <typename K, int V, int W, int NB, bool STATS>
 __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, ColRed *red, int64_t off,
                                               int col, bool have, const ColOut &o) {
@@ -203,7 +214,7 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
   static_assert(!STATS || (W == 1 && !NARROW), "statistics: 64-bit words, one wave");
   const int lane = (int)(threadIdx.x & 63), sw = (int)(threadIdx.x >> 6) % W;
   const bool mine = sw == 0 && lane == 0 && have;
-  uint32_t n = 0;
+  uint32_t n = 0, marks = 0, low = 0;  // marks: cells that are far; low: below
   K mn = none<K>(), mx = 0;  // mx: the largest + 1 (0 for none)
 #pragma unroll
   for (int v = 0; v < V; v++) {
@@ -232,13 +243,57 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
     }
     __syncthreads();
   }
-  const K range = n > 0 ? (K)(mx - 1 - mn) : 0;
-  // deviations |2u - med2| of 32-bit offsets need twice the range
-  const bool wide = NARROW && n > 0 && (mx > (K)WIDE || range > (K)0x7ffffffeu);
-  if (NARROW && mine) o.wide[col] = wide ? 1 : 0;
-  if (wide) {
-    if (mine) o.mu[col] = nan_f64();
-    return;  // the whole group
+  if (NARROW && (mn == (K)FAR_LOW || mx > (K)FAR_HIGH)) {  // uniform; the same without the marks
+    mn = none<K>();
+    mx = 0;
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+      const bool lo = u[v] == (K)FAR_LOW, key = u[v] - 1 < (K)FAR_HIGH - 1;
+      low += lo ? 1u : 0u;
+      marks += lo || u[v] == (K)FAR_HIGH ? 1u : 0u;
+      mn = key && u[v] < mn ? u[v] : mn;
+      mx = key && u[v] + 1 > mx ? u[v] + 1 : mx;
+      pace(v);
+    }
+    mn = wave_min(mn);
+    mx = wave_max(mx);
+    low = wave_sum(low);
+    marks = wave_sum(marks);
+    if (W > 1) {
+      if (lane == 0) {
+        red[sw].mn = mn;
+        red[sw].mx = mx;
+        red[sw].m = marks;
+        red[sw].low = low;
+      }
+      __syncthreads();
+      marks = low = 0;
+#pragma unroll
+      for (int q = 0; q < W; q++) {
+        mn = (K)red[q].mn < mn ? (K)red[q].mn : mn;
+        mx = (K)red[q].mx > mx ? (K)red[q].mx : mx;
+        marks += red[q].m;
+        low += red[q].low;
+      }
+      __syncthreads();
+    }
+  }
+  const uint32_t keys = n - marks;
+  const K range = keys > 0 ? (K)(mx - 1 - mn) : 0;
+  const uint32_t k = n > 0 ? (n - 1) / 2 : 0, two = n > 0 && (n & 1) == 0 ? 1u : 0u;
+  const bool even = two != 0;
+  auto list_wide = [&]() {  // the whole group returns
+    if (mine) {
+      o.wide[1 + atomicAdd(o.wide, 1u)] = (uint32_t)col;
+      o.group[col / 64] = 1;
+      o.mu[col] = nan_f64();
+    }
+  };
+  // deviations |2u - med2| of 32-bit offsets need twice the range; with marks,
+  // both middle cells and both middle deviations have to be keys
+  if (NARROW && n > 0 && (range > (K)0x7ffffffeu || k < low || k - low + two >= keys || k + two >= keys)) {
+    list_wide();
+    return;
   }
 
   // offsets from the smallest cell (a word that is no key stays above `range`)
@@ -290,11 +345,10 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
   }
 
   // the median, then the MAD of |2u - med2|
-  const uint32_t k = (n - 1) / 2;
-  const bool even = (n & 1) == 0;
+  const uint32_t km = k - low;
   K a = 0, b = 0;
-  if (k + (even ? 1u : 0u) >= zeros)  // else both middle cells are the smallest
-    reg_select<true>(S, u, (K)0, zeros, range, nbits64(range), n, k, even, a, b);
+  if (km + two >= zeros)  // else both middle cells are the smallest
+    reg_select<true>(S, u, (K)0, zeros, range, nbits64(range), keys, km, even, a, b);
   const K m2 = a + b;
   uint32_t hits = 0;  // deviations equal to med2: the smallest cells', which may be many
 #pragma unroll
@@ -315,9 +369,18 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
   }
   const K far = (K)(2 * range - m2), dmax = far > m2 ? far : m2;
   a = b = 0;
-  if (m2 != 0 || k + (even ? 1u : 0u) >= zeros)  // else both middle deviations are 0
-    reg_select<true>(S, u, m2, hits, dmax, nbits64(dmax), n, k, even, a, b);
+  if (m2 != 0 || k + two >= zeros)  // else both middle deviations are 0
+    reg_select<true>(S, u, m2, hits, dmax, nbits64(dmax), keys, k, even, a, b);
   const uint64_t mad4 = (uint64_t)a + (uint64_t)b;
+  if (NARROW && marks > 0) {
+    // a far cell's deviation is at least that of the mark itself; the mean
+    // deviation, wanted when the MAD is 0, needs the cells
+    const uint64_t med = 2 * (uint64_t)mn + (uint64_t)m2, hi = 2 * (uint64_t)FAR_HIGH - med;
+    if (mad4 == 0 || (uint64_t)b > (med < hi ? med : hi)) {
+      list_wide();
+      return;
+    }
+  }
   uint64_t sd = 0;  // the sum of the deviations is wanted when the MAD is 0
   if (mad4 == 0) {
 #pragma unroll
@@ -336,7 +399,8 @@ __device__ __forceinline__ void select_column(K (&u)[V], SelGroup<W, NB, K> &S, 
     z_coefs((int64_t)mad4, (int64_t)sd, (int64_t)n, z.zc, z.zd);
     z.zy = 1.0 / z.zd;
     o.cz[col] = z;
-    if (NARROW) o.mu[col] = (double)(2 * (uint64_t)mn + (uint64_t)m2);
+    const double mu = (double)(2 * (uint64_t)mn + (uint64_t)m2);  // above 0
+    if (NARROW) o.mu[col] = marks > 0 ? -mu : mu;
   }
 }
 
@@ -346,10 +410,11 @@ constexpr int col_bins() {  // 4 to 16 bins per lane of a single wave, else 2,04
 }
 
 // Waves per SIMD that V key words and what else a lane needs leave room for (the
-// compiler takes up to twice the registers when it is not told).
+// compiler takes up to twice the registers when it is not told; so it keeps 2 to 26
+// registers of the rarer branches in scratch).
 template <int V>
 constexpr int sel_waves() {
-  return V <= 40 ? 8 : V <= 48 ? 6 : V <= 64 ? 5 : 4;
+  return V <= 32 ? 8 : V <= 48 ? 6 : V <= 64 ? 5 : 4;
 }
 
 // Columns of the 32-bit copy: W waves and V key words per lane each; a single
@@ -385,30 +450,89 @@ __global__ __launch_bounds__(W > 1 ? 64 * W : 256, sel_waves<V>()) void col_sele
   select_column<uint32_t, V, W, NB, false>(u, L[cl], red, off, col, true, o);
 }
 
-// The columns that the 32-bit form marked wide, in 64-bit words straight from
-// the tensor (8-byte pieces of rows: for data with a spread of 2^31 ns and
-// more within a column).  Returns at once when there is none.
-__global__ __launch_bounds__(1024) void col_select_wide(const int64_t *__restrict__ T, int64_t R, int IG,
-                                                        int G, const int32_t *__restrict__ it, ColOut o) {
-  constexpr int W = 16, V = (int)(COL_REG_MAX / 1024);
+// The wide columns' keys in two 32-bit halves, the low words in their place of the
+// 32-bit copy, the high words in hi[IG][copy_ranks(R)]: a workgroup takes 128
+// ranks of every gridDim.y-th group of 64 columns that has a wide one; both halves
+// go through the same LDS tile.  Returns at once when there are none.  Bound by HBM
+// (16 bytes per cell): 6,400 columns of 16,000 ranks 334 us, 4.9 TB/s.
+__global__ __launch_bounds__(256, 4) void col_copy_wide(const int64_t *__restrict__ T, int64_t R, int IG, int G,
+                                                        const int32_t *__restrict__ it, uint32_t *__restrict__ cp,
+                                                        uint32_t *__restrict__ hi, ColOut o) {
+  constexpr int LD = CT + 1, U = CT / 4;
+  __shared__ uint32_t tile[64 * LD];
+  if (o.wide[0] == 0) return;
+  const int64_t Rp = copy_ranks(R), r0 = (int64_t)blockIdx.x * CT;
+  const int lane = (int)(threadIdx.x & 63), wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  for (int c0 = (int)blockIdx.y * 64; c0 < IG; c0 += (int)gridDim.y * 64) {
+    if (!o.group[c0 / 64]) continue;  // uniform
+    const int col = c0 + lane < IG ? c0 + lane : IG - 1, ic = col / G;
+    const bool mine = c0 + lane < IG && !(o.mu[col] == o.mu[col]);
+    const uint64_t wide = __ballot(mine);  // the same in every wave
+    uint64_t x[U];
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const int64_t r = r0 + 4 * k + wid;
+      x[k] = (uint64_t)T[(r < R ? r : R - 1) * IG + col];
+    }
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      const int64_t r = r0 + 4 * k + wid;
+      const bool in = r < R && (!it || ic < it[r]);
+      x[k] = in ? x[k] + (uint64_t)HALF64 : none<uint64_t>();
+    }
+#pragma unroll
+    for (int half = 0; half < 2; half++) {
+      __syncthreads();  // the previous half is written out
+#pragma unroll
+      for (int k = 0; k < U; k++) tile[lane * LD + 4 * k + wid] = (uint32_t)(x[k] >> (32 * half));
+      __syncthreads();
+      uint32_t *to = half ? hi : cp;
+      for (int c = (int)threadIdx.x / 32; c < 64; c += 8) {
+        if (!(wide >> c & 1)) continue;
+        const int q = 4 * ((int)threadIdx.x & 31);
+        const uint32_t *l = &tile[c * LD + q];
+        *reinterpret_cast<v4u *>(to + (int64_t)(c0 + c) * Rp + r0 + q) = v4u{l[0], l[1], l[2], l[3]};
+      }
+    }
+  }
+}
+
+// The wide columns, in 64-bit words: a workgroup per column.  Without high words
+// (hi NULL) they are read from the tensor, in 8-byte pieces of rows.
+template <int W, int V>
+__global__ __launch_bounds__(64 * W) void col_select_wide(const uint32_t *__restrict__ cp, const uint32_t *__restrict__ hi,
+                                                          const int64_t *__restrict__ T, int64_t R, int IG,
+                                                          int G, const int32_t *__restrict__ it, ColOut o) {
   __shared__ SelGroup<W, 2048, uint64_t> L;
   __shared__ ColRed red[W];
-  __shared__ uint32_t todo[1024], n_todo;
   const int tid = (int)threadIdx.x;
-  if (tid == 0) n_todo = 0;
-  __syncthreads();
-  const int64_t c = blockIdx.x + (int64_t)tid * gridDim.x;  // the grid leaves at most 1,024 per workgroup
-  if (c < IG && o.wide[c]) todo[atomicAdd(&n_todo, 1u)] = (uint32_t)c;
-  __syncthreads();
-  const int turns = (int)n_todo;
-  for (int turn = 0; turn < turns; turn++) {
-    const int col = (int)todo[turn], ic = col / G;
+  const uint32_t n = o.wide[0];
+  const int64_t Rp = copy_ranks(R);
+  for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
+    const int col = (int)o.wide[1 + e], ic = col / G;
     uint64_t u[V];
+    const int own = opaque(tid);  // else V offsets and iteration counts are kept over the columns
+    if (hi) {
 #pragma unroll
-    for (int v = 0; v < V; v++) {
-      const int64_t r = (int64_t)v * 1024 + tid;
-      u[v] = none<uint64_t>();
-      if (r < R && (!it || ic < it[r])) u[v] = (uint64_t)(T[r * IG + col] + HALF64);
+      for (int v = 0; v < V; v += 4) {
+        const int64_t r = (int64_t)(v / 4) * 256 * W + 4 * own;
+        v4u l = {none<uint32_t>(), none<uint32_t>(), none<uint32_t>(), none<uint32_t>()}, h = l;
+        if (r < Rp) {
+          l = *reinterpret_cast<const v4u *>(cp + (int64_t)col * Rp + r);
+          h = *reinterpret_cast<const v4u *>(hi + (int64_t)col * Rp + r);
+        }
+        u[v] = (uint64_t)h.x << 32 | l.x;
+        u[v + 1] = (uint64_t)h.y << 32 | l.y;
+        u[v + 2] = (uint64_t)h.z << 32 | l.z;
+        u[v + 3] = (uint64_t)h.w << 32 | l.w;
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; v++) {
+        const int r = v * 64 * W + own;
+        u[v] = none<uint64_t>();
+        if (r < (int)R && (!it || ic < it[r])) u[v] = (uint64_t)(T[(int64_t)r * IG + col] + HALF64);
+      }
     }
     __syncthreads();
     sel_clear(L);
@@ -512,8 +636,8 @@ __device__ __forceinline__ int rank_iters(const int32_t *it, int64_t r, int I) {
 // columns 127 -> 63 us, 10,000 x 9,600 145 -> 100 us).  Bound by the copy's 4
 // bytes per cell for long columns, by the loads' round trips for short ones.
 template <int RPL, int IU>
-__global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ cp, const int64_t *__restrict__ T,
-                                                  int64_t R, int I, int G, const int32_t *__restrict__ it,
+__global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ cp, const uint32_t *__restrict__ hi,
+                                                  const int64_t *__restrict__ T, int64_t R, int I, int G, const int32_t *__restrict__ it,
                                                   const ColZ *__restrict__ cz, const double *__restrict__ mu,
                                                   double *m_t) {
   constexpr int SI = 256;
@@ -558,7 +682,7 @@ __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ c
       for (int j = 0; j < IU; j++) {
         if (i0 + j >= ns) break;
         const Num z = num[i0 + j];
-        if (z.mu == z.mu) {
+        if (z.mu >= 0.0) {
 #pragma unroll
           for (int q = 0; q < RPL; q++) {
             // 2x - med2 in key words: both terms are integers below 2^34
@@ -566,14 +690,46 @@ __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ c
             const double t = acc[q] + div_by(d * z.zc, z.zd, z.zy);
             acc[q] = w[j][q] != none<uint32_t>() ? t : acc[q];
           }
+        } else if (z.mu < 0.0) {  // a column with far cells
+          const int64_t c = (int64_t)(s0 + i0 + j) * G + g;
+#pragma unroll
+          for (int q = 0; q < RPL; q++) {
+            if (w[j][q] == none<uint32_t>()) continue;
+            double d = fma(2.0, (double)w[j][q], z.mu);
+            if (w[j][q] == FAR_LOW || w[j][q] == FAR_HIGH)
+              d = (double)(2 * T[(r0 + q) * (int64_t)I * G + c] - cz[c].med2);
+            acc[q] += div_by(d * z.zc, z.zd, z.zy);
+          }
         } else {  // a wide column
           const int64_t c = (int64_t)(s0 + i0 + j) * G + g, med2 = cz[c].med2;
-#pragma unroll
-          for (int q = 0; q < RPL; q++)
-            if (r0 + q < R && s0 + i0 + j < rank_iters(it, r0 + q, I)) {
-              const int64_t x = T[(r0 + q) * (int64_t)I * G + c];
-              acc[q] += div_by((double)(2 * x - med2) * z.zc, z.zd, z.zy);
+          uint64_t key[RPL];
+          if (hi) {
+            const uint32_t *src = hi + c * Rp + (r0 < R ? r0 : 0);
+            uint32_t h[RPL];
+            if (RPL == 4) {
+              const v4u v = *reinterpret_cast<const v4u *>(src);
+              h[0] = v.x;
+              h[1 % RPL] = v.y;
+              h[2 % RPL] = v.z;
+              h[3 % RPL] = v.w;
+            } else {
+              h[0] = src[0];
             }
+#pragma unroll
+            for (int q = 0; q < RPL; q++) key[q] = (uint64_t)h[q] << 32 | w[j][q];
+          } else {
+#pragma unroll
+            for (int q = 0; q < RPL; q++)
+              key[q] = r0 + q < R && s0 + i0 + j < rank_iters(it, r0 + q, I)
+                           ? (uint64_t)(T[(r0 + q) * (int64_t)I * G + c] + HALF64)
+                           : none<uint64_t>();
+          }
+#pragma unroll
+          for (int q = 0; q < RPL; q++) {
+            const int64_t x = (int64_t)(key[q] - (uint64_t)HALF64);
+            const double t = acc[q] + div_by((double)(2 * x - med2) * z.zc, z.zd, z.zy);
+            acc[q] = key[q] != none<uint64_t>() ? t : acc[q];
+          }
         }
       }
     }
@@ -764,9 +920,15 @@ __global__ __launch_bounds__(256) void score_tensor(const int64_t *__restrict__ 
 struct ColWs {
   ColZ *cz;
   double *mu;
-  uint8_t *wide;
+  uint32_t *wide;
   uint32_t *cp;
+  uint8_t *group;
+  uint32_t *hi;
 };
+
+// Whether the workspace holds high words for wide columns: up to 2^33 cells (beside
+// a tensor of more than 64 GB it stays at half the tensor's size).
+bool high_words(int64_t R, int IG) { return copy_ranks(R) * IG <= (int64_t)1 << 33; }
 
 ColWs carve(void *ws, int64_t R, int IG, size_t *used) {
   size_t off = 0;
@@ -779,8 +941,10 @@ ColWs carve(void *ws, int64_t R, int IG, size_t *used) {
   w.cz = (ColZ *)take((size_t)IG * sizeof(ColZ));
   if (R > COL_DIRECT_MAX) {
     w.mu = (double *)take((size_t)IG * 8);
-    w.wide = (uint8_t *)take((size_t)IG);
+    w.wide = (uint32_t *)take(((size_t)IG + 1) * 4);
+    w.group = (uint8_t *)take((size_t)(IG + 63) / 64);
     w.cp = (uint32_t *)take((size_t)IG * copy_ranks(R) * 4);
+    if (high_words(R, IG)) w.hi = (uint32_t *)take((size_t)IG * copy_ranks(R) * 4);
   }
   *used = off;
   return w;
@@ -832,7 +996,7 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
   size_t used = 0;
   const int IG = I * G;
   const ColWs w = carve(ws, R, IG, &used);
-  const ColOut o{w.cz, w.mu, w.wide, st};
+  const ColOut o{w.cz, w.mu, w.wide, w.group, st};
   const bool stats = st.rc > 0;
   hipError_t e = hipSuccess;
   if (R <= COL_DIRECT_MAX) {
@@ -858,9 +1022,9 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
   const int64_t Rp = copy_ranks(R);
   const dim3 cgrid((unsigned)(Rp / CT), (unsigned)((IG + 63) / 64));
   if (stats)
-    hipLaunchKernelGGL(col_copy<true>, cgrid, dim3(256), 0, s, T, R, IG, G, it, w.cp, st);
+    hipLaunchKernelGGL(col_copy<true>, cgrid, dim3(256), 0, s, T, R, IG, G, it, w.cp, w.wide, w.group, st);
   else
-    hipLaunchKernelGGL(col_copy<false>, cgrid, dim3(256), 0, s, T, R, IG, G, it, w.cp, st);
+    hipLaunchKernelGGL(col_copy<false>, cgrid, dim3(256), 0, s, T, R, IG, G, it, w.cp, w.wide, w.group, st);
   e = hipGetLastError();
   if (e == hipSuccess && stats && stats_ready) e = hipEventRecord(stats_ready, s);
   if (e != hipSuccess) return e;
@@ -872,7 +1036,9 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
   // is a chain of barriers and exchanges, so as many columns as possible should
   // be in flight, and beside the column a lane needs 20 to 45 registers.  With
   // 24 or 32 words per lane (twice the waves, half the columns) 10,000 ranks
-  // took 311 us instead of 206, 16,000 ranks 354 instead of 261.
+  // took 311 us instead of 206, 16,000 ranks 354 instead of 261; with 16 waves of 40
+  // words 32,000 columns of 40,000 ranks 3.00 ms instead of 2.75 (64 registers a
+  // lane, 21 of them in scratch).
   auto shape = [&](auto w, auto v) {
     constexpr int W = decltype(w)::value, V = decltype(v)::value;
     go(col_select<W, V>, W > 1 ? 64 * W : 256, W > 1 ? 1 : 4);
@@ -889,18 +1055,34 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
   else if (R <= 20480) shape(std::integral_constant<int, 4>(), std::integral_constant<int, 80>());
   else if (R <= 24576) shape(std::integral_constant<int, 8>(), std::integral_constant<int, 48>());
   else if (R <= 32768) shape(std::integral_constant<int, 8>(), std::integral_constant<int, 64>());
-  else if (R <= 40960) shape(std::integral_constant<int, 16>(), std::integral_constant<int, 40>());
+  else if (R <= 40960) shape(std::integral_constant<int, 8>(), std::integral_constant<int, 80>());
   else shape(std::integral_constant<int, 16>(), std::integral_constant<int, 48>());
-  const unsigned wg = (unsigned)std::max(std::min(IG, cus), (IG + 1023) / 1024);
-  hipLaunchKernelGGL(col_select_wide, dim3(wg), dim3(1024), 0, s, T, R, IG, G, it, o);
+  const uint32_t *cp = w.cp, *hi = w.hi;
+  const int64_t tiles = Rp / CT;
+  if (w.hi)
+    hipLaunchKernelGGL(col_copy_wide,
+                       dim3((unsigned)tiles, (unsigned)std::min<int64_t>((IG + 63) / 64, (4 * cus + tiles - 1) / tiles)),
+                       dim3(256), 0, s, T, R, IG, G, it, w.cp, w.hi, o);
+  auto wide = [&](auto w, auto v) {
+    constexpr int W = decltype(w)::value, V = decltype(v)::value;
+    hipLaunchKernelGGL((col_select_wide<W, V>), dim3((unsigned)std::min(IG, 16 / W * cus)), dim3(64 * W), 0, s,
+                       cp, hi, T, R, IG, G, it, o);
+  };
+  if (R <= 2048) wide(std::integral_constant<int, 4>(), std::integral_constant<int, 8>());
+  else if (R <= 4096) wide(std::integral_constant<int, 8>(), std::integral_constant<int, 8>());
+  else if (R <= 12288) wide(std::integral_constant<int, 16>(), std::integral_constant<int, 12>());
+  else if (R <= 20480) wide(std::integral_constant<int, 16>(), std::integral_constant<int, 20>());
+  else if (R <= 32768) wide(std::integral_constant<int, 16>(), std::integral_constant<int, 32>());
+  else if (R <= 40960) wide(std::integral_constant<int, 16>(), std::integral_constant<int, 40>());
+  else wide(std::integral_constant<int, 16>(), std::integral_constant<int, (int)(COL_REG_MAX / 1024)>());
   // four ranks per lane (16-byte loads) once that leaves 16 waves per CU
   const int64_t b4 = (R + 1023) / 1024 * G;
   if (b4 >= 4 * (int64_t)cus)
-    hipLaunchKernelGGL((score_copy<4, 4>), dim3((unsigned)b4), dim3(256), 0, s, (const uint32_t *)w.cp, T, R,
-                       I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
+    hipLaunchKernelGGL((score_copy<4, 4>), dim3((unsigned)b4), dim3(256), 0, s, cp, hi, T, R, I, G, it,
+                       (const ColZ *)w.cz, (const double *)w.mu, m_t);
   else
-    hipLaunchKernelGGL((score_copy<1, 16>), dim3((unsigned)((R + 255) / 256 * G)), dim3(256), 0, s,
-                       (const uint32_t *)w.cp, T, R, I, G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
+    hipLaunchKernelGGL((score_copy<1, 16>), dim3((unsigned)((R + 255) / 256 * G)), dim3(256), 0, s, cp, hi, T, R, I,
+                       G, it, (const ColZ *)w.cz, (const double *)w.mu, m_t);
   return hipGetLastError();
 }
 
