@@ -1378,8 +1378,9 @@ __global__ __launch_bounds__(256) void score_rows(const int64_t *__restrict__ T,
 template <int TPR>
 __global__ __launch_bounds__(256) void rank_totals_t(const int64_t *__restrict__ T, int64_t R, int I,
                                                      int G, const int32_t *it, int64_t *S_t) {
-  rank_region_sums<TPR, false>(T, R, I, G, it,
-                               [&](int64_t r, int g, int64_t s, u128) { S_t[(int64_t)g * R + r] = s; });
+  auto put = [&](int64_t r, int g, int64_t s, u128) { S_t[(int64_t)g * R + r] = s; };
+  if constexpr (TPR == 1) rank_region_sums_short<false>(T, R, I, G, it, put);
+  else rank_region_sums<TPR, false>(T, R, I, G, it, put);
 }
 
 // ----------------------------------------------------------------------------
@@ -2488,12 +2489,13 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
         launch_sel_regions<true, false>((const void *)w.m_t, a.R, a.G, a.it, a.I, w.z_t,
                                          a.region_score, a.n_flagged, s);
     } else {
-      if (rank_sums_by_wave(IG))
-        hipLaunchKernelGGL(rank_totals_t<64>, dim3((unsigned)((a.R + 3) / 4)), dim3(256), 0, s, a.T, a.R, a.I,
-                           a.G, a.it, w.S_t);
-      else
-        hipLaunchKernelGGL(rank_totals_t<256>, dim3((unsigned)a.R), dim3(256), 0, s, a.T, a.R, a.I, a.G, a.it,
-                           w.S_t);
+      auto go = [&](auto kern, int64_t grid) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, a.T, a.R, a.I, a.G, a.it, w.S_t);
+      };
+      const int tpr = rank_sums_threads(a.I, a.G);
+      if (tpr == 1) go(rank_totals_t<1>, (a.R * a.G + 255) / 256);
+      else if (tpr == 64) go(rank_totals_t<64>, (a.R + 3) / 4);
+      else go(rank_totals_t<256>, a.R);
       if (mad)
         launch_sel_regions<false, true>((const void *)w.S_t, a.R, a.G, a.it, a.I, w.z_t,
                                          a.region_score, a.n_flagged, s);

@@ -122,18 +122,20 @@ __global__ __launch_bounds__(CT) void colstats_final(int IG, int RC, int ddof, C
 }
 
 // Per-(rank, region) totals over the rank's valid iterations, when the
-// segmentation pass did not provide them.  A thread per (rank, region) walked its
-// iterations one load at a time: 3,001 ranks of 217 x 37 cells 113 us, now 31.
+// segmentation pass did not provide them.  With a thread per (rank, region), one
+// load at a time, 3,001 ranks of 217 x 37 cells took 113 us, now 31.
 template <int TPR>
 __global__ __launch_bounds__(CT) void rank_stats(const int64_t *__restrict__ T, int64_t R, int I,
                                                  int G, const int32_t *it, int64_t *S,
                                                  uint64_t *Q) {
-  rank_region_sums<TPR, true>(T, R, I, G, it, [&](int64_t r, int g, int64_t s, u128 q) {
+  auto put = [&](int64_t r, int g, int64_t s, u128 q) {
     const int64_t p = r * G + g;
     S[p] = s;
     Q[2 * p] = (uint64_t)q;
     Q[2 * p + 1] = (uint64_t)(q >> 64);
-  });
+  };
+  if constexpr (TPR == 1) rank_region_sums_short<true>(T, R, I, G, it, put);
+  else rank_region_sums<TPR, true>(T, R, I, G, it, put);
 }
 
 constexpr int RT = 256;
@@ -385,14 +387,17 @@ hipError_t launch_imbalance(const ImbArgs &a, void *ws, size_t ws_bytes, hipStre
   const int64_t *S = a.rank_sum;
   const uint64_t *Q = a.rank_sumsq;
   if (rankst) {
-    if (a.R > 0)
-    {
-      if (rank_sums_by_wave(IG))
-        hipLaunchKernelGGL(rank_stats<64>, dim3((unsigned)((a.R + 3) / 4)), dim3(CT), 0, s, a.T, a.R, a.I, a.G,
-                           a.it, w.S, w.Q);
-      else
-        hipLaunchKernelGGL(rank_stats<256>, dim3((unsigned)a.R), dim3(CT), 0, s, a.T, a.R, a.I, a.G, a.it, w.S,
-                           w.Q);
+    auto go = [&](auto kern, int64_t grid) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(CT), 0, s, a.T, a.R, a.I, a.G, a.it, w.S, w.Q);
+    };
+    const int tpr = rank_sums_threads(a.I, a.G);
+    if (a.R == 0) {
+    } else if (tpr == 1) {
+      go(rank_stats<1>, (a.R * a.G + CT - 1) / CT);
+    } else if (tpr == 64) {
+      go(rank_stats<64>, (a.R + 3) / 4);
+    } else {
+      go(rank_stats<256>, a.R);
     }
     S = w.S;
     Q = w.Q;

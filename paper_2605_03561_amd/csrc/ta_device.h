@@ -286,7 +286,42 @@ __device__ __forceinline__ void rank_region_sums(const int64_t *__restrict__ T, 
     __syncthreads();
   }
 }
-// Threads per rank: a wave while a row is no more than some 16 loads of it.
-inline bool rank_sums_by_wave(int64_t IG) { return IG <= 1024; }
+// The same with a thread per (rank, region), eight iterations' loads in flight: for
+// rows of few iterations, where a wave per rank leaves lanes without a cell.
+template <bool SQ, class F>
+__device__ __forceinline__ void rank_region_sums_short(const int64_t *__restrict__ T, int64_t R, int I, int G,
+                                                       const int32_t *__restrict__ it, F &&f) {
+  constexpr int U = 8;
+  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (p >= R * G) return;
+  const int64_t r = p / G;
+  const int g = (int)(p - r * G);
+  int ni = it ? it[r] : I;
+  ni = ni > I ? I : ni;
+  const int64_t *row = T + r * (int64_t)I * G + g;
+  int64_t s = 0;
+  u128 q = 0;
+  for (int i = 0; i < ni; i += U) {
+    int64_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) x[u] = i + u < ni ? row[(int64_t)(i + u) * G] : 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      s += x[u];
+      if (SQ) q += (u128)((i128)x[u] * x[u]);
+    }
+  }
+  f(r, g, s, q);
+}
+
+// Threads per rank: one per region while a row is no more than 256 cells in 32
+// iterations and does not fill a wave (40,000 ranks of 8 x 5 cells, sums and squares
+// of an imbalance: 259 us for the call, with a wave per rank 277; 300,000 of 4 x 1 1,074
+// and 1,404; of 8 x 64 1,121 and 1,087; 2,000 of 64 x 1 112 and 109), a wave while it
+// is no more than some 16 loads of it, else a workgroup.
+inline int rank_sums_threads(int I, int G) {
+  const int64_t IG = (int64_t)I * G;
+  return G < 64 && I <= 32 && IG <= 256 ? 1 : IG <= 1024 ? 64 : 256;
+}
 
 }  // namespace ta

@@ -1,0 +1,82 @@
+"""Statistics of tensors with few cells per rank: the forms that a thread per
+region, a wave and a workgroup per rank take, against the oracle, and their cost."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ta():
+    from paper_2605_03561_amd import ta as T
+    return T
+
+
+@pytest.fixture(scope="module")
+def h(ta):
+    hh = ta.Handle(0)
+    yield hh
+    hh.close()
+
+
+def best_time(f, n=9):
+    import torch
+    f()
+    t = []
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b))
+    return min(t)
+
+
+def tensor(rng, R, I, G):
+    T = rng.integers(0, 10**6, (R, I, G))
+    T[:, :, 1 % G] = rng.integers(-2**42, 2**42, (R, I))  # sums of deviations below 2^62
+    T[:, I // 2] *= rng.random((R, G)) < 0.5
+    it = np.where(rng.random(R) < 0.2, rng.integers(0, I + 1, R), I).astype(np.int32)
+    return T.astype(np.int64), it
+
+
+SHAPES = [(1, 1), (1, 63), (1, 64), (2, 5), (4, 63), (7, 3), (8, 32), (9, 29), (16, 16), (31, 8),
+          (32, 8), (32, 9), (33, 7), (33, 1), (3, 128), (1, 129), (2, 100)]
+
+
+@pytest.mark.parametrize("R", [1, 3, 255, 4097, 20001])
+@pytest.mark.parametrize("I,G", SHAPES)
+def test_rank_sums(ta, h, oracle, R, I, G):
+    """Totals and imbalance where the number of threads per rank changes; sums of
+    integers, so the totals' scan is the oracle's bit for bit."""
+    import torch
+    T, it = tensor(np.random.default_rng([R, I, G]), R, I, G)
+    dT, dit = torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda()
+    o = h.outliers(dT, dit, mode=ta.SCAN_TOTALS, region=True)
+    st, score, flag, nf, reg = oracle.outliers(T, it, mode=1)
+    assert st == 0
+    assert np.array_equal(o["region_score"].cpu().numpy(), reg)
+    assert np.array_equal(o["rank_flag"].cpu().numpy(), flag)
+    g = h.imbalance(dT, dit)
+    _, ref = oracle.imbalance(T, it)
+    for k in ("min", "max"):
+        assert np.array_equal(g[k].cpu().numpy(), ref[k])
+    for k in ("mean", "std", "max_minus_mean", "cv_across", "cv_within"):
+        np.testing.assert_allclose(g[k].cpu().numpy(), ref[k], rtol=1e-12, atol=1e-9)
+
+
+def test_sums_of_single_cells_cost(ta, h):
+    """Rank sums of 2,000,000 ranks of one cell: an imbalance without them against
+    one with the sums in hand.  The sums read 16 MB and write 48; a wave per rank
+    made the call more than half as long again as it is with a thread."""
+    import torch
+    R = 2_000_000
+    T = torch.randint(0, 10**6, (R, 1, 1), device="cuda")
+    s = T.sum(1)
+    q = torch.zeros((R, 1, 2), dtype=torch.int64, device="cuda")
+    q[..., 0] = (T * T).sum(1)
+    without = best_time(lambda: h.imbalance(T)) * 1e3
+    given = best_time(lambda: h.imbalance(T, rank_sum=s, rank_sumsq=q)) * 1e3
+    print(f"without {without:.0f} us, given {given:.0f} us")
+    assert without < 1.5 * given
