@@ -799,6 +799,12 @@ __global__ __launch_bounds__(256) void score_rank(const int64_t *__restrict__ T,
       if (r0 + q < R) m_t[(int64_t)tid * R + r0 + q] = ni[q] > 0 ? acc[q] / (double)ni[q] : 0.0;
 }
 
+__device__ __forceinline__ double plain_z(int64_t x, const ColMom &z) {
+  const i128 num = (i128)z.n * x - z.s1;
+  const int64_t lo = (int64_t)num;
+  return div_by(num == (i128)lo ? (double)lo : i128_to_f64(num), z.zd, z.zy);
+}
+
 // m(r,g) with plain z scores, from the row-major tensor: a workgroup scores NR
 // ranks' rows, every cell by a thread of its own, into LDS, and a thread per
 // (rank, region) adds the scores in ascending iteration.  Regions beyond 256 by
@@ -847,9 +853,7 @@ __global__ __launch_bounds__(256) void score_plain(const int64_t *__restrict__ T
 #pragma unroll
         for (int q = 0; q < NR; q++) {
           const int64_t x = r0 + q < R ? T[(r0 + q) * IG + c] : 0;
-          const i128 num = (i128)z.n * x - z.s1;
-          const int64_t lo = (int64_t)num;
-          sc[q * CELLS + k] = div_by(num == (i128)lo ? (double)lo : i128_to_f64(num), z.zd, z.zy);
+          sc[q * CELLS + k] = plain_z(x, z);
         }
       }
     }
@@ -866,6 +870,35 @@ __global__ __launch_bounds__(256) void score_plain(const int64_t *__restrict__ T
   for (int j = 0; j < NR; j++)
     if (eq[j] < NR && r0 + eq[j] < R)
       m_t[(int64_t)(g0 + eg[j]) * R + r0 + eq[j]] = en[j] > 0 ? acc[j] / (double)en[j] : 0.0;
+}
+
+// The same for rows of few iterations, a thread per (rank, region).
+__global__ __launch_bounds__(256) void score_plain_short(const int64_t *__restrict__ T, int64_t R, int I, int G,
+                                                         const int32_t *__restrict__ it,
+                                                         const ColMom *__restrict__ cm, double *m_t) {
+  constexpr int U = 4;
+  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (p >= R * G) return;
+  const int64_t r = p / G;
+  const int g = (int)(p - r * G), ni = rank_iters(it, r, I);
+  const int64_t *row = T + r * (int64_t)I * G + g;
+  double acc = 0.0;
+  for (int i = 0; i < ni; i += U) {
+    int64_t x[U];
+    ColMom z[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int64_t c = (int64_t)(i + u < ni ? i + u : ni - 1) * G;
+      x[u] = row[c];
+      z[u] = cm[c + g];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const double v = plain_z(x[u], z[u]);
+      acc = i + u < ni ? acc + v : acc;
+    }
+  }
+  m_t[(int64_t)g * R + r] = ni > 0 ? acc / (double)ni : 0.0;
 }
 
 // Robust scores from the row-major tensor for many regions or ranks.  A lane owns a
@@ -964,6 +997,13 @@ size_t col_scan_ws_bytes(int64_t R, int IG) {
 
 hipError_t launch_score_plain(const int64_t *T, int64_t R, int I, int G, const int32_t *it,
                               const ColMom *cm, double *m_t, hipStream_t s) {
+  // (for the call: 300,000 ranks of 8 x 5 cells 1,534 us, by ranks' rows 1,788; 40,000
+  // of 32 x 16 356 and 384; 2,000 of 64 x 5 61 and 57)
+  if (I <= 32) {
+    hipLaunchKernelGGL(score_plain_short, dim3((unsigned)((R * G + 255) / 256)), dim3(256), 0, s, T, R, I, G, it, cm,
+                       m_t);
+    return hipGetLastError();
+  }
   const unsigned gb = (unsigned)((G + 255) / 256);
   // four ranks share a column's moments once they still fill the chip
   if (R >= 2048)

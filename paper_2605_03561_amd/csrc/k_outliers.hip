@@ -2176,8 +2176,13 @@ inline bool row_major_path(int64_t R, int mode, int kind) {
          transpose_groups_of(R) <= SEG_MAX;
 }
 
-// Chunks of ranks of the plain z-score's column sums: at least 64 ranks each.
-int plain_chunks(int64_t R) { return (int)std::min<int64_t>(64, (R + 63) / 64 + (R == 0)); }
+// Chunks of ranks of the plain z-score's column sums: at least 64 ranks each, up to
+// 64 of them; rows of at most 128 cells, of which a workgroup takes several side by
+// side: at least 32 cells a thread, up to 256.
+int plain_chunks(int64_t R, int IG) {
+  const int64_t n = IG <= 128 ? std::min<int64_t>(256, R * IG / (256 * 32)) : std::min<int64_t>(64, (R + 63) / 64);
+  return (int)std::max<int64_t>(n, 1);
+}
 
 OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
   size_t off = 0;
@@ -2224,7 +2229,7 @@ OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
       w.cs.n = (int64_t *)take(IG * 8);
     } else {
       w.cm = (ColMom *)take(IG * sizeof(ColMom));
-      w.zp.rc = plain_chunks(R);
+      w.zp.rc = plain_chunks(R, (int)IG);
       w.zp.n = (int64_t *)take(IG * w.zp.rc * 8);
       w.zp.s1 = (int64_t *)take(IG * w.zp.rc * 8);
       w.zp.lo = (uint64_t *)take(IG * w.zp.rc * 8);
@@ -2455,7 +2460,7 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
       (void)hipGetDevice(&dev);
       (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
       hipError_t e = hipSuccess;
-      if (a.stats.rc > 0 && a.stats.rc != scan_stat_chunks(a.R, a.kind)) return hipErrorInvalidValue;
+      if (a.stats.rc > 0 && a.stats.rc != scan_stat_chunks(a.R, IG, a.kind)) return hipErrorInvalidValue;
       const bool reg = reg_path(a.R, a.mode, a.kind);
       if (reg && IG > 0) {
         e = launch_col_scan(a.T, a.R, a.I, a.G, a.it, a.stats, a.stats_ready, w.m_t, w.cols, cus, s);
@@ -2513,8 +2518,8 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
   return hipGetLastError();
 }
 
-int scan_stat_chunks(int64_t R, int32_t kind) {
-  if (kind != TA_SCORE_MAD) return plain_chunks(R);
+int scan_stat_chunks(int64_t R, int IG, int32_t kind) {
+  if (kind != TA_SCORE_MAD) return plain_chunks(R, IG);
   return reg_path(R, TA_SCAN_FULL, kind) ? col_stat_chunks(R) : transpose_groups_of(R);
 }
 

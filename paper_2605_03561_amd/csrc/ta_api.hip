@@ -1289,7 +1289,7 @@ ta_status ta_plan_create(ta_handle h, const ta_traces *t, const int64_t *offsets
   const bool need_rs = !d->seg.rank_sum || !d->seg.rank_sumsq;
   const bool fuse = d->with_imbalance && d->with_outliers && d->outlier_mode == TA_SCAN_FULL &&
                     R > 0 && (int64_t)I * G > 0;
-  const int rc_t = fuse ? ta::scan_stat_chunks(R, d->outlier_kind) : 0;
+  const int rc_t = fuse ? ta::scan_stat_chunks(R, I * G, d->outlier_kind) : 0;
   const size_t ws_out =
       d->with_outliers ? (ta::outliers_ws_bytes(R, I, G, d->outlier_mode, d->outlier_kind) + 255) / 256 * 256 : 0;
   const size_t ws_imb = d->with_imbalance ? ta::imbalance_ws_bytes(R, I, G, need_rs, rc_t) : 0;

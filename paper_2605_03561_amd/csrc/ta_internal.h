@@ -133,7 +133,7 @@ struct OutArgs {
   int64_t *n_flagged;
   double *region_score;
   // FULL scan: its first pass also writes the imbalance column partials here
-  // (stats.rc must be scan_stat_chunks(R, kind)).
+  // (stats.rc must be scan_stat_chunks(R, I * G, kind)).
   ColPartials stats;
   // When set (with stats), recorded on the stream right after the pass that
   // writes the imbalance partials, so a consumer on another stream can start.
@@ -147,7 +147,7 @@ struct OutArgs {
   hipEvent_t ev[10] = {};
 };
 // Rank chunks of the imbalance partials that the FULL scan's first pass writes.
-int scan_stat_chunks(int64_t R, int32_t kind);
+int scan_stat_chunks(int64_t R, int IG, int32_t kind);
 // Robust z over active ranks of per-rank region values v_t[G][R] (median and
 // MAD per region, the exact scan's second stage), z_t[G][R], and FP32
 // score[r] = max_g |z|.

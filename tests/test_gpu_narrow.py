@@ -80,3 +80,51 @@ def test_sums_of_single_cells_cost(ta, h):
     given = best_time(lambda: h.imbalance(T, rank_sum=s, rank_sumsq=q)) * 1e3
     print(f"without {without:.0f} us, given {given:.0f} us")
     assert without < 1.5 * given
+
+
+@pytest.mark.parametrize("R", [1, 2, 63, 64, 4099, 20001])
+@pytest.mark.parametrize("I,G", SHAPES + [(128, 1), (129, 1), (25, 5), (43, 3)])
+def test_plain_scores(ta, h, oracle, R, I, G):
+    """The plain scan where its column sums take several ranks' rows side by side
+    and its scores a thread per region.  Column sums are exact; a region's second
+    stage adds R scores in another order than the oracle: within R * 2^-53 of the
+    largest of them."""
+    import torch
+    T, it = tensor(np.random.default_rng([R, I, G, 1]), R, I, G)
+    dT, dit = torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda()
+    for have, dh in ((it, dit), (np.full(R, I, np.int32), None)):
+        o = h.outliers(dT, dh, kind=ta.SCORE_Z, region=True)
+        st, score, flag, nf, reg = oracle.outliers(T, have, kind=1)
+        assert st == 0
+        tol = max(R, 64) * 2.0**-53 * max(1.0, float(np.abs(reg).max()))
+        np.testing.assert_allclose(o["region_score"].cpu().numpy(), reg, rtol=1e-12, atol=tol)
+        np.testing.assert_allclose(o["rank_score"].cpu().numpy(), score, rtol=1e-12, atol=tol)
+        near = np.abs(score - 3.5) < 1e-9
+        assert np.array_equal(o["rank_flag"].cpu().numpy()[~near], flag[~near])
+        assert abs(int(o["n_flagged"].item()) - nf) <= near.sum()
+
+
+@pytest.mark.parametrize("R,I,G", [(300, 40, 5), (20000, 3, 7), (5000, 30, 16), (70000, 2, 3)])
+def test_plain_plan(ta, h, oracle, R, I, G):
+    """A plan's plain scan, whose column sums the imbalance shares."""
+    from paper_2605_03561_amd import synth
+    w = synth.plain_workload(seed=R, n_ranks=R, events=4 * I, n_nodes=60, n_iters=I, n_regions=G,
+                             mean_gap_ns=3000.0)
+    h.set_tree(w.parent)
+    h.set_regions(w.marker, w.regions)
+    p = h.plan(ta.DeviceTraces(w.offsets, w.ts, w.ctx), I, w.offsets, autotune=0, region=True,
+               kind=ta.SCORE_Z)
+    for _ in range(2):
+        p.launch()
+    h.sync_status()
+    T, it = p.seg["tensor"].cpu().numpy(), p.seg["iters_found"].cpu().numpy()
+    st, score, flag, nf, reg = oracle.outliers(T, it, kind=1)
+    assert st == 0
+    tol = R * 2.0**-53 * max(1.0, float(np.abs(reg).max()))
+    np.testing.assert_allclose(p.out["region_score"].cpu().numpy(), reg, rtol=1e-12, atol=tol)
+    _, ref = oracle.imbalance(T, it, span=p.seg["span"].cpu().numpy())
+    for k in ("min", "max"):
+        assert np.array_equal(p.imb[k].cpu().numpy(), ref[k])
+    for k in ("mean", "std", "max_minus_mean"):
+        np.testing.assert_allclose(p.imb[k].cpu().numpy(), ref[k], rtol=1e-12, atol=1e-9)
+    p.close()
