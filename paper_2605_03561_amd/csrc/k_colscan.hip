@@ -998,8 +998,9 @@ size_t col_scan_ws_bytes(int64_t R, int IG) {
 hipError_t launch_score_plain(const int64_t *T, int64_t R, int I, int G, const int32_t *it,
                               const ColMom *cm, double *m_t, hipStream_t s) {
   // (for the call: 300,000 ranks of 8 x 5 cells 1,534 us, by ranks' rows 1,788; 40,000
-  // of 32 x 16 356 and 384; 2,000 of 64 x 5 61 and 57)
-  if (I <= 32) {
+  // of 32 x 16 356 and 384; 2,000 of 64 x 5 61 and 57); also where 64 threads per
+  // rank were 2^32 and more
+  if (I <= 32 || R >= (int64_t)1 << 26) {
     hipLaunchKernelGGL(score_plain_short, dim3((unsigned)((R * G + 255) / 256)), dim3(256), 0, s, T, R, I, G, it, cm,
                        m_t);
     return hipGetLastError();

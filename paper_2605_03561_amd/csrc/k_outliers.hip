@@ -2497,7 +2497,7 @@ hipError_t launch_outliers(const OutArgs &a, void *ws, size_t ws_bytes, hipStrea
       auto go = [&](auto kern, int64_t grid) {
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, s, a.T, a.R, a.I, a.G, a.it, w.S_t);
       };
-      const int tpr = rank_sums_threads(a.I, a.G);
+      const int tpr = rank_sums_threads(a.R, a.I, a.G);
       if (tpr == 1) go(rank_totals_t<1>, (a.R * a.G + 255) / 256);
       else if (tpr == 64) go(rank_totals_t<64>, (a.R + 3) / 4);
       else go(rank_totals_t<256>, a.R);

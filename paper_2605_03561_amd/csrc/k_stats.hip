@@ -461,7 +461,7 @@ hipError_t launch_imbalance(const ImbArgs &a, void *ws, size_t ws_bytes, hipStre
     auto go = [&](auto kern, int64_t grid) {
       hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(CT), 0, s, a.T, a.R, a.I, a.G, a.it, w.S, w.Q);
     };
-    const int tpr = rank_sums_threads(a.I, a.G);
+    const int tpr = rank_sums_threads(a.R, a.I, a.G);
     if (a.R == 0) {
     } else if (tpr == 1) {
       go(rank_stats<1>, (a.R * a.G + CT - 1) / CT);

@@ -318,10 +318,12 @@ __device__ __forceinline__ void rank_region_sums_short(const int64_t *__restrict
 // iterations and does not fill a wave (40,000 ranks of 8 x 5 cells, sums and squares
 // of an imbalance: 259 us for the call, with a wave per rank 277; 300,000 of 4 x 1 1,074
 // and 1,404; of 8 x 64 1,121 and 1,087; 2,000 of 64 x 1 112 and 109), a wave while it
-// is no more than some 16 loads of it, else a workgroup.
-inline int rank_sums_threads(int I, int G) {
+// is no more than some 16 loads of it, else a workgroup.  A launch has fewer than 2^32
+// threads: of more ranks again one per region.
+inline int rank_sums_threads(int64_t R, int I, int G) {
   const int64_t IG = (int64_t)I * G;
-  return G < 64 && I <= 32 && IG <= 256 ? 1 : IG <= 1024 ? 64 : 256;
+  const int n = G < 64 && I <= 32 && IG <= 256 ? 1 : IG <= 1024 ? 64 : 256;
+  return (R + 3) * n < (int64_t)1 << 32 ? n : 1;
 }
 
 }  // namespace ta

@@ -128,3 +128,32 @@ def test_plain_plan(ta, h, oracle, R, I, G):
     for k in ("mean", "std", "max_minus_mean"):
         np.testing.assert_allclose(p.imb[k].cpu().numpy(), ref[k], rtol=1e-12, atol=1e-9)
     p.close()
+
+
+def test_more_ranks_than_waves_fit_a_launch(ta, h):
+    """70,000,000 ranks of 40 cells: 64 threads per rank would be more than a launch
+    can have.  Totals and plain scores against torch in FP64 (sums of 70,000,000
+    terms, so within 1e-6), the imbalance's mean and rank sums."""
+    import torch
+    R, I = 70_000_000, 40
+    if torch.cuda.mem_get_info()[0] < 60 << 30:
+        pytest.skip("needs 60 GB of device memory")
+    T = torch.randint(0, 1000, (R, I, 1), device="cuda")
+    S = T.sum(1)[:, 0].double()
+    z = (S - S.mean()) / S.std()
+    o = h.outliers(T, mode=ta.SCAN_TOTALS, kind=ta.SCORE_Z)
+    torch.testing.assert_close(o["rank_score"], z.abs(), rtol=1e-6, atol=1e-6)
+    cols = T[:, :, 0]
+    m = torch.zeros(R, dtype=torch.float64, device="cuda")
+    for i in range(I):
+        c = cols[:, i].double()
+        m += (c - c.mean()) / c.std()
+    m /= I
+    z = (m - m.mean()) / m.std()
+    o = h.outliers(T, kind=ta.SCORE_Z)
+    torch.testing.assert_close(o["rank_score"], z.abs(), rtol=1e-6, atol=1e-6)
+    g = h.imbalance(T)
+    torch.testing.assert_close(g["mean"][:, 0], cols.sum(0).double() / R, rtol=1e-12, atol=0)
+    h.sync_status()
+    del T, S, z, m, cols, o, g
+    torch.cuda.empty_cache()
