@@ -105,11 +105,14 @@ __device__ inline void rank_range(const int64_t *off, int64_t r, int64_t E, int6
 // first event counts as following an event outside).  The markers are staged as
 // one bit per node (MARK_LDS, up to MARK_NODES nodes).  With one wave per rank
 // the longest rank's chain of steps was the time: 1,500 ranks, 4.7e7 events 788
-// -> 139 us.
-constexpr int RT = 512;
+// -> 139 us.  Ranks of less than ROWS_WAVE events on average take a wave each all the
+// same (RT = 64, markers from the table): a workgroup per rank would hold more
+// lanes than events (200,000 ranks of 20 events 177 us, with workgroups 1,087; 16 of
+// 2,000 8.1 and 5.4).
 constexpr int MARK_NODES = 1 << 17;
+constexpr int64_t ROWS_WAVE = 1024;
 
-template <bool MARK_LDS>
+template <int RT, bool MARK_LDS>
 __global__ __launch_bounds__(RT) void nm_rows(const int64_t *__restrict__ off,
                                               const int32_t *__restrict__ ctx, int64_t R, int64_t E, int I,
                                               const uint32_t *__restrict__ info, int N,
@@ -545,8 +548,10 @@ __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
 // costs need) is then one word's count.  Durations are added to the node's
 // accumulator by LDS atomics and scanned into Q.  The tree (parent + 1 and
 // subtree end) and the position of every caller id are staged as 16-bit pairs
-// and words.  A wave takes NMB consecutive rows of its
-// workgroup's share from a counter, reads their bounds at once and loads the next row's events while it works on one.
+// and words.  A wave takes `per` consecutive rows of its workgroup's share from a
+// counter (NMB; fewer while not every wave that fits had a turn: 640 rows of 50 events
+// 31 us with 16, now 5), reads their bounds at once and loads the next row's events
+// while it works on one.
 // LO < events of a row <= CAP as above.
 //
 // Bound by the chain of LDS operations per row.  The radix sort (four phases of
@@ -556,7 +561,7 @@ __global__ __launch_bounds__(NT) void nm_short(NmArgs a) {
 // rows); this takes 353 + 826 and 310 + 636.  One counter of all workgroups for the
 // turns made each of the four kernels 300 us longer; the inclusive entries are
 // staged because written along the walks they cost the fills 170 to 260 us more.
-constexpr int NMB = 16;           // rows per turn
+constexpr int NMB = 16;           // rows per turn at most
 constexpr int NM_STAGE = 192;     // 16 waves of them beside the tables of SMALL_TAB_NODES nodes
 constexpr int BM_WORDS = SMALL_TAB_NODES / 32;
 
@@ -588,7 +593,7 @@ __device__ __forceinline__ uint64_t wave_scan_u64(uint64_t x) {
 }
 
 template <bool FILL, int CAP, int LO, int NT>
-__global__ __launch_bounds__(NT) void nm_bits(NmArgs a) {
+__global__ __launch_bounds__(NT) void nm_bits(NmArgs a, int per) {
   constexpr int NW = NT / 64, NCH = CAP / 64;
   __shared__ BitLds<CAP> lds_all[NW];
   __shared__ unsigned taken;  // turns that this workgroup's waves have taken
@@ -619,12 +624,12 @@ __global__ __launch_bounds__(NT) void nm_bits(NmArgs a) {
     unsigned turn = 0;
     if (lane == 0) turn = atomicAdd(&taken, 1u);
     turn = (unsigned)__builtin_amdgcn_readfirstlane((int)turn);
-    const int64_t q0 = ((int64_t)turn * gridDim.x + blockIdx.x) * NMB;
+    const int64_t q0 = ((int64_t)turn * gridDim.x + blockIdx.x) * per;
     if (q0 >= rows) break;
-    // lane l < NMB: the bounds of row q0 + l
+    // lane l < per: the bounds of row q0 + l
     int64_t s = 0, e = 0, re = 0;
     bool have = false;
-    if (lane < NMB && q0 + lane < rows) {
+    if (lane < per && q0 + lane < rows) {
       have = row_range(a, q0 + lane, &s, &e, &re);
       const int64_t n = e - s;
       if (!have || n <= 0) {
@@ -1104,14 +1109,14 @@ hipError_t launch_node_model(const NodeModelArgs &m, bool fill, void *ws, int cu
   a.long_cap = w.long_cap;
   a.long_ws = w.long_ws;
   if (!fill) {
-    if (m.R > 0)
-    {
-      auto go = [&](auto kern, size_t lds) {
-        hipLaunchKernelGGL(kern, dim3(grid_for(m.R, cus, 4)), dim3(RT), lds, s, m.off, m.ctx, m.R, m.E, m.I,
+    if (m.R > 0) {
+      auto go = [&](auto kern, int rt, size_t lds) {
+        hipLaunchKernelGGL(kern, dim3(grid_for(m.R, cus, 2048 / rt)), dim3(rt), lds, s, m.off, m.ctx, m.R, m.E, m.I,
                            m.info, m.N, m.row_start, m.iters_found, m.err);
       };
-      if (m.N <= MARK_NODES) go(nm_rows<true>, (size_t)((m.N + 63) / 64) * 8);
-      else go(nm_rows<false>, 0);
+      if (m.E < ROWS_WAVE * m.R) go(nm_rows<64, false>, 64, 0);
+      else if (m.N <= MARK_NODES) go(nm_rows<512, true>, 512, (size_t)((m.N + 63) / 64) * 8);
+      else go(nm_rows<512, false>, 512, 0);
     }
     // counts go to the offset arrays, then scanned in place
     a.cnt_x = m.row_off_x;
@@ -1143,16 +1148,19 @@ hipError_t launch_node_model(const NodeModelArgs &m, bool fill, void *ws, int cu
     });
     if (m.N <= SMALL_TAB_NODES) {
       const size_t tabs = ((size_t)m.N * 6 + 15) & ~(size_t)15;
-      const int64_t turns = (rows + NMB - 1) / NMB;
-      const int per1 = (int)std::max<size_t>(1, 160 * 1024 / (8 * sizeof(BitLds<64>) + tabs));
-      const int g1 = grid_for((turns + 7) / 8, cus, std::min(per1, 4));
-      const int g2 = grid_for((turns + 15) / 16, cus, 1);
+      const int wg1 = std::min((int)std::max<size_t>(1, 160 * 1024 / (8 * sizeof(BitLds<64>) + tabs)), 4);
+      auto go = [&](auto kern, int nt, int per_cu) {
+        const int waves = nt / 64;
+        const int per = (int)std::min<int64_t>(NMB, std::max<int64_t>(1, rows / ((int64_t)cus * per_cu * waves)));
+        const int64_t turns = (rows + per - 1) / per;
+        hipLaunchKernelGGL(kern, dim3(grid_for((turns + waves - 1) / waves, cus, per_cu)), dim3(nt), tabs, s, a, per);
+      };
       if (fill) {
-        hipLaunchKernelGGL((nm_bits<true, 64, 0, 512>), dim3(g1), dim3(512), tabs, s, a);
-        hipLaunchKernelGGL((nm_bits<true, SHORT_CAP, 64, 1024>), dim3(g2), dim3(1024), tabs, s, a);
+        go(nm_bits<true, 64, 0, 512>, 512, wg1);
+        go(nm_bits<true, SHORT_CAP, 64, 1024>, 1024, 1);
       } else {
-        hipLaunchKernelGGL((nm_bits<false, 64, 0, 512>), dim3(g1), dim3(512), tabs, s, a);
-        hipLaunchKernelGGL((nm_bits<false, SHORT_CAP, 64, 1024>), dim3(g2), dim3(1024), tabs, s, a);
+        go(nm_bits<false, 64, 0, 512>, 512, wg1);
+        go(nm_bits<false, SHORT_CAP, 64, 1024>, 1024, 1);
       }
     } else {
       const int g1 = grid_for((rows + 7) / 8, cus, 2), g2 = grid_for((rows + NMW - 1) / NMW, cus, 3);
