@@ -1513,8 +1513,10 @@ constexpr int S2CAP = 14336;           // interior keys held in LDS (112 KB)
 constexpr int64_t S2_MIN_N = 16384;    // fewer active ranks: radix passes only (regions
                                        // above SEL_REG_MAX ranks come here)
 constexpr size_t S2_LDS_BYTES = (size_t)S2CAP * sizeof(uint64_t);
-// Regions of up to this many ranks are selected in registers (the most that 16
-// waves hold at 32 keys per lane); longer ones by the passes over memory.
+// Regions of up to this many ranks are selected without passes over memory, by 16
+// waves of at most 32 keys per lane (of which the compiler keeps a third of a
+// lane's words in scratch at 32; 64 regions of 32,768 ranks still 124 us for 151 of
+// the passes); longer ones by the passes.
 constexpr int64_t SEL_REG_MAX = 32768;
 
 // Appends v to buf (LDS) when `in`; all lanes of the wave call it together.
@@ -2395,11 +2397,16 @@ void launch_sel_regions(const void *vals_t, int64_t R, int G, const int32_t *it,
       hipLaunchKernelGGL(kern, dim3(G), dim3(nt), 0, s, vals_t, R, G, it, I, z_t, region_score,
                          n_flagged);
     };
+    // The fewest keys per lane of 1, 4, 8, 12, 16, 24 and 32 (a lane without a key
+    // still takes every step; 64 regions, totals scan: 10,000 ranks with 16 keys 49 us,
+    // with 12 44; 20,000 with 32 91, with 24 74); 32 do not all stay in registers.
     if (R <= 256) go(sel_regions_reg<4, 1, F64>, 256);
     else if (R <= 1024) go(sel_regions_reg<4, 4, F64>, 256);
     else if (R <= 4096) go(sel_regions_reg<8, 8, F64>, 512);
     else if (R <= 8192) go(sel_regions_reg<16, 8, F64>, 1024);
+    else if (R <= 12288) go(sel_regions_reg<16, 12, F64>, 1024);
     else if (R <= 16384) go(sel_regions_reg<16, 16, F64>, 1024);
+    else if (R <= 24576) go(sel_regions_reg<16, 24, F64>, 1024);
     else go(sel_regions_reg<16, 32, F64>, 1024);
     return;
   }

@@ -171,3 +171,32 @@ def test_scores_of_many_ranks_and_regions(ta, h, oracle, R, I, G):
     it = np.where(rng.random(R) < 0.1, rng.integers(0, I + 1, R), I).astype(np.int32)
     o = h.outliers(torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda(), region=True)
     same_scan(o, oracle.outliers(T, it))
+
+
+@pytest.mark.parametrize("R", [8193, 12288, 12289, 16385, 24576, 24577, 32768])
+def test_keys_per_lane(ta, h, oracle, R):
+    """The regions' selection on both sides of 12 and 24 keys per lane, both modes,
+    with equal, spread and negative values and ranks without iterations; the
+    pre-screen's second stage and top-k against its own scores."""
+    import torch
+    rng = np.random.default_rng([R, 12])
+    I, G = 2, 5
+    T = rng.integers(0, 10**6, (R, I, G))
+    T[..., 1] = rng.integers(-2**50, 2**50, (R, I))
+    T[..., 2] = 777
+    T[..., 3] = rng.integers(0, 2, (R, I))
+    it = np.where(rng.random(R) < 0.1, rng.integers(0, I + 1, R), I).astype(np.int32)
+    dT, dit = torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda()
+    for mode in (0, 1):
+        same_scan(h.outliers(dT, dit, mode=mode, region=True), oracle.outliers(T, it, mode=mode))
+    X = torch.from_numpy(rng.integers(0, 10**6, (R, 3, 64))).cuda()
+    X[R // 3: R // 3 + 50] = X[R // 3]
+    h.ae_init(2)
+    h.ae_fit_norm(X, None)
+    h.ae_set_score_kind(ta.AE_SCORE_RESIDUAL_Z)
+    for k in (1, R // 2, R):
+        top, sc, fb = h.prescreen(X, None, k)
+        s = sc.cpu().numpy()
+        assert not fb and np.isfinite(s).all()
+        assert np.array_equal(top.cpu().numpy(), np.sort(np.lexsort((np.arange(R), -s))[:k]))
+    assert len(np.unique(s[R // 3: R // 3 + 50])) == 1
