@@ -225,7 +225,7 @@ ta_status ta_imbalance_noalloc(ta_handle h, const int64_t *tensor, int64_t n_ran
  * (TA_ERR_SIZE_OVERFLOW otherwise).  The FULL scan's workspace is about as
  * large as the tensor or smaller: none of that size for the robust kind up to
  * 1,024 ranks; up to 49,152 ranks a 32-bit column-major copy (half its size) and,
- * for tensors of up to 2^33 cells, as much again for the upper halves of columns
+ * for tensors of 2^23 to 2^33 cells, as much again for the upper halves of columns
  * that are spread over 2^31 and more; above, a 32-bit copy and a slot of 256
  * cells per column and chunk of 1,024 ranks for the bracket interiors (a quarter
  * of the tensor), plus the column samples and one gathered column per selection

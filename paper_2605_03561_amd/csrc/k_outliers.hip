@@ -2221,14 +2221,13 @@ OWs carve(void *ws, int64_t R, int I, int G, int mode, int kind, size_t *used) {
       w.Tt = (int64_t *)take((size_t)pad_ranks(R) * IG * 8);
       w.scr = (int64_t *)take((size_t)std::min<size_t>(IG, SEL_GRID_MAX) * sel_cap(R) * 8);
     }
-    if (reg_path(R, mode, kind)) {
-    } else if (kind == TA_SCORE_MAD && !row_major_path(R, mode, kind)) {
-      w.cz = (ColZ *)take(IG * sizeof(ColZ));
-    } else if (kind == TA_SCORE_MAD) {
+    if (row_major_path(R, mode, kind)) {
       w.cs.med2 = (int64_t *)take(IG * 8);
       w.cs.mad4 = (int64_t *)take(IG * 8);
       w.cs.sumdev = (int64_t *)take(IG * 8);
       w.cs.n = (int64_t *)take(IG * 8);
+    } else if (kind == TA_SCORE_MAD) {
+      if (!reg_path(R, mode, kind)) w.cz = (ColZ *)take(IG * sizeof(ColZ));
     } else {
       w.cm = (ColMom *)take(IG * sizeof(ColMom));
       w.zp.rc = plain_chunks(R, (int)IG);

@@ -139,6 +139,26 @@ def test_far_cells(ta, h, oracle, R):
         assert np.array_equal(o["rank_flag"].cpu().numpy(), flag)
 
 
+@pytest.mark.parametrize("R", [1025, 2050, 4100, 9999, 17001, 33001, 41000])
+def test_far_cells_of_larger_tensors(ta, h, oracle, R):
+    """The same columns in as many regions as make 2^23 cells, from where on wide
+    columns are copied in two halves; ranks that end early."""
+    import torch
+    rng = np.random.default_rng([R, 2])
+    cells = far_columns(rng, R)
+    I = cells.shape[1]
+    G = 2**23 // (R * I) + 2
+    T = np.repeat(cells[:, :, None], G, axis=2) + rng.integers(0, 1000, (1, I, G))
+    it = np.where(rng.random(R) < 0.15, rng.integers(0, I + 1, R), I).astype(np.int32)
+    it[0] = I
+    o = h.outliers(torch.from_numpy(T).cuda(), torch.from_numpy(it).cuda(), region=True)
+    st, score, flag, nf, reg = oracle.outliers(T, it)
+    assert st == 0
+    assert np.array_equal(o["region_score"].cpu().numpy(), reg)
+    assert np.array_equal(o["rank_score"].cpu().numpy(), score)
+    assert np.array_equal(o["rank_flag"].cpu().numpy(), flag)
+
+
 def best_time(f, n=9):
     import torch
     f()
