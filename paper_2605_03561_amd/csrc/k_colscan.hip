@@ -12,7 +12,7 @@
 //                 do not fit in 32 bits are listed there, copied in two 32-bit
 //                 halves by col_copy_wide and selected by col_select_wide
 // Everything between the count of a column and its MAD happens on registers
-// (ta_select.h).  The row-major passes of longer columns (k_outliers.hip) took
+// (ta_select.h), but for the few that the compiler keeps in scratch (sel_waves).  The row-major passes of longer columns (k_outliers.hip) took
 // 10.0 ms for 32,000 columns of 40,000 ranks where this takes 7.1.
 #include <algorithm>
 #include <type_traits>
@@ -47,11 +47,11 @@ __host__ __device__ inline int64_t copy_ranks(int64_t R) { return (R + CT - 1) /
 // Column-major copy cp[IG][copy_ranks(R)] of the tensor in 32-bit key words:
 // 64 columns x 128 ranks per workgroup, all 16 loads of a thread in flight, 512-byte pieces of rows in and of columns out.  Bound by
 // HBM (12 bytes per cell): 9,600 columns of 10,000 ranks in 229 us, 5.0 TB/s
-// (the 8-byte copy that it replaces, with the statistics, 358 us).  Several tiles
+// (an 8-byte copy, with the statistics, 358 us).  Several tiles
 // per workgroup were slower (330 -> 537 us for 16,000 ranks): one tile's loads
 // wait for the other's stores.
 // STATS: also each column's valid cells as one chunk of the imbalance partials
-// per workgroup.  The copy leaves the VALU some room for it (233 -> 279 us), the
+// per workgroup.  The copy leaves the VALU some room for it (233 -> 267 us), the
 // selection does not (206 -> 311 us).
 struct ColSum {  // exact, over any cells of one column
   int64_t s1;
@@ -420,7 +420,7 @@ constexpr int sel_waves() {
 // Columns of the 32-bit copy: W waves and V key words per lane each; a single
 // wave's columns come four to a workgroup.  Radix passes over the column in
 // memory took 566 us for 9,600 columns of 10,000 ranks and 1,296 us for 11,520
-// of 9,190; this takes 206 and 228 us, bound by its instructions (about 30 per
+// of 9,190; this takes 219 and 240 us, bound by its instructions (about 30 per
 // key) and the LDS atomics (a quarter of the time).
 template <int W, int V>
 __global__ __launch_bounds__(W > 1 ? 64 * W : 256, sel_waves<V>()) void col_select(const uint32_t *__restrict__ cp, int64_t R,
@@ -633,8 +633,10 @@ __device__ __forceinline__ int rank_iters(const int32_t *it, int64_t r, int I) {
 // region.  The region's column numbers are staged in LDS, SI iterations at a
 // time, and IU iterations' cells are loaded before the first is scored (read by
 // scalar loads, the numbers kept every iteration waiting: 1,741 ranks x 19,200
-// columns 127 -> 63 us, 10,000 x 9,600 145 -> 100 us).  Bound by the copy's 4
+// columns 127 -> 63 us, 10,000 x 9,600 145 -> 102 us).  Bound by the copy's 4
 // bytes per cell for long columns, by the loads' round trips for short ones.
+// Staged columns that are all without far cells are scored with no branch (with
+// one per column: 10,000 x 9,600 134 us).
 template <int RPL, int IU>
 __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ cp, const uint32_t *__restrict__ hi,
                                                   const int64_t *__restrict__ T, int64_t R, int I, int G, const int32_t *__restrict__ it,
@@ -656,12 +658,14 @@ __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ c
   for (int s0 = 0; s0 < I; s0 += SI) {
     const int ns = I - s0 < SI ? I - s0 : SI;
     __syncthreads();  // the previous numbers are read
+    bool near = true;
     if (tid < ns) {
       const int64_t c = (int64_t)(s0 + tid) * G + g;
       const ColZ z = cz[c];
+      near = mu[c] >= 0.0;
       num[tid] = Num{mu[c], z.zc, z.zd, z.zy};
     }
-    __syncthreads();
+    near = __syncthreads_and(near);
     for (int i0 = 0; i0 < ns; i0 += IU) {
       uint32_t w[IU][RPL];
 #pragma unroll
@@ -678,18 +682,26 @@ __global__ __launch_bounds__(256) void score_copy(const uint32_t *__restrict__ c
           w[j][0] = src[0];
         }
       }
+      auto score = [&](const Num &z, const uint32_t *x) {  // a column without far cells
+#pragma unroll
+        for (int q = 0; q < RPL; q++) {
+          // 2x - med2 in key words: both terms are integers below 2^34
+          const double d = fma(2.0, (double)x[q], -z.mu);
+          const double t = acc[q] + div_by(d * z.zc, z.zd, z.zy);
+          acc[q] = x[q] != none<uint32_t>() ? t : acc[q];
+        }
+      };
+      if (near && i0 + IU <= ns) {
+#pragma unroll
+        for (int j = 0; j < IU; j++) score(num[i0 + j], w[j]);
+        continue;
+      }
 #pragma unroll
       for (int j = 0; j < IU; j++) {
         if (i0 + j >= ns) break;
         const Num z = num[i0 + j];
         if (z.mu >= 0.0) {
-#pragma unroll
-          for (int q = 0; q < RPL; q++) {
-            // 2x - med2 in key words: both terms are integers below 2^34
-            const double d = fma(2.0, (double)w[j][q], -z.mu);
-            const double t = acc[q] + div_by(d * z.zc, z.zd, z.zy);
-            acc[q] = w[j][q] != none<uint32_t>() ? t : acc[q];
-          }
+          score(z, w[j]);
         } else if (z.mu < 0.0) {  // a column with far cells
           const int64_t c = (int64_t)(s0 + i0 + j) * G + g;
 #pragma unroll
@@ -1083,7 +1095,8 @@ hipError_t launch_col_scan(const int64_t *T, int64_t R, int I, int G, const int3
   // is a chain of barriers and exchanges, so as many columns as possible should
   // be in flight, and beside the column a lane needs 20 to 45 registers.  With
   // 24 or 32 words per lane (twice the waves, half the columns) 10,000 ranks
-  // took 311 us instead of 206, 16,000 ranks 354 instead of 261; with 16 waves of 40
+  // took 311 us instead of 206, 16,000 ranks 354 instead of 261 (before the marks of
+  // far cells, which cost 10 us); with 16 waves of 40
   // words 32,000 columns of 40,000 ranks 3.00 ms instead of 2.75 (64 registers a
   // lane, 21 of them in scratch).
   auto shape = [&](auto w, auto v) {
