@@ -230,7 +230,9 @@ ta_status ta_imbalance_noalloc(ta_handle h, const int64_t *tensor, int64_t n_ran
  * cells per column and chunk of 1,024 ranks for the bracket interiors (a quarter
  * of the tensor), plus the column samples and one gathered column per selection
  * workgroup; for the plain z-score four sums per column and chunk of ranks (at
- * most 64 chunks). */
+ * most 64 chunks; 256 for rows of at most 128 cells).  A plan's imbalance
+ * statistics take 48 bytes more per column and chunk of ranks (128 ranks from
+ * 1,025 to 49,152 ranks; 1,024 beyond). */
 enum { TA_SCAN_FULL = 0, TA_SCAN_TOTALS = 1 };
 enum { TA_SCORE_MAD = 0, TA_SCORE_Z = 1 };
 ta_status ta_outliers(ta_handle h, const int64_t *tensor, int64_t n_ranks, int32_t n_iters,

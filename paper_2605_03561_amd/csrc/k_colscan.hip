@@ -5,7 +5,7 @@
 //   up to COL_DIRECT_MAX ranks   col_select_direct reads the row-major tensor
 //                 (a workgroup's columns side by side, tiles of rows through
 //                 LDS into the registers of the wave that owns a column), and
-//                 score_tensor reads it again
+//                 score_rank (up to 256 regions; else score_tensor) reads it again
 //   more ranks    col_copy writes a column-major copy in 32-bit offsets,
 //                 col_select reads a column of it into the registers of a
 //                 workgroup, score_copy reads it again; the columns whose cells

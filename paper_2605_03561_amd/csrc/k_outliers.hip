@@ -1954,12 +1954,13 @@ __global__ __launch_bounds__(RT) void sel_regions(const void *vals_t, int64_t R,
 }
 
 // Stage 2 of the robust kind over up to 64 * W * V ranks: one workgroup of W
-// waves per region, the region's keys in registers from one read to the
+// waves per region, the region's keys by lane from one read to the
 // score.  Bound by latency (a chain of a few barriers per order statistic);
 // sel_regions' radix passes re-read every key from memory eight times per
 // order statistic and walk each histogram with one thread.  Measured, 16
 // regions: 16 ranks 174 -> 6.6 us, 64 ranks 163 -> 9.6 us; 32 regions of
-// 10,000 ranks 273 -> 44 us; 64 regions of 1,000 ranks 217 -> 14 us.
+// 10,000 ranks 273 -> 34 us; 64 regions of 1,000 ranks 217 -> 12 us.  Of 24 and 32
+// keys a lane keeps 22 to 81 registers in scratch.
 template <int W, int V, bool F64>
 __global__ __launch_bounds__(64 * W) void sel_regions_reg(const void *vals_t, int64_t R, int G,
                                                           const int32_t *it, int I, double *z_t,
@@ -2398,7 +2399,7 @@ void launch_sel_regions(const void *vals_t, int64_t R, int G, const int32_t *it,
     };
     // The fewest keys per lane of 1, 4, 8, 12, 16, 24 and 32 (a lane without a key
     // still takes every step; 64 regions, totals scan: 10,000 ranks with 16 keys 49 us,
-    // with 12 44; 20,000 with 32 91, with 24 74); 32 do not all stay in registers.
+    // with 12 44; 20,000 with 32 91, with 24 74).
     if (R <= 256) go(sel_regions_reg<4, 1, F64>, 256);
     else if (R <= 1024) go(sel_regions_reg<4, 4, F64>, 256);
     else if (R <= 4096) go(sel_regions_reg<8, 8, F64>, 512);

@@ -274,7 +274,7 @@ constexpr int64_t TABLE_MEAN = 2048, TABLE_MIN = 1 << 19, WAVE_MEAN = 512, COUNT
 // Bound by the atomics: with one on the output per event, 97,833 nodes, the
 // 3,000 ranks' events in a twentieth of the longest one's time took 629 us, all
 // events of 429 ranks (20,000 at the median, 200,000 at most) 1,001; now both
-// together take 298.
+// together take 214.
 template <bool LDSH>
 __global__ __launch_bounds__(WWT) void window_excl(const int64_t *__restrict__ ts,
                                                  const int32_t *__restrict__ ctx, int64_t E,
@@ -684,7 +684,7 @@ hipError_t launch_sparse_profiles(const int64_t *off, const int64_t *ts, const i
   if (R <= 0) return hipSuccess;
   // Ranks that take more than a step of the workgroup on average differ in how
   // many: a workgroup per rank, placed as others end (3,000 ranks of 20,000 events
-  // at the median, lognormal, over 97,833 nodes: 398 us, two workgroups per CU in
+  // at the median, lognormal, over 97,833 nodes: 420 us, two workgroups per CU in
   // turns 474; all of 20,000 events: 218 and 209).  Shorter ranks: in turns, which
   // saves the launch of a workgroup (100,000 ranks of 20 events over 5,000 nodes: 1,329
   // and 1,270 us).
